@@ -237,14 +237,11 @@ extern "C" cpic_status cpic_create(const cpic_glasma_params* gp, const cpic_part
     // more particles than sites: evaluate the fields once per site (force table)
     c->push_table = c->nc == 3 && c->np > c->V && c->pp.color_update == CPIC_COLOR_ROTATE;
     if (e == hipSuccess && c->push_table) e = hipMalloc(&c->ftab, (size_t)48 * c->V * c->tsz);
-    // field update: compressed-link LDS tiles of 64 x 8 sites (the tuner's pick
-    // at 512^2, 1-2 % per step ahead of 64 x 4).  The fused step (variant 4)
-    // is chosen explicitly: at 512^2 with 1e5 particles it computes the
-    // fields at every site of a tile, more FP64 work than the gather push's
-    // evaluation at the particles' cells (0.145 against 0.127 ms per step)
-    c->cfg.split = 3;
-    c->cfg.bx = 64;
-    c->cfg.by = 8;
+    // field update by lattice size.  The fused step (variant 4) is chosen
+    // explicitly: at 512^2 with 1e5 particles it computes the fields at every
+    // site of a tile, more FP64 work than the gather push's evaluation at the
+    // particles' cells (0.145 against 0.127 ms per step)
+    default_field_launch(c->N, &c->cfg);
     set_store_policy(c);
     c->pblocks = c->np > 0 ? push_blocks((int)c->np, c->tpp) : 0;
     c->nslots = c->np > 0 ? num_slots(c->sc) : 0;
@@ -1461,6 +1458,7 @@ extern "C" cpic_status cpic_set_launch(cpic_ctx* c, int32_t bx, int32_t by, int3
     c->cfg.by = by;
     c->cfg.xcd_remap = remap ? 1 : 0;
     c->cfg.waves = waves;
+    c->cfg.roles = 0;  // the shape as given
     drop_graphs(c);
     return CPIC_OK;
 }
@@ -1516,7 +1514,11 @@ extern "C" cpic_status cpic_timing(cpic_ctx* c, double* field_ms, double* push_m
 // field kernel reads the current buffer and writes the free one (the step is
 // not advanced); the push runs on a saved copy of the particle records, which
 // is restored after every trial.  The fastest configuration is kept.
-static const char* const kVariantName[5] = {"site", "link", "tile", "ctile", "fused"};
+static const char* variant_name(const LaunchCfg& cfg)
+{
+    static const char* const name[5] = {"site", "link", "tile", "ctile", "fused"};
+    return cfg.split == 3 && cfg.roles ? "roles" : name[cfg.split];
+}
 
 template <typename T> static cpic_status tune_t(cpic_ctx* c, int reps, std::string& rep)
 {
@@ -1548,6 +1550,8 @@ template <typename T> static cpic_status tune_t(cpic_ctx* c, int reps, std::stri
     const int cshapes[][2] = {{64, 4}, {32, 8}, {16, 16}, {32, 4}, {64, 8}};
     for (const auto& sh : cshapes)
         for (int remap = 0; remap <= 1; remap++) cands.push_back(LaunchCfg{sh[0], sh[1], remap, 1, 3});
+    cands.push_back(LaunchCfg{64, 4, 1, 1, 3});
+    cands.back().roles = 1;
     for (LaunchCfg& cfg : cands) cfg.nt_store = c->cfg.nt_store;
     for (const LaunchCfg& cfg : cands) {
                 HIPCHK(c, launch_field_step<T>(A, B, G, c->N, c->sc, c->d_step, cfg, c->st), "tune");  // warm-up
@@ -1560,14 +1564,14 @@ template <typename T> static cpic_status tune_t(cpic_ctx* c, int reps, std::stri
                 HIPCHK(c, hipEventElapsedTime(&ms, e0, e1), "tune");
                 const double per = ms / reps;
                 std::snprintf(line, sizeof line, "field %s bx=%d by=%d waves=%d remap=%d: %.2f us\n",
-                              kVariantName[cfg.split], cfg.bx, cfg.by, cfg.waves, cfg.xcd_remap, per * 1e3);
+                              variant_name(cfg), cfg.bx, cfg.by, cfg.waves, cfg.xcd_remap, per * 1e3);
                 rep += line;
                 if (per < best_ms) { best_ms = per; best = cfg; }
                 timed.push_back({per, cfg});
             }
     c->cfg = best;
     std::snprintf(line, sizeof line, "best field: %s bx=%d by=%d waves=%d remap=%d %.2f us%s\n",
-                  kVariantName[best.split], best.bx, best.by, best.waves, best.xcd_remap, best_ms * 1e3,
+                  variant_name(best), best.bx, best.by, best.waves, best.xcd_remap, best_ms * 1e3,
                   best.split == 3 && best.nt_store ? " (non-temporal stores of the new state)" : "");
     rep += line;
     const int lanes[4] = {1, 2, 4, 8};
@@ -1696,7 +1700,7 @@ template <typename T> static cpic_status tune_t(cpic_ctx* c, int reps, std::stri
             const LaunchCfg keep = c->cfg;
             auto same = [](const LaunchCfg& a, const LaunchCfg& b) {
                 return a.bx == b.bx && a.by == b.by && a.xcd_remap == b.xcd_remap && a.waves == b.waves &&
-                       a.split == b.split && a.nt_store == b.nt_store;
+                       a.split == b.split && a.nt_store == b.nt_store && a.roles == b.roles;
             };
             // the trials: the three fastest in isolation with both store
             // policies, and the configuration before tuning
@@ -1765,7 +1769,7 @@ template <typename T> static cpic_status tune_t(cpic_ctx* c, int reps, std::stri
                     if (ls) { c->cfg = keep; (void)restore(); release(); return ls; }
                     if (te != hipSuccess) break;
                     std::snprintf(line, sizeof line, "step with field %s bx=%d by=%d waves=%d remap=%d nt=%d: %.2f us\n",
-                                  kVariantName[cfg.split], cfg.bx, cfg.by, cfg.waves, cfg.xcd_remap, cfg.nt_store,
+                                  variant_name(cfg), cfg.bx, cfg.by, cfg.waves, cfg.xcd_remap, cfg.nt_store,
                                   per * 1e3);
                     rep += line;
                     if (per < best_pair) { best_pair = per; best_step = cfg; }
@@ -1815,7 +1819,7 @@ template <typename T> static cpic_status tune_t(cpic_ctx* c, int reps, std::stri
             if (te != hipSuccess) { c->cfg = keep; return hip_fail(c, te, "tune"); }
             std::snprintf(line, sizeof line,
                           "chosen: field %s bx=%d by=%d waves=%d remap=%d nt=%d, push lanes=%d, step %.2f us\n",
-                          kVariantName[best_step.split], best_step.bx, best_step.by, best_step.waves,
+                          variant_name(best_step), best_step.bx, best_step.by, best_step.waves,
                           best_step.xcd_remap, best_step.nt_store, c->tpp, best_pair * 1e3);
             rep += line;
         }

@@ -88,7 +88,31 @@ struct LaunchCfg {
                           // 3 as 2 with two rows per link in LDS and the scalars from global memory,
                           // 4 as 3 with the particle push of the tile in the same kernel (fused.hip)
     int nt_store = 0;     // variant 3 with particles: the new links and phi stored non-temporal
+    int roles = 0;        // variant 3: four wavefronts per 64 sites instead of one (small lattices; bx, by unused)
 };
+// The field update of a new context, by lattice size (both precisions).  Up to
+// 384^2 the chip is short of wavefronts and four of them share 64 sites; above
+// that, one thread per site, in tiles of 64 x 8 where they fill the 256 CUs in
+// one or two whole rounds (one such workgroup per CU: a partly filled last
+// round leaves most CUs idle, and with more rounds two smaller workgroups per CU
+// overlap staging and arithmetic better), else 64 x 4.  Measured per step, FP64,
+// particles at 0.35 per site, four wavefronts per 64 sites / 64 x 8 / 64 x 4:
+// 384^2 70.2 / 81.0 / 72.7 us, 432^2 81.6 / 87.4 / 81.6, 486^2 103.6 / 106.4 /
+// 104.2, 512^2 123.0 / 110.0 / 110.9, 576^2 168.2 / 148.7 / 146.3, 768^2 313.5 /
+// 294.2 / 283.2, 1024^2 557.2 / 525.4 / 515.6; FP32: 384^2 46.3 / 50.0 / 47.9,
+// 512^2 66.2 / 63.4 / 63.7, 864^2 208.7 / 182.3 / 175.2.
+inline void default_field_launch(int N, LaunchCfg* cfg)
+{
+    cfg->split = 3;
+    cfg->bx = 64;
+    cfg->by = 4;
+    if (N <= 384) {
+        cfg->roles = 1;
+        return;
+    }
+    const int tiles = ((N + 63) / 64) * ((N + 7) / 8);
+    if (tiles == 256 || tiles == 512) cfg->by = 8;
+}
 
 struct PushArgs {
     int N, np, is_static;
