@@ -126,6 +126,23 @@ static void set_store_policy(cpic_ctx* c)
     c->cfg.nt_store = (c->np > 0 || c->jets) && reals * (double)c->tsz > 256.0 * 1024 * 1024;
 }
 
+// Wavefronts per group of 64 particles (tunable with cpic_tune).  Four shorten
+// each wavefront's chain of gathers and let the group's wavefronts share the
+// lines they fetch.  Measured push times, four against two and one: FP64
+// rotation at 1024^2 with 4e5 particles 250 / 288 / 327 us, with 1e6 418 / 423 /
+// 436, at 512^2 with 262144 88 / 99 / 96; FP32 at 1024^2 with 1e6 241 / 274 / 282,
+// at 512^2 with 1e6 188 / 217 / 216.  One is ahead in FP64 above a particle per
+// site (512^2, 1e6: 322 / 321 / 301; the default there is the force table), and
+// for the logarithm update, whose owner wavefront has the longest chain, from
+// about half a particle per site (512^2, 262144: 155 / 125 / 119; 1024^2, 4e5: 301 /
+// 320 / 388; below 1e5 particles four cover the latency).
+static int default_push_lanes(const cpic_ctx* c)
+{
+    if (c->nc == 2) return 1;
+    if (c->pp.color_update == CPIC_COLOR_LOG) return c->np <= (1 << 17) || 2 * c->np <= c->V ? 4 : 1;
+    return c->prec == CPIC_FP64 && c->np > (1 << 18) && c->np > c->V ? 1 : 4;
+}
+
 extern "C" cpic_status cpic_create(const cpic_glasma_params* gp, const cpic_particle_params* pp, void* hip_stream,
                                    cpic_ctx** out)
 {
@@ -231,9 +248,7 @@ extern "C" cpic_status cpic_create(const cpic_glasma_params* gp, const cpic_part
             if (e == hipSuccess) e = hipMemsetAsync(c->d_strag_total, 0, sizeof(unsigned long long), c->st);
         }
     }
-    // few particles: several wavefronts share each particle group so that the
-    // push still fills the 1024 SIMDs (tunable with cpic_tune)
-    c->tpp = c->nc == 2 ? 1 : (c->np <= (1 << 18) ? 4 : (c->np <= (1 << 20) ? 2 : 1));
+    c->tpp = default_push_lanes(c);
     // more particles than sites: evaluate the fields once per site (force table)
     c->push_table = c->nc == 3 && c->np > c->V && c->pp.color_update == CPIC_COLOR_ROTATE;
     if (e == hipSuccess && c->push_table) e = hipMalloc(&c->ftab, (size_t)48 * c->V * c->tsz);
