@@ -70,6 +70,7 @@ struct cpic_batch {
     EventDesc* d_desc = nullptr;
     std::vector<EventDesc> desc;  // host copy (kept alive for the asynchronous upload)
     std::map<std::vector<int>, Plan> plans;
+    ICWorkspace icw{};  // of the events' initial conditions, made one after the other
     std::string err;
 };
 
@@ -276,6 +277,7 @@ extern "C" cpic_status cpic_batch_create(int32_t n_events, const cpic_glasma_par
         // the batch launches its own kernels over all events: the events'
         // records keep the gather push's order
         if (c->cfg.split == 4) c->cfg.split = 3;
+        c->icw = &b->icw;
         b->ev.push_back(c);
     }
     // compressed-link LDS tiles of 64 x 4 sites (cpic_batch_tune picks among the shapes)
@@ -650,6 +652,7 @@ extern "C" void cpic_batch_destroy(cpic_batch* b)
     }
     if (b->ev_fork) (void)hipEventDestroy(b->ev_fork);
     for (auto c : b->ev) cpic_destroy(c);
+    b->icw.release();
     if (b->own_stream) (void)hipStreamDestroy(b->st);
     delete b;
 }

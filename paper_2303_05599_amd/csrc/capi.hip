@@ -109,6 +109,7 @@ static void free_all(cpic_ctx* c)
     (void)hipFree(c->sb.count); (void)hipFree(c->sb.offs);
     (void)hipFree(c->tile_start); (void)hipFree(c->strag); (void)hipFree(c->strag_count);
     (void)hipFree(c->d_strag_total);
+    c->icw_own.release();
     if (c->own_stream && c->st) (void)hipStreamDestroy(c->st);
 }
 
@@ -309,9 +310,7 @@ extern "C" const char* cpic_last_error(const cpic_ctx* c) { return c ? c->err.c_
 static cpic_status reset_pid(cpic_ctx* c)
 {
     if (c->np <= 0) return CPIC_OK;
-    std::vector<int> iota(c->np);
-    for (int64_t p = 0; p < c->np; p++) iota[p] = (int)p;
-    HIPCHK(c, hipMemcpy(c->pid, iota.data(), sizeof(int) * iota.size(), hipMemcpyHostToDevice), "pid");
+    HIPCHK(c, launch_iota(c->pid, (int)c->np, c->st), "pid");
     c->static_sorted = false;
     c->sorted_at = -1;
     c->sort_tx = c->sort_ty = 0;
@@ -414,6 +413,27 @@ static cpic_status reset_counters(cpic_ctx* c, int n)
     return CPIC_OK;
 }
 
+// the initial condition of the fields (into buffer 0) and the particles
+template <typename T> static cpic_status enqueue_ic(cpic_ctx* c, const ICArgs& a)
+{
+    hipError_t e = c->nc == 2 ? ic_glasma2<T>(a, *c->icw, F2<T>(c, 0), c->st)
+                              : ic_glasma<T>(a, *c->icw, F<T>(c, 0), c->d_fails, c->st);
+    if (e == hipSuccess && c->np > 0) {
+        PartICArgs pa{};
+        pa.N = c->N;
+        pa.np = (int)c->np;
+        pa.azimuth_uniform = c->pp.azimuth_uniform;
+        pa.seed = c->pp.seed;
+        pa.pt_min = c->pp.pT_min_GeV * c->a_gev;
+        pa.pt_max = c->pp.pT_max_GeV * c->a_gev;
+        for (int k = 0; k < 8; k++) pa.q0[k] = c->q0[k];
+        T* r = static_cast<T*>(c->pr);
+        e = c->nc == 2 ? ic_particles2<T>(pa, c->q2ref, r, c->pcell, c->st) : ic_particles<T>(pa, r, c->pcell, c->st);
+    }
+    if (e != hipSuccess) return hip_fail(c, e, "cpic_init_mv");
+    return CPIC_OK;
+}
+
 extern "C" cpic_status cpic_init_mv(cpic_ctx* c)
 {
     if (!c) return fail(nullptr, CPIC_E_INVALID, "cpic_init_mv: NULL context");
@@ -426,52 +446,22 @@ extern "C" cpic_status cpic_init_mv(cpic_ctx* c)
     a.uvhat = c->gp.uv_GeV > 0 ? c->gp.uv_GeV * c->a_gev : 0.0;
     a.tol = 1e-14;
     a.maxit = 50;
-    void* dbl = c->fbuf[0];
-    void* stage = nullptr;
-    if (c->prec == CPIC_FP32) {
-        HIPCHK(c, hipMalloc(&stage, sizeof(double) * c->rps * c->V), "IC staging");
-        dbl = stage;
-    }
     HIPCHK(c, hipMemsetAsync(c->d_fails, 0, sizeof(int), c->st), "IC");
-    hipError_t e = c->nc == 2 ? ic_glasma2(a, fields2_at<double>(dbl, c->V), c->st)
-                              : ic_glasma(a, fields_at<double>(dbl, c->V), c->d_fails, c->st);
-    if (e == hipSuccess && c->prec == CPIC_FP32)
-        e = convert_to_float((const double*)stage, (float*)c->fbuf[0], (size_t)c->rps * c->V, c->st);
-    if (e == hipSuccess && c->np > 0) {
-        PartICArgs pa{};
-        pa.N = c->N;
-        pa.np = (int)c->np;
-        pa.azimuth_uniform = c->pp.azimuth_uniform;
-        pa.seed = c->pp.seed;
-        pa.pt_min = c->pp.pT_min_GeV * c->a_gev;
-        pa.pt_max = c->pp.pT_max_GeV * c->a_gev;
-        for (int k = 0; k < 8; k++) pa.q0[k] = c->q0[k];
-        double* pdst = (double*)c->pr;
-        void* pstage = nullptr;
-        if (c->prec == CPIC_FP32) {
-            e = hipMalloc(&pstage, sizeof(double) * kPartReals * c->np);
-            pdst = (double*)pstage;
-        }
-        if (e == hipSuccess)
-            e = c->nc == 2 ? ic_particles2(pa, c->q2ref, pdst, c->pcell, c->st) : ic_particles(pa, pdst, c->pcell, c->st);
-        if (e == hipSuccess && c->prec == CPIC_FP32)
-            e = convert_to_float(pdst, (float*)c->pr, (size_t)kPartReals * c->np, c->st);
-        if (e == hipSuccess) e = hipStreamSynchronize(c->st);
-        (void)hipFree(pstage);
+    cpic_status s = c->prec == CPIC_FP64 ? enqueue_ic<double>(c, a) : enqueue_ic<float>(c, a);
+    if (s) {
+        (void)hipStreamSynchronize(c->st);
+        return s;
     }
-    if (e == hipSuccess) e = hipStreamSynchronize(c->st);
-    (void)hipFree(stage);
-    if (e != hipSuccess) return hip_fail(c, e, "cpic_init_mv");
-    int fails = 0;
-    HIPCHK(c, hipMemcpy(&fails, c->d_fails, sizeof(int), hipMemcpyDeviceToHost), "IC");
-    c->cur = 0;
-    c->initialised = true;
-    cpic_status s = reset_counters(c, 0);
-    if (s) return s;
+    int* fails = static_cast<int*>(c->h_stage);
+    HIPCHK(c, hipMemcpyAsync(fails, c->d_fails, sizeof(int), hipMemcpyDeviceToHost, c->st), "IC");
     s = reset_pid(c);
     if (s) return s;
-    if (fails) return fail(c, CPIC_E_IC_NEWTON, "cpic_init_mv: initial-link Newton solve failed on " +
-                                                    std::to_string(fails) + " links");
+    c->cur = 0;
+    c->initialised = true;
+    s = reset_counters(c, 0);  // synchronises
+    if (s) return s;
+    if (*fails) return fail(c, CPIC_E_IC_NEWTON, "cpic_init_mv: initial-link Newton solve failed on " +
+                                                     std::to_string(*fails) + " links");
     return CPIC_OK;
 }
 

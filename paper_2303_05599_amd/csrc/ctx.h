@@ -54,6 +54,8 @@ struct cpic_ctx {
     int* d_step = nullptr;
     int* d_err = nullptr;
     int* d_fails = nullptr;
+    cpic::ICWorkspace icw_own{};             // of a single event
+    cpic::ICWorkspace* icw = &icw_own;       // an event of a batch uses the batch's
     double* dpart = nullptr;  // diagnostics partials
     double* dout = nullptr;   // diagnostics results [8 + 2]
     int dcap = 0;

@@ -1,16 +1,20 @@
 // ic.hip -- MV-model initial condition on the GPU (Sec. II, II.A) and the
 // test-particle initial conditions (Sec. III.B, IV.B).  Always double
-// precision; a float run converts the finished state.
+// precision; a float run rounds the finished values.
 //
-//   charges   Gaussian colour charges per sheet from Philox4x64-10
-//   Poisson   2-D FFT (rows in LDS, mixed radix 2/3/4 Stockham) -> multiply by
-//             1/(khat^2 + m^2) with the zero mode and the modes above the UV
-//             cut removed -> inverse FFT
-//   Wilson    V^+(x) <- V^+(x) exp(-i alpha_n(x)), sheets in order
+//   rows      Gaussian colour charges per sheet from Philox4x64-10 and their
+//             transform along x, of which only the columns below the UV cut
+//             are stored
+//   columns   transform along y, times 1/(khat^2 + m^2) with the zero mode and
+//             the modes above the UV cut removed, and back along y
+//   Wilson    the inverse transform along x and, without storing alpha,
+//             V^+(x) <- V^+(x) exp(-i alpha_n(x)), sheets in order
 //   links     U^X_i(x) = V(x) V(x+i)^+, then the tau = 0 Glasma links from the
 //             lattice initial condition, solved per link by Newton's method
 //   pi(0)     from U, U^A, U^B
-#include <vector>
+// The transforms are mixed-radix (8, 4, 2, 3) Stockham FFTs in LDS.
+#include <algorithm>
+#include <type_traits>
 
 #include "internal.h"
 #include "philox.h"
@@ -21,36 +25,16 @@ namespace cpic {
 
 using d2 = double2;
 
-// ------------------------------------------------------------------ charges
-// out[(sheet*pairs + pair)*V + s] = (rho^{2 pair}, rho^{2 pair + 1}) for the
-// sheet index sheet0 + sheet of nucleus `nucleus`; stream key (seed,
-// 1 + nucleus), counter (s, sheet, block, 0), block b holding colours
-// 4b .. 4b+3.  pairs = 4 for SU(3) (colours 0..7), 2 for SU(2) (colours 0..2
-// and an unused fourth).
-__global__ void charges_kernel(d2* out, int V, uint64_t seed, int nucleus, int sheet0, double sigma, int pairs)
-{
-    const int s = blockIdx.x * blockDim.x + threadIdx.x;
-    const int sh = blockIdx.y;
-    if (s >= V) return;
-    double z[8];
-    for (int b = 0; b < 2; b++) {
-        if (2 * b >= pairs) break;
-        const u64x4 r = philox4x64((uint64_t)s, (uint64_t)(sheet0 + sh), (uint64_t)b, 0, seed, 1 + (uint64_t)nucleus);
-        box_muller(r.v[0], r.v[1], z[4 * b], z[4 * b + 1]);
-        box_muller(r.v[2], r.v[3], z[4 * b + 2], z[4 * b + 3]);
-    }
-    for (int p = 0; p < pairs; p++)
-        out[((size_t)sh * pairs + p) * V + s] = make_double2(sigma * z[2 * p], sigma * z[2 * p + 1]);
-}
-
 // ------------------------------------------------------------------ FFT
+// Stages of a length-N transform, largest radix first.
 struct Radices {
     int n;
-    int r[20];
+    int r[10];
 };
 static Radices radices_of(int N)
 {
     Radices R{};
+    while (N % 8 == 0) { R.r[R.n++] = 8; N /= 8; }
     while (N % 4 == 0) { R.r[R.n++] = 4; N /= 4; }
     while (N % 2 == 0) { R.r[R.n++] = 2; N /= 2; }
     while (N % 3 == 0) { R.r[R.n++] = 3; N /= 3; }
@@ -64,29 +48,66 @@ __device__ __forceinline__ d2 ad(d2 a, d2 b) { return make_double2(a.x + b.x, a.
 __device__ __forceinline__ d2 sb(d2 a, d2 b) { return make_double2(a.x - b.x, a.y - b.y); }
 __device__ __forceinline__ d2 mul_i(d2 a, double sg) { return make_double2(-sg * a.y, sg * a.x); }  // (sg i) a
 
-// The radices of the stages packed two bits each (R - 2), first stage lowest:
-// the kernels read them from one register instead of indexing an array.
+// The radices packed four bits each, first stage lowest: the kernels read them
+// from one register instead of indexing an array.
 static unsigned radix_code(const Radices& R)
 {
     unsigned c = 0;
-    for (int s = R.n - 1; s >= 0; s--) c = (c << 2) | (unsigned)(R.r[s] - 2);
+    for (int s = R.n - 1; s >= 0; s--) c = (c << 4) | (unsigned)R.r[s];
     return c;
 }
-__device__ __forceinline__ int stage_radix(unsigned code, int stg) { return (int)((code >> (2 * stg)) & 3u) + 2; }
+__device__ __forceinline__ int stage_radix(unsigned code, int stg) { return (int)((code >> (4 * stg)) & 15u); }
+
+// One transform as the kernels take it: its stages and the twiddle table of
+// its direction.  inv_r[s] = 1 / (N / R), inv_ns[s] = 1 / Ns of stage s, for the
+// divisions of small integers by floating-point products.
+struct Fft {
+    const d2* tw;
+    unsigned code;
+    int n;
+    float inv_r[7], inv_ns[7];
+};
+static Fft make_fft(const d2* tw, int N, const Radices& R)
+{
+    Fft f{};
+    f.tw = tw;
+    f.code = radix_code(R);
+    f.n = R.n;
+    int Ns = 1;
+    for (int s = 0; s < R.n; s++) {
+        f.inv_r[s] = 1.0f / (float)(N / R.r[s]);
+        f.inv_ns[s] = 1.0f / (float)Ns;
+        Ns *= R.r[s];
+    }
+    return f;
+}
+// LDS place of entry i: one entry of padding per eight.  The first stage's
+// outputs lie R entries (R = 8: 128 bytes, all the banks once) apart from lane to
+// lane; unpadded, every lane of a store would use the same banks.
+__host__ __device__ constexpr int lds_at(int i) { return i + (i >> 3); }
+// a / b for 0 <= a < 2^16 and inv = 1 / b in single precision: (a + 1/2) / b is
+// at least 1 / (2 b) away from an integer, above the product's rounding error
+__device__ __forceinline__ int small_div(int a, float inv) { return (int)(((float)a + 0.5f) * inv); }
 
 // The twiddle factors of every stage (R, Ns) of the Stockham FFT below,
-// tw[(Ns - 1) + k (R - 1) + q - 1] = exp(sign 2 pi i k q / (Ns R)) for k < Ns
-// and 1 <= q < R.  The stages' entries follow one another without gaps, since
-// the Ns of a stage is the product of the radices before it: N - 1 in all.
-// Made once per initial condition (one block), so that the butterflies read
-// their factors instead of evaluating a sine and a cosine each.
-__global__ void twiddle_kernel(d2* tw, int nstages, unsigned rcode, int sign)
+// tw[(Ns - 1) + (q - 1) Ns + k] = exp(sign 2 pi i k q / (Ns R)) for k < Ns and
+// 1 <= q < R: k fastest, so that the butterflies of a wavefront read
+// consecutive entries.  The stages' entries follow one another without gaps,
+// since the Ns of a stage is the product of the radices before it: N - 1 in all.
+// Made once per initial condition, so that the butterflies read their factors
+// instead of evaluating a sine and a cosine each.  Block 0 makes the table of
+// the forward transforms and block 1 that of the inverse ones in the same stage
+// order, block 2 that of the inverse in the opposite order.
+__global__ void twiddle_kernel(d2* tw, int N, int nstages, unsigned rcode, unsigned rcode_back)
 {
+    const unsigned code = blockIdx.x == 2 ? rcode_back : rcode;
+    const int sign = blockIdx.x == 0 ? -1 : 1;
+    tw += (size_t)blockIdx.x * N;
     int Ns = 1;
     for (int stg = 0; stg < nstages; stg++) {
-        const int R = stage_radix(rcode, stg);
+        const int R = stage_radix(code, stg);
         for (int t = threadIdx.x; t < Ns * (R - 1); t += blockDim.x) {
-            const int k = t / (R - 1), q = t % (R - 1) + 1;
+            const int k = t % Ns, q = t / Ns + 1;
             double sn, cs;
             sincospi((double)sign * 2.0 * (double)(k * q) / (double)(Ns * R), &sn, &cs);
             tw[Ns - 1 + t] = make_double2(cs, sn);
@@ -95,107 +116,271 @@ __global__ void twiddle_kernel(d2* tw, int nstages, unsigned rcode, int sign)
     }
 }
 
-// One radix-R stage of the Stockham FFT: butterfly j < N / R takes the inputs
-// j + q N / R, multiplies them by the twiddles of its k = j mod Ns, and writes
-// the R outputs to (j - k) R + k + q Ns.
-template <int R>
-__device__ __forceinline__ void fft_stage(const d2* __restrict__ in, d2* __restrict__ out, int N, int Ns, double sg,
-                                          const d2* __restrict__ tw)
+// DFT of R values, sign sg
+template <int R> __device__ __forceinline__ void dft(d2 (&v)[R], double sg)
 {
-    const int NR = N / R;
-    for (int j = threadIdx.x; j < NR; j += blockDim.x) {
-        const int k = (int)((unsigned)j % (unsigned)Ns);
-        d2 v[R];
+    if constexpr (R == 2) {
+        const d2 t = v[0];
+        v[0] = ad(t, v[1]);
+        v[1] = sb(t, v[1]);
+    } else if constexpr (R == 3) {
+        const d2 t = ad(v[1], v[2]);
+        const d2 m = make_double2(v[0].x - 0.5 * t.x, v[0].y - 0.5 * t.y);
+        const d2 dd = sb(v[1], v[2]);
+        const d2 d = mul_i(make_double2(0.86602540378443864676 * dd.x, 0.86602540378443864676 * dd.y), sg);
+        v[0] = ad(v[0], t);
+        v[1] = ad(m, d);
+        v[2] = sb(m, d);
+    } else if constexpr (R == 4) {
+        const d2 a = ad(v[0], v[2]), b = sb(v[0], v[2]), c = ad(v[1], v[3]), d = mul_i(sb(v[1], v[3]), sg);
+        v[0] = ad(a, c);
+        v[1] = ad(b, d);
+        v[2] = sb(a, c);
+        v[3] = sb(b, d);
+    } else {
+        static_assert(R == 8, "radix 2, 3, 4 or 8");
+        d2 e[4] = {v[0], v[2], v[4], v[6]}, o[4] = {v[1], v[3], v[5], v[7]};
+        dft<4>(e, sg);
+        dft<4>(o, sg);
+        constexpr double h = 0.70710678118654752440;
+        // times exp(sg i pi q / 4)
+        o[1] = make_double2(h * (o[1].x - sg * o[1].y), h * (o[1].y + sg * o[1].x));
+        o[2] = mul_i(o[2], sg);
+        o[3] = make_double2(h * (-o[3].x - sg * o[3].y), h * (-o[3].y + sg * o[3].x));
 #pragma unroll
-        for (int q = 0; q < R; q++) v[q] = in[j + q * NR];
-        if (Ns > 1) {
-            const d2* w = tw + (Ns - 1) + k * (R - 1) - 1;
-#pragma unroll
-            for (int q = 1; q < R; q++) v[q] = cm(v[q], w[q]);
+        for (int q = 0; q < 4; q++) {
+            v[q] = ad(e[q], o[q]);
+            v[q + 4] = sb(e[q], o[q]);
         }
-        d2 o[R];
-        if constexpr (R == 2) {
-            o[0] = ad(v[0], v[1]);
-            o[1] = sb(v[0], v[1]);
-        } else if constexpr (R == 4) {
-            const d2 a = ad(v[0], v[2]), b = sb(v[0], v[2]), c = ad(v[1], v[3]), d = mul_i(sb(v[1], v[3]), sg);
-            o[0] = ad(a, c); o[2] = sb(a, c); o[1] = ad(b, d); o[3] = sb(b, d);
-        } else {
-            static_assert(R == 3, "radix 2, 3 or 4");
-            const d2 t = ad(v[1], v[2]);
-            const d2 m = make_double2(v[0].x - 0.5 * t.x, v[0].y - 0.5 * t.y);
-            const d2 dd = sb(v[1], v[2]);
-            const d2 d = mul_i(make_double2(0.86602540378443864676 * dd.x, 0.86602540378443864676 * dd.y), sg);
-            o[0] = ad(v[0], t); o[1] = ad(m, d); o[2] = sb(m, d);
-        }
-        const int base = (j - k) * R + k;
-#pragma unroll
-        for (int q = 0; q < R; q++) out[base + q * Ns] = o[q];
     }
 }
 
-// One complex DFT of length N per block (X[k] = sum_n x[n] exp(sign 2 pi i n k / N)),
-// Stockham autosort stages in LDS (2 N complex values, dynamic), twiddles from
-// the table of twiddle_kernel for this sign.
-__global__ __launch_bounds__(256) void fft_rows_kernel(d2* data, int N, int sign, int nstages, unsigned rcode,
-                                                       const d2* __restrict__ tw)
+// One radix-R stage of the Stockham FFT on nb transforms: butterfly j < N / R
+// takes the inputs j + q N / R, multiplies them by the twiddles of its k = j mod
+// Ns, and writes the R outputs to (j - k) R + k + q Ns.  load(b, i) and
+// store(b, i, value) reach entry i of transform b.  The threads take the
+// butterflies with j fastest, or, with BFAST, the transform fastest (nb = 1 << bsh).
+// A thread holds all its butterflies (about VALS values; nb N <= VALS blockDim)
+// across a barrier between its loads and its stores, so one LDS buffer serves
+// both; with VALS = 0 the stage goes from one buffer to another instead, which
+// keeps fewer registers.  The stage ends with a barrier: every thread of the
+// workgroup calls it.
+template <int R, bool BFAST, int VALS, typename L, typename S, typename P>
+__device__ __forceinline__ void fft_stage(int nb, int bsh, int N, int Ns, float inv_r, float inv_ns, double sg,
+                                          const d2* __restrict__ tw, L load, S store, P mid)
 {
-    extern __shared__ d2 lds[];
-    d2 *a = lds, *b = lds + N;
-    d2* row = data + (size_t)blockIdx.x * N;
-    for (int i = threadIdx.x; i < N; i += blockDim.x) a[i] = row[i];
-    __syncthreads();
-    int Ns = 1;
-    const double sg = sign;
-    for (int stg = 0; stg < nstages; stg++) {
-        const int R = stage_radix(rcode, stg);
-        if (R == 4) fft_stage<4>(a, b, N, Ns, sg, tw);
-        else if (R == 2) fft_stage<2>(a, b, N, Ns, sg, tw);
-        else fft_stage<3>(a, b, N, Ns, sg, tw);
+    constexpr int M = VALS > 0 ? (VALS + R - 1) / R : 1;
+    const int NR = N / R, total = nb * NR;
+    if constexpr (VALS == 0) {
+        for (int i = threadIdx.x; i < total; i += blockDim.x) {
+            const int b = BFAST ? i & (nb - 1) : small_div(i, inv_r), j = BFAST ? i >> bsh : i - b * NR;
+            const int k = Ns > 1 ? j - Ns * small_div(j, inv_ns) : 0;
+            d2 v[R];
+#pragma unroll
+            for (int q = 0; q < R; q++) v[q] = load(b, j + q * NR);
+            if (Ns > 1) {
+                const d2* w = tw + (Ns - 1) + k;
+#pragma unroll
+                for (int q = 1; q < R; q++) v[q] = cm(v[q], w[(q - 1) * Ns]);
+            }
+            dft<R>(v, sg);
+            const int base = (j - k) * R + k;
+#pragma unroll
+            for (int q = 0; q < R; q++) store(b, base + q * Ns, v[q]);
+        }
         __syncthreads();
-        d2* t = a;
-        a = b;
-        b = t;
-        Ns *= R;
+        return;
     }
-    for (int i = threadIdx.x; i < N; i += blockDim.x) row[i] = a[i];
-}
-
-// out[f][c][r] = in[f][r][c]
-__global__ void transpose_kernel(const d2* __restrict__ in, d2* __restrict__ out, int N)
-{
-    __shared__ d2 tile[32][33];
-    const size_t f = blockIdx.z, off = f * (size_t)N * N;
-    const int c0 = blockIdx.x * 32, r0 = blockIdx.y * 32;
-    for (int k = threadIdx.y; k < 32; k += blockDim.y) {
-        const int r = r0 + k, c = c0 + threadIdx.x;
-        if (r < N && c < N) tile[k][threadIdx.x] = in[off + (size_t)r * N + c];
+    d2 v[M][R];
+#pragma unroll
+    for (int m = 0; m < M; m++) {
+        const int i = (int)threadIdx.x + m * (int)blockDim.x;
+        if (i >= total) break;
+        const int b = BFAST ? i & (nb - 1) : small_div(i, inv_r), j = BFAST ? i >> bsh : i - b * NR;
+#pragma unroll
+        for (int q = 0; q < R; q++) v[m][q] = load(b, j + q * NR);
+        if (Ns > 1) {
+            const d2* w = tw + (Ns - 1) + (j - Ns * small_div(j, inv_ns));
+#pragma unroll
+            for (int q = 1; q < R; q++) v[m][q] = cm(v[m][q], w[(q - 1) * Ns]);
+        }
+        dft<R>(v[m], sg);
+        mid(b, j, v[m]);
     }
     __syncthreads();
-    for (int k = threadIdx.y; k < 32; k += blockDim.y) {
-        const int r = c0 + k, c = r0 + threadIdx.x;
-        if (r < N && c < N) out[off + (size_t)r * N + c] = tile[threadIdx.x][k];
+#pragma unroll
+    for (int m = 0; m < M; m++) {
+        const int i = (int)threadIdx.x + m * (int)blockDim.x;
+        if (i >= total) break;
+        const int b = BFAST ? i & (nb - 1) : small_div(i, inv_r), j = BFAST ? i >> bsh : i - b * NR;
+        const int k = Ns > 1 ? j - Ns * small_div(j, inv_ns) : 0, base = (j - k) * R + k;
+#pragma unroll
+        for (int q = 0; q < R; q++) store(b, base + q * Ns, v[m][q]);
     }
+    __syncthreads();
+}
+template <bool BFAST = false, int VALS = 8, typename L, typename S>
+__device__ __forceinline__ void fft_any(int R, int nb, int bsh, int N, int Ns, float inv_r, float inv_ns, double sg,
+                                        const d2* __restrict__ tw, L load, S store)
+{
+    auto none = [](int, int, auto&) {};
+    if (R == 8) fft_stage<8, BFAST, VALS>(nb, bsh, N, Ns, inv_r, inv_ns, sg, tw, load, store, none);
+    else if (R == 4) fft_stage<4, BFAST, VALS>(nb, bsh, N, Ns, inv_r, inv_ns, sg, tw, load, store, none);
+    else if (R == 2) fft_stage<2, BFAST, VALS>(nb, bsh, N, Ns, inv_r, inv_ns, sg, tw, load, store, none);
+    else fft_stage<3, BFAST, VALS>(nb, bsh, N, Ns, inv_r, inv_ns, sg, tw, load, store, none);
 }
 
-// multiply by K(k1,k2) = 1/(khat^2 + m^2), khat^2 = 4 sum_i sin^2(pi k_i/N); K = 0 at
-// k = 0 and where the continuum |k| = (2 pi/N) |k~| exceeds the UV cut (k~ signed)
-__global__ void poisson_kernel(d2* data, int N, int nfields, double mhat, double uvhat, double scale)
+// ------------------------------------------------------------------ Poisson
+// The modes along x that the UV cut leaves: |k~| <= kc, nk = 2 kc + 1 columns
+// (all N where nothing is cut), column c < nk holding k = c for c <= kc and
+// k = N - nk + c above.  Spectral planes are [plane][y][nk].
+struct Band {
+    int nk, kc;
+};
+static Band band_of(int N, double uvhat)
 {
-    const size_t V = (size_t)N * N;
-    const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= V * nfields) return;
-    const int e = (int)(i % V);
-    const int k1 = e / N, k2 = e % N;
+    int kc = N / 2;
+    if (uvhat > 0)
+        while (kc > 0 && (2.0 * M_PI / N) * kc > uvhat) kc--;
+    if (2 * kc + 1 >= N) return {N, N};
+    return {2 * kc + 1, kc};
+}
+__host__ __device__ inline int column_mode(int c, int N, int nk, int kc) { return c <= kc ? c : N - nk + c; }
+
+// K[c][k2] = 1/(khat^2 + m^2), khat^2 = 4 sum_i sin^2(pi k_i/N), of the stored columns;
+// K = 0 at k = 0 and where the continuum |k| = (2 pi/N) |k~| exceeds the UV cut (k~ signed)
+__global__ void poisson_kernel(double* K, int N, int nk, int kc, double mhat, double uvhat)
+{
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= nk * N) return;
+    const int k1 = column_mode(i / N, N, nk, kc), k2 = i % N;
     const double s1 = sinpi((double)k1 / N), s2 = sinpi((double)k2 / N);
-    double K = 1.0 / (4.0 * (s1 * s1 + s2 * s2) + mhat * mhat);
-    if (k1 == 0 && k2 == 0) K = 0.0;
+    double v = 1.0 / (4.0 * (s1 * s1 + s2 * s2) + mhat * mhat);
+    if (k1 == 0 && k2 == 0) v = 0.0;
     if (uvhat > 0) {
         const double q1 = k1 > N / 2 ? k1 - N : k1, q2 = k2 > N / 2 ? k2 - N : k2;
-        if ((2.0 * M_PI / N) * sqrt(q1 * q1 + q2 * q2) > uvhat) K = 0.0;
+        if ((2.0 * M_PI / N) * sqrt(q1 * q1 + q2 * q2) > uvhat) v = 0.0;
     }
-    d2 v = data[i];
-    data[i] = make_double2(v.x * K * scale, v.y * K * scale);
+    K[i] = v;
+}
+
+// Charges and their transform along x.  Colours are paired: plane
+// sheet * pairs + pair holds rho^{2 pair} + i rho^{2 pair + 1} of sheet sheet0 +
+// sheet of nucleus `nucleus`; stream key (seed, 1 + nucleus), counter (s, sheet,
+// block, 0), Philox block b giving the four normals of pairs 2b and 2b + 1
+// (SU(3): blocks 0, 1; SU(2): block 0, whose fourth normal is unused).  A
+// workgroup makes both pairs of one Philox block on RB rows in LDS and
+// transforms the 2 RB rows there; only the kept columns go to memory.
+// Bound: arithmetic (Philox, Box-Muller).  36 KB of LDS (RB N <= 1024 sites),
+// four workgroups per CU.
+__global__ __launch_bounds__(256) void rows_forward_kernel(d2* __restrict__ out, int N, int nk, int kc, uint64_t seed,
+                                                           int nucleus, int sheet0, double sigma, int pairs, int RB,
+                                                           Fft f)
+{
+    __shared__ d2 lds[lds_at(2 * 1024)];
+    const int blocks = pairs / 2, sheet = (int)blockIdx.y / blocks, pb = (int)blockIdx.y - sheet * blocks;
+    const int y0 = (int)blockIdx.x * RB, rows = min(RB, N - y0);
+    for (int i = threadIdx.x; i < rows * N; i += blockDim.x) {
+        const u64x4 r = philox4x64((uint64_t)(y0 * N + i), (uint64_t)(sheet0 + sheet), (uint64_t)pb, 0, seed,
+                                   1 + (uint64_t)nucleus);
+        double z[4];
+        box_muller(r.v[0], r.v[1], z[0], z[1]);
+        box_muller(r.v[2], r.v[3], z[2], z[3]);
+        lds[lds_at(i)] = make_double2(sigma * z[0], sigma * z[1]);             // transforms 0 .. rows - 1: pair 2 pb
+        lds[lds_at(rows * N + i)] = make_double2(sigma * z[2], sigma * z[3]);  // rows .. 2 rows - 1: pair 2 pb + 1
+    }
+    __syncthreads();
+    d2* const plane = out + (size_t)(sheet * pairs + 2 * pb) * N * nk + (size_t)y0 * nk;
+    int Ns = 1;
+    auto load = [&](int t, int i) { return lds[lds_at(t * N + i)]; };
+    auto keep = [&](int t, int i, d2 v) { lds[lds_at(t * N + i)] = v; };
+    auto emit = [&](int t, int i, d2 v) {
+        if (i > kc && i < N - nk + kc + 1) return;  // cut
+        const int second = t >= rows, c = i <= kc ? i : i - (N - nk);
+        plane[(size_t)second * N * nk + (size_t)(t - second * rows) * nk + c] = v;
+    };
+    for (int s = 0; s < f.n; s++) {
+        const int R = stage_radix(f.code, s);
+        if (s + 1 < f.n) fft_any(R, 2 * rows, 0, N, Ns, f.inv_r[s], f.inv_ns[s], -1.0, f.tw, load, keep);
+        else fft_any(R, 2 * rows, 0, N, Ns, f.inv_r[s], f.inv_ns[s], -1.0, f.tw, load, emit);
+        Ns *= R;
+    }
+}
+
+// Transform along y, times K, and back, in place, for nb = 1 << bsh columns of
+// one plane per workgroup (the columns past nk repeat the last one and store
+// nothing).  The inverse runs its stages in the opposite order: its first stage
+// takes the same R modes as the last forward stage produces, so the two and the
+// multiplication between them need no exchange.  Memory is one read and one
+// write of the kept columns.  f: the forward transform; g: the inverse.
+template <int NT>
+__global__ __launch_bounds__(NT) void columns_kernel(d2* __restrict__ data, int N, int nk, int bsh,
+                                                     const double* __restrict__ Ktab, double scale, Fft f, Fft g)
+{
+    // nb N <= 8 NT entries, one of padding per column
+    __shared__ d2 lds[lds_at(8 * NT + 32)];
+    const int nb = 1 << bsh, ngroups = (nk + nb - 1) >> bsh;
+    // consecutive column groups share lines: keep them on one XCD
+    const int per = (ngroups + 7) / 8, grp = ((int)blockIdx.x & 7) * per + ((int)blockIdx.x >> 3);
+    if (grp >= ngroups) return;
+    const int c0 = grp << bsh, P = N + 1;
+    d2* const plane = data + (size_t)blockIdx.y * N * nk + c0;
+    const int last = nk - 1 - c0;  // the last column of the plane, from c0
+    auto gload = [&](int b, int i) { return plane[(size_t)i * nk + min(b, last)]; };
+    auto gstore = [&](int b, int i, d2 v) {
+        if (b <= last) plane[(size_t)i * nk + b] = v;
+    };
+    auto lload = [&](int b, int i) { return lds[lds_at(b * P + i)]; };
+    auto lstore = [&](int b, int i, d2 v) { lds[lds_at(b * P + i)] = v; };
+    int Ns = 1;
+    for (int s = 0; s + 1 < f.n; s++) {
+        const int R = stage_radix(f.code, s);
+        if (s == 0) fft_any<true>(R, nb, bsh, N, Ns, f.inv_r[s], f.inv_ns[s], -1.0, f.tw, gload, lstore);
+        else fft_any<true>(R, nb, bsh, N, Ns, f.inv_r[s], f.inv_ns[s], -1.0, f.tw, lload, lstore);
+        Ns *= R;
+    }
+    {
+        // the last forward stage (k = j), K, and the first inverse stage, whose
+        // output q of butterfly j is entry j R + q
+        const int R = stage_radix(f.code, f.n - 1), s = f.n - 1;
+        auto turn = [&](auto ld, auto st) {
+            auto solve = [&](int b, int j, auto& v) {
+                constexpr int RR = sizeof(v) / sizeof(d2);
+                const double* K = Ktab + (size_t)(c0 + min(b, last)) * N + j;
+#pragma unroll
+                for (int q = 0; q < RR; q++) {
+                    const double k = K[q * (N / RR)];
+                    v[q] = make_double2(v[q].x * k * scale, v[q].y * k * scale);
+                }
+                dft<RR>(v, 1.0);
+            };
+            // outputs come as (j - k) R + k + q Ns = j + q Ns: back to j R + q
+            auto flip = [&](auto RC) {
+                constexpr int RR = decltype(RC)::value;
+                auto st2 = [&](int b, int i, d2 v) {
+                    const int q = small_div(i, f.inv_r[s]);
+                    st(b, (i - q * (N / RR)) * RR + q, v);
+                };
+                fft_stage<RR, true, 8>(nb, bsh, N, Ns, f.inv_r[s], f.inv_ns[s], -1.0, f.tw, ld, st2, solve);
+            };
+            if (R == 8) flip(std::integral_constant<int, 8>{});
+            else if (R == 4) flip(std::integral_constant<int, 4>{});
+            else if (R == 2) flip(std::integral_constant<int, 2>{});
+            else flip(std::integral_constant<int, 3>{});
+        };
+        if (f.n == 1) {
+            turn(gload, gstore);  // N of one stage: every butterfly is a whole column
+            return;
+        }
+        turn(lload, lstore);
+        Ns = R;
+    }
+    for (int s = 1; s < g.n; s++) {
+        const int R = stage_radix(g.code, s);
+        if (s + 1 < g.n) fft_any<true>(R, nb, bsh, N, Ns, g.inv_r[s], g.inv_ns[s], 1.0, g.tw, lload, lstore);
+        else fft_any<true>(R, nb, bsh, N, Ns, g.inv_r[s], g.inv_ns[s], 1.0, g.tw, lload, gstore);
+        Ns *= R;
+    }
 }
 
 // ------------------------------------------------------------------ Wilson lines
@@ -213,38 +398,7 @@ __device__ __forceinline__ void stM(double* p, int s, int V, const m3<double>& m
     }
 }
 
-__global__ void identity_kernel(double* M, int V)
-{
-    const int s = blockIdx.x * blockDim.x + threadIdx.x;
-    if (s < V) stM(M, s, V, identity<double>());
-}
-
-// Vdag(x) <- Vdag(x) exp(-i alpha_n(x)) for the sheets of one chunk, in order
-__global__ void wilson_kernel(const d2* __restrict__ alpha, int nsh, int V, double* Vdag)
-{
-    const int s = blockIdx.x * blockDim.x + threadIdx.x;
-    if (s >= V) return;
-    m3<double> v = ldM(Vdag, s, V);
-    for (int sh = 0; sh < nsh; sh++) {
-        a8<double> a;
-        for (int p = 0; p < 4; p++) {
-            const d2 w = alpha[((size_t)sh * 4 + p) * V + s];
-            a.v[2 * p] = w.x;
-            a.v[2 * p + 1] = w.y;
-        }
-        v = mul(v, expi(a, -1.0));
-    }
-    stM(Vdag, s, V, v);
-}
-
-// SU(2): V^+ as quaternions [4][V]; colours (0, 1) from pair 0, colour 2 from pair 1
-__global__ void identity2_kernel(double* Q, int V)
-{
-    const int s = blockIdx.x * blockDim.x + threadIdx.x;
-    if (s >= V) return;
-    Q[s] = 1.0;
-    Q[(size_t)V + s] = Q[2 * (size_t)V + s] = Q[3 * (size_t)V + s] = 0.0;
-}
+// SU(2): V^+ as quaternions [4][V]
 __device__ __forceinline__ q4<double> ldQ(const double* p, int s, int V)
 {
     return {p[s], p[(size_t)V + s], p[2 * (size_t)V + s], p[3 * (size_t)V + s]};
@@ -256,32 +410,118 @@ __device__ __forceinline__ void stQ(double* p, int s, int V, const q4<double>& q
     p[2 * (size_t)V + s] = q.y;
     p[3 * (size_t)V + s] = q.z;
 }
-__global__ void wilson2_kernel(const d2* __restrict__ alpha, int nsh, int V, double* Vdag)
+
+// The inverse transform along x and the Wilson lines: a workgroup owns RB whole
+// rows (one thread per site, SPT where a row is longer than the workgroup) and
+// takes the sheets of its segment (blockIdx.y) in order.  Per sheet it reads the
+// kept columns of the planes, transforms them in LDS, and every thread
+// multiplies V^+(x) <- V^+(x) exp(-i alpha_n(x)), kept in registers.  out[segment]
+// receives the product of the segment's sheets.  Bound: the FP64 arithmetic of
+// the exponentials and the LDS traffic of the transforms, about equal.
+template <int NC, int SITES>
+__global__ __launch_bounds__(SITES > 512 ? 512 : SITES, SITES > 512 ? 2 : 4) void rows_wilson_kernel(
+    const d2* __restrict__ spec, int N, int nk, int kc, int RB, int nsh, int seg_len, double* __restrict__ out, Fft f)
 {
-    const int s = blockIdx.x * blockDim.x + threadIdx.x;
-    if (s >= V) return;
-    q4<double> v = ldQ(Vdag, s, V);
-    for (int sh = 0; sh < nsh; sh++) {
-        const d2 w0 = alpha[((size_t)sh * 2) * V + s], w1 = alpha[((size_t)sh * 2 + 1) * V + s];
-        v = qmul(v, qexpi(v3<double>{{w0.x, w0.y, w1.x}}, -1.0));
+    constexpr int PAIRS = NC == 2 ? 2 : 4, SPT = SITES > 512 ? 2 : 1, MW = NC == 2 ? 4 : 18;
+    __shared__ d2 lds[2][PAIRS * SITES];
+    const int V = N * N, y0 = (int)blockIdx.x * RB, rows = min(RB, N - y0), ns = rows * N;
+    const int first = (int)blockIdx.y * seg_len, last = min(nsh, first + seg_len);
+    m3<double> v[SPT];
+    q4<double> w[SPT];
+#pragma unroll
+    for (int k = 0; k < SPT; k++) {
+        v[k] = identity<double>();
+        w[k] = qone<double>();
     }
-    stQ(Vdag, s, V, v);
+    // transform b = pair * rows + row
+    const float inv_rows = 1.0f / (float)rows;
+    for (int sh = first; sh < last; sh++) {
+        const d2* const plane = spec + (size_t)sh * PAIRS * N * nk + (size_t)y0 * nk;
+        auto gload = [&](int b, int i) {
+            if (i > kc && i < N - nk + kc + 1) return make_double2(0.0, 0.0);
+            const int p = small_div(b, inv_rows), c = i <= kc ? i : i - (N - nk);
+            return plane[(size_t)p * N * nk + (size_t)(b - p * rows) * nk + c];
+        };
+        int Ns = 1;
+        for (int s = 0; s < f.n; s++) {
+            const int R = stage_radix(f.code, s);
+            const d2* a = lds[(s & 1) ^ 1];
+            d2* b = lds[s & 1];
+            auto lload = [&](int t, int i) { return a[t * N + i]; };
+            auto lstore = [&](int t, int i, d2 x) { b[t * N + i] = x; };
+            if (s == 0) fft_any<false, 0>(R, PAIRS * rows, 0, N, Ns, f.inv_r[s], f.inv_ns[s], 1.0, f.tw, gload, lstore);
+            else fft_any<false, 0>(R, PAIRS * rows, 0, N, Ns, f.inv_r[s], f.inv_ns[s], 1.0, f.tw, lload, lstore);
+            Ns *= R;
+        }
+        const d2* const alpha = lds[(f.n - 1) & 1];
+#pragma unroll
+        for (int k = 0; k < SPT; k++) {
+            const int t = (int)threadIdx.x + k * (int)blockDim.x;
+            if (t >= ns) continue;
+            if constexpr (NC == 2) {
+                const d2 w0 = alpha[t], w1 = alpha[ns + t];
+                w[k] = qmul(w[k], qexpi(v3<double>{{w0.x, w0.y, w1.x}}, -1.0));
+            } else {
+                a8<double> x;
+#pragma unroll
+                for (int p = 0; p < PAIRS; p++) {
+                    const d2 z = alpha[p * ns + t];
+                    x.v[2 * p] = z.x;
+                    x.v[2 * p + 1] = z.y;
+                }
+                v[k] = mul(v[k], expi(x, -1.0));
+            }
+        }
+        __syncthreads();  // the next sheet's first stage overwrites a buffer
+    }
+    out += (size_t)blockIdx.y * MW * V;
+#pragma unroll
+    for (int k = 0; k < SPT; k++) {
+        const int t = (int)threadIdx.x + k * (int)blockDim.x;
+        if (t >= ns) continue;
+        if constexpr (NC == 2) stQ(out, y0 * N + t, V, w[k]);
+        else stM(out, y0 * N + t, V, v[k]);
+    }
 }
 
-// U^X_i(x) = V(x) V(x+i)^+ = (V^+(x))^+ V^+(x+i)
-__global__ void pure_gauge_kernel(const double* __restrict__ Vdag, int N, double* UX)
+// Vdag <- [Vdag] seg_0 seg_1 ... (with Vdag in front unless `fresh`)
+template <int NC>
+__global__ void join_segments_kernel(const double* __restrict__ seg, int nseg, int V, int fresh, double* Vdag)
 {
-    const int V = N * N;
     const int s = blockIdx.x * blockDim.x + threadIdx.x;
     if (s >= V) return;
-    const int x = s % N, y = s / N;
-    const int sx = y * N + (x + 1 == N ? 0 : x + 1), sy = (y + 1 == N ? 0 : y + 1) * N + x;
-    const m3<double> here = ldM(Vdag, s, V);
-    stM(UX, s, V, adj_mul(here, ldM(Vdag, sx, V)));
-    stM(UX + 18 * (size_t)V, s, V, adj_mul(here, ldM(Vdag, sy, V)));
+    if constexpr (NC == 2) {
+        q4<double> q = fresh ? ldQ(seg, s, V) : ldQ(Vdag, s, V);
+        for (int k = fresh ? 1 : 0; k < nseg; k++) q = qmul(q, ldQ(seg + (size_t)k * 4 * V, s, V));
+        stQ(Vdag, s, V, q);
+    } else {
+        m3<double> m = fresh ? ldM(seg, s, V) : ldM(Vdag, s, V);
+        for (int k = fresh ? 1 : 0; k < nseg; k++) m = mul(m, ldM(seg + (size_t)k * 18 * V, s, V));
+        stM(Vdag, s, V, m);
+    }
 }
 
-// rows 1, 2 by Gram-Schmidt, row 3 = conj(r1 x r2)
+// the pure-gauge link U^X_i(x) = V(x) V(x+i)^+ = (V^+(x))^+ V^+(x+i) of sites s and s+i
+__device__ __forceinline__ m3<double> pure_link(const double* Vdag, int s, int si, int V)
+{
+    return adj_mul(ldM(Vdag, s, V), ldM(Vdag, si, V));
+}
+__device__ __forceinline__ q4<double> pure_link2(const double* Vdag, int s, int si, int V)
+{
+    return qmul(qadj(ldQ(Vdag, s, V)), ldQ(Vdag, si, V));
+}
+// the neighbours of site s at +i and -i
+__device__ __forceinline__ int site_up(int s, int i, int N)
+{
+    const int x = s % N, y = s / N;
+    return i == 0 ? y * N + (x + 1 == N ? 0 : x + 1) : (y + 1 == N ? 0 : y + 1) * N + x;
+}
+__device__ __forceinline__ int site_down(int s, int i, int N)
+{
+    const int x = s % N, y = s / N;
+    return i == 0 ? y * N + (x == 0 ? N - 1 : x - 1) : (y == 0 ? N - 1 : y - 1) * N + x;
+}
+
 // Gaussian elimination with partial pivoting, unrolled so that J stays in
 // registers: the pivot (the first largest |J[r][c]|, r >= c) is brought up by
 // conditional swaps instead of an indexed row exchange.
@@ -324,13 +564,14 @@ __device__ __forceinline__ int solve8(double (&J)[8][8], double (&b)[8], double 
 // tau = 0 links: Newton on Proj[(U^A + U^B)(1 + U^+)] = 0 in the coordinates of
 // U = exp(iX) U_0, Jacobian columns Proj[-i W U^+ T^b] (W = U^A + U^B), start at
 // the row-projected W; stop at |F|_inf < tol or when the step is at rounding level
-__global__ __launch_bounds__(128) void links_kernel(const double* __restrict__ UA, const double* __restrict__ UB, int V, double tol,
+__global__ __launch_bounds__(128) void links_kernel(const double* __restrict__ VA, const double* __restrict__ VB, int N, double tol,
                              int maxit, double* U, int* fails)
 {
+    const int V = N * N;
     const int id = blockIdx.x * blockDim.x + threadIdx.x;
     if (id >= 2 * V) return;
-    const int i = id / V, s = id % V;
-    const m3<double> A = ldM(UA + (size_t)i * 18 * V, s, V), B = ldM(UB + (size_t)i * 18 * V, s, V);
+    const int i = id / V, s = id % V, si = site_up(s, i, N);
+    const m3<double> A = pure_link(VA, s, si, V), B = pure_link(VB, s, si, V);
     m3<double> W;
     for (int c = 0; c < 9; c++) W.e[c] = {A.e[c].re + B.e[c].re, A.e[c].im + B.e[c].im};
     m3<double> u = reunitarize(W);
@@ -365,19 +606,19 @@ __global__ __launch_bounds__(128) void links_kernel(const double* __restrict__ U
 }
 
 // pi(x) = (1/2) sum_i Proj[(U_i(x)-1)(U^B_i(x)^+ - U^A_i(x)^+) + (U_i(x-i)^+ - 1)(U^B_i(x-i) - U^A_i(x-i))]
-__global__ void pi0_kernel(const double* __restrict__ UA, const double* __restrict__ UB, const double* __restrict__ U,
-                           int N, double* pi)
+template <typename T>
+__global__ __launch_bounds__(128) void pi0_kernel(const double* __restrict__ VA, const double* __restrict__ VB,
+                                                  const double* __restrict__ U, int N, T* pi)
 {
     const int V = N * N;
     const int s = blockIdx.x * blockDim.x + threadIdx.x;
     if (s >= V) return;
-    const int x = s % N, y = s / N;
     m3<double> acc;
     for (int c = 0; c < 9; c++) acc.e[c] = {0, 0};
     for (int i = 0; i < 2; i++) {
-        const int sm = i == 0 ? y * N + (x == 0 ? N - 1 : x - 1) : (y == 0 ? N - 1 : y - 1) * N + x;
+        const int sm = site_down(s, i, N), sp = site_up(s, i, N);
         const size_t o = (size_t)i * 18 * V;
-        m3<double> u = ldM(U + o, s, V), a = ldM(UA + o, s, V), b = ldM(UB + o, s, V);
+        m3<double> u = ldM(U + o, s, V), a = pure_link(VA, s, sp, V), b = pure_link(VB, s, sp, V);
         m3<double> L = u, R;
         L.e[0].re -= 1; L.e[4].re -= 1; L.e[8].re -= 1;
         for (int c = 0; c < 9; c++) {  // U^B^+ - U^A^+
@@ -385,7 +626,7 @@ __global__ void pi0_kernel(const double* __restrict__ UA, const double* __restri
             R.e[c] = {b.e[tr].re - a.e[tr].re, -(b.e[tr].im - a.e[tr].im)};
         }
         m3<double> P1 = mul(L, R);
-        u = ldM(U + o, sm, V); a = ldM(UA + o, sm, V); b = ldM(UB + o, sm, V);
+        u = ldM(U + o, sm, V); a = pure_link(VA, sm, s, V); b = pure_link(VB, sm, s, V);
         L = adj(u);
         L.e[0].re -= 1; L.e[4].re -= 1; L.e[8].re -= 1;
         for (int c = 0; c < 9; c++) R.e[c] = {b.e[c].re - a.e[c].re, b.e[c].im - a.e[c].im};
@@ -396,13 +637,13 @@ __global__ void pi0_kernel(const double* __restrict__ UA, const double* __restri
         }
     }
     const a8<double> p = proj(acc);
-    for (int a = 0; a < 8; a++) pi[(size_t)a * V + s] = 0.5 * p.v[a];
+    for (int a = 0; a < 8; a++) pi[(size_t)a * V + s] = (T)(0.5 * p.v[a]);
 }
 
-__global__ void zero_kernel(double* p, size_t n)
+template <typename T> __global__ void zero_kernel(T* p, size_t n)
 {
     const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = 0.0;
+    if (i < n) p[i] = T(0);
 }
 
 // ------------------------------------------------------------------ particles
@@ -410,7 +651,7 @@ __global__ void zero_kernel(double* p, size_t n)
 // Blocks 1..5: normals; the 3x3 complex Ginibre matrix Z takes entry (r,c)
 // from normals 2(3r+c), 2(3r+c)+1; its columns orthonormalised by modified
 // Gram-Schmidt give a Haar unitary (positive R diagonal), Q = U Q0 U^+.
-__global__ void particles_kernel(PartICArgs a, double* r, int* cell)
+template <typename T> __global__ void particles_kernel(PartICArgs a, T* r, int* cell)
 {
     const int p = blockIdx.x * blockDim.x + threadIdx.x;
     const int np = a.np, N = a.N;
@@ -451,12 +692,12 @@ __global__ void particles_kernel(PartICArgs a, double* r, int* cell)
     for (int c = 0; c < 8; c++) q0.v[c] = a.q0[c];
     const a8<double> Q = transport(G, q0);
     const double cph = cos(phi0), sph = sin(phi0);
-    auto col = [&](int c) -> double& { return r[(size_t)c * np + p]; };
-    col(PX_) = x; col(PY_) = y; col(PETA_) = 0;
-    col(PPX) = pt * cph; col(PPY) = pt * sph; col(PPETA) = 0; col(PDETA) = 0;
-    col(PUX0) = cph; col(PUY0) = sph; col(PPT0) = pt;
-    col(PPTAU) = 0.0;  // set by the push at the formation step
-    for (int c = 0; c < 8; c++) col(PQ0 + c) = Q.v[c];
+    auto col = [&](int c) -> T& { return r[(size_t)c * np + p]; };
+    col(PX_) = T(x); col(PY_) = T(y); col(PETA_) = T(0);
+    col(PPX) = T(pt * cph); col(PPY) = T(pt * sph); col(PPETA) = T(0); col(PDETA) = T(0);
+    col(PUX0) = T(cph); col(PUY0) = T(sph); col(PPT0) = T(pt);
+    col(PPTAU) = T(0.0);  // set by the push at the formation step
+    for (int c = 0; c < 8; c++) col(PQ0 + c) = T(Q.v[c]);
     int nx = (int)floor(x + 0.5), ny = (int)floor(y + 0.5);
     cell[p] = nx >= N ? nx - N : nx;
     cell[np + p] = ny >= N ? ny - N : ny;
@@ -469,184 +710,217 @@ __global__ void convert_kernel(const double* __restrict__ s, float* __restrict__
 }
 
 // ------------------------------------------------------------------ drivers
+static hipError_t convert_to_float(const double* src, float* dst, size_t n, hipStream_t st)
+{
+    if (!n) return hipSuccess;
+    hipLaunchKernelGGL(convert_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, src, dst, n);
+    return hipGetLastError();
+}
+
 #define CK(x)                                \
     do {                                     \
         hipError_t e_ = (x);                 \
         if (e_ != hipSuccess) return e_;     \
     } while (0)
 
-// the forward and inverse twiddle tables (2 N entries, freed by the caller)
-static hipError_t make_twiddles(d2** tw, int N, const Radices& R, hipStream_t st)
-{
-    CK(hipMalloc(tw, sizeof(d2) * 2 * N));
-    hipLaunchKernelGGL(twiddle_kernel, dim3(1), dim3(256), 0, st, *tw, R.n, radix_code(R), -1);
-    hipLaunchKernelGGL(twiddle_kernel, dim3(1), dim3(256), 0, st, *tw + N, R.n, radix_code(R), +1);
-    return hipGetLastError();
-}
+// Spectral planes are made, solved and consumed in chunks of sheets of at most
+// this much memory: a chunk then stays in the last-level cache from one kernel
+// to the next.
+constexpr size_t kChunkBytes = (size_t)64 << 20;
 
-// one nucleus: Wilson line V^+ of its sheets (SU(3): [18][V] matrices; SU(2):
-// [4][V] quaternions)
-// tw: the twiddle tables of the forward (first N entries) and inverse transforms
-static hipError_t nucleus_wilson(const ICArgs& a, int nucleus, d2* buf, d2* tmp, int chunk, double* Vdag,
-                                 const Radices& R, const d2* tw, hipStream_t st, int nc = 3)
+// The parts of the workspace of an initial condition
+struct ICWork {
+    d2 *tw, *spec;             // twiddle tables [3][N], spectral planes of a chunk
+    double *K, *seg, *VA, *VB; // Poisson factors, segment products, Wilson lines
+    double* U;                 // links in double precision (single-precision runs)
+};
+
+// The Wilson lines V^+ of both nuclei (SU(3): [18][V] matrices; SU(2): [4][V]
+// quaternions).
+template <int NC>
+static hipError_t wilson_lines(const ICArgs& a, ICWorkspace& ws, bool double_links, ICWork& w, hipStream_t st)
 {
+    constexpr int pairs = NC == 2 ? 2 : 4, MW = NC == 2 ? 4 : 18;
     const int N = a.N, V = N * N;
-    const int pairs = nc == 2 ? 2 : 4;
-    const size_t lds = (size_t)2 * N * sizeof(d2);
-    const unsigned rc = radix_code(R);
-    const double sigma = a.g2mua / sqrt((double)a.n_sheets);
-    if (nc == 2) hipLaunchKernelGGL(identity2_kernel, dim3((V + 255) / 256), dim3(256), 0, st, Vdag, V);
-    else hipLaunchKernelGGL(identity_kernel, dim3((V + 255) / 256), dim3(256), 0, st, Vdag, V);
-    for (int s0 = 0; s0 < a.n_sheets; s0 += chunk) {
-        const int nsh = a.n_sheets - s0 < chunk ? a.n_sheets - s0 : chunk;
-        const int nf = pairs * nsh;
-        hipLaunchKernelGGL(charges_kernel, dim3((V + 255) / 256, nsh), dim3(256), 0, st, buf, V, a.seed, nucleus, s0,
-                           sigma, pairs);
-        hipLaunchKernelGGL(fft_rows_kernel, dim3(nf * N), dim3(256), lds, st, buf, N, -1, R.n, rc, tw);
-        hipLaunchKernelGGL(transpose_kernel, dim3((N + 31) / 32, (N + 31) / 32, nf), dim3(32, 8), 0, st, buf, tmp, N);
-        hipLaunchKernelGGL(fft_rows_kernel, dim3(nf * N), dim3(256), lds, st, tmp, N, -1, R.n, rc, tw);
-        const size_t tot = (size_t)V * nf;
-        hipLaunchKernelGGL(poisson_kernel, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, st, tmp, N, nf, a.mhat,
-                           a.uvhat, 1.0 / ((double)N * N));
-        hipLaunchKernelGGL(fft_rows_kernel, dim3(nf * N), dim3(256), lds, st, tmp, N, +1, R.n, rc, tw + N);
-        hipLaunchKernelGGL(transpose_kernel, dim3((N + 31) / 32, (N + 31) / 32, nf), dim3(32, 8), 0, st, tmp, buf, N);
-        hipLaunchKernelGGL(fft_rows_kernel, dim3(nf * N), dim3(256), lds, st, buf, N, +1, R.n, rc, tw + N);
-        if (nc == 2) hipLaunchKernelGGL(wilson2_kernel, dim3((V + 255) / 256), dim3(256), 0, st, buf, nsh, V, Vdag);
-        else hipLaunchKernelGGL(wilson_kernel, dim3((V + 255) / 256), dim3(256), 0, st, buf, nsh, V, Vdag);
-        CK(hipGetLastError());
+    const Radices R = radices_of(N);
+    if (R.n < 0 || N > kMaxFFT || N < 4) return hipErrorInvalidValue;
+    Radices B = R;  // the opposite order
+    for (int s = 0; s < R.n; s++) B.r[s] = R.r[R.n - 1 - s];
+    const Band bd = band_of(N, a.uvhat);
+    const size_t per_sheet = (size_t)pairs * N * bd.nk * sizeof(d2);
+    // (and of at most 16383 sheets: four planes each in a grid dimension of 65535)
+    const int chunk = (int)std::max<size_t>(1, std::min<size_t>(std::min(a.n_sheets, 16383), kChunkBytes / per_sheet));
+    // Wilson lines: workgroups of whole rows, 256 sites where a row is
+    // shorter.  The sheets of a chunk are split into up to 16 segments (joined
+    // afterwards) so that the workgroups fill the chip in whole rounds: the
+    // register file holds 16 of their wavefronts per CU.  The cost is counted in
+    // sheets: the rounds times a segment's sheets and its start and end, and the
+    // joining.  (384^2: four segments 37 sheets long instead of one of 50.)
+    const int RB = std::max(1, 256 / N), groups = (N + RB - 1) / RB;
+    const int sites = RB * N, wt = std::min(512, (sites + 63) / 64 * 64), slots = 256 * (16 / (wt / 64));
+    int seg_len = chunk;
+    for (double best = 1e300, k = 1; k <= std::min(chunk, 16); k++) {
+        const int len = (chunk + (int)k - 1) / (int)k, nseg = (chunk + len - 1) / len;
+        const double cost = ((groups * nseg + slots - 1) / slots) * (len + 0.7) + 0.1 * nseg;
+        if (cost < best) {
+            best = cost;
+            seg_len = len;
+        }
+    }
+    const int max_seg = (chunk + seg_len - 1) / seg_len;
+    const bool direct = max_seg == 1 && chunk >= a.n_sheets;  // one segment: no joining
+    {
+        // one block of memory, every part on a 256-byte boundary
+        size_t at = 0;
+        auto part = [&](size_t bytes) {
+            const size_t p = at;
+            at += (bytes + 255) / 256 * 256;
+            return p;
+        };
+        const size_t mw = sizeof(double) * MW * V;
+        const size_t o_tw = part(sizeof(d2) * 3 * N), o_K = part(sizeof(double) * bd.nk * N);
+        const size_t o_spec = part(per_sheet * chunk), o_A = part(mw), o_B = part(mw);
+        const size_t o_seg = part(direct ? 0 : mw * max_seg), o_U = part(double_links ? 2 * mw : 0);
+        CK(ws.reserve(at));
+        char* base = static_cast<char*>(ws.base);
+        w.tw = (d2*)(base + o_tw);
+        w.K = (double*)(base + o_K);
+        w.spec = (d2*)(base + o_spec);
+        w.VA = (double*)(base + o_A);
+        w.VB = (double*)(base + o_B);
+        w.seg = (double*)(base + o_seg);
+        w.U = (double*)(base + o_U);
+    }
+    hipLaunchKernelGGL(twiddle_kernel, dim3(3), dim3(256), 0, st, w.tw, N, R.n, radix_code(R), radix_code(B));
+    hipLaunchKernelGGL(poisson_kernel, dim3((bd.nk * N + 255) / 256), dim3(256), 0, st, w.K, N, bd.nk, bd.kc, a.mhat,
+                       a.uvhat);
+    const Fft fwd = make_fft(w.tw, N, R), inv = make_fft(w.tw + N, N, R), back = make_fft(w.tw + 2 * N, N, B);
+    const double sigma = a.g2mua / sqrt((double)a.n_sheets), scale = 1.0 / ((double)N * N);
+    const int rb = std::max(1, 1024 / N), row_groups = (N + rb - 1) / rb;
+    int bsh = 0;  // columns per workgroup: 2048 entries (4096 above 512)
+    while (bsh < 5 && (2 << bsh) * N <= (N > 512 ? 4096 : 2048)) bsh++;
+    const int col_groups = 8 * ((((bd.nk + (1 << bsh) - 1) >> bsh) + 7) / 8);
+    for (int nucleus = 0; nucleus < 2; nucleus++) {
+        double* Vdag = nucleus == 0 ? w.VA : w.VB;
+        for (int s0 = 0; s0 < a.n_sheets; s0 += chunk) {
+            const int nsh = std::min(chunk, a.n_sheets - s0), nseg = (nsh + seg_len - 1) / seg_len;
+            hipLaunchKernelGGL(rows_forward_kernel, dim3(row_groups, nsh * (pairs / 2)), dim3(256), 0, st, w.spec, N,
+                               bd.nk, bd.kc, a.seed, nucleus, s0, sigma, pairs, rb, fwd);
+            const dim3 cg(col_groups, nsh * pairs);
+            if (N > 512) hipLaunchKernelGGL(columns_kernel<512>, cg, dim3(512), 0, st, w.spec, N, bd.nk, bsh, w.K, scale, fwd, back);
+            else hipLaunchKernelGGL(columns_kernel<256>, cg, dim3(256), 0, st, w.spec, N, bd.nk, bsh, w.K, scale, fwd, back);
+            double* dst = direct ? Vdag : w.seg;
+            const dim3 wg(groups, nseg);
+            if (sites <= 256) hipLaunchKernelGGL((rows_wilson_kernel<NC, 256>), wg, dim3(wt), 0, st, w.spec, N, bd.nk, bd.kc, RB, nsh, seg_len, dst, inv);
+            else if (sites <= 512) hipLaunchKernelGGL((rows_wilson_kernel<NC, 512>), wg, dim3(wt), 0, st, w.spec, N, bd.nk, bd.kc, RB, nsh, seg_len, dst, inv);
+            else hipLaunchKernelGGL((rows_wilson_kernel<NC, 1024>), wg, dim3(wt), 0, st, w.spec, N, bd.nk, bd.kc, RB, nsh, seg_len, dst, inv);
+            if (!direct)
+                hipLaunchKernelGGL(join_segments_kernel<NC>, dim3((V + 255) / 256), dim3(256), 0, st, w.seg, nseg, V,
+                                   s0 == 0 ? 1 : 0, Vdag);
+            CK(hipGetLastError());
+        }
     }
     return hipSuccess;
 }
 
-hipError_t ic_glasma(const ICArgs& a, Fields<double> out, int* d_fails, hipStream_t st)
+hipError_t ICWorkspace::reserve(size_t need)
 {
-    const int N = a.N, V = N * N;
-    const Radices R = radices_of(N);
-    if (R.n < 0 || N > kMaxFFT || N < 4) return hipErrorInvalidValue;
-    const size_t per_sheet = (size_t)4 * V * sizeof(d2);
-    int chunk = (int)((size_t)256 << 20) / (int)(per_sheet > 0 ? per_sheet : 1);
-    chunk = chunk < 1 ? 1 : (chunk > a.n_sheets ? a.n_sheets : chunk);
-    d2 *buf = nullptr, *tmp = nullptr;
-    d2* tw = nullptr;
-    double *Vdag = nullptr, *UA = nullptr, *UB = nullptr;
-    hipError_t e = make_twiddles(&tw, N, R, st);
-    if (e == hipSuccess) e = hipMalloc(&buf, per_sheet * chunk);
-    if (e == hipSuccess) e = hipMalloc(&tmp, per_sheet * chunk);
-    if (e == hipSuccess) e = hipMalloc(&Vdag, sizeof(double) * 18 * V);
-    if (e == hipSuccess) e = hipMalloc(&UA, sizeof(double) * 36 * V);
-    if (e == hipSuccess) e = hipMalloc(&UB, sizeof(double) * 36 * V);
-    if (e == hipSuccess) e = nucleus_wilson(a, 0, buf, tmp, chunk, Vdag, R, tw, st);
-    if (e == hipSuccess) {
-        hipLaunchKernelGGL(pure_gauge_kernel, dim3((V + 255) / 256), dim3(256), 0, st, Vdag, N, UA);
-        e = nucleus_wilson(a, 1, buf, tmp, chunk, Vdag, R, tw, st);
-    }
-    if (e == hipSuccess) {
-        hipLaunchKernelGGL(pure_gauge_kernel, dim3((V + 255) / 256), dim3(256), 0, st, Vdag, N, UB);
-        hipLaunchKernelGGL(links_kernel, dim3((2 * V + 127) / 128), dim3(128), 0, st, UA, UB, V, a.tol, a.maxit,
-                           out.U, d_fails);
-        hipLaunchKernelGGL(pi0_kernel, dim3((V + 255) / 256), dim3(256), 0, st, UA, UB, out.U, N, out.pi);
-        const size_t nz = (size_t)24 * V;  // phi (8V) and E (16V) are adjacent
-        hipLaunchKernelGGL(zero_kernel, dim3((unsigned)((nz + 255) / 256)), dim3(256), 0, st, out.phi, nz);
-        e = hipGetLastError();
-    }
-    hipError_t e2 = hipStreamSynchronize(st);
-    if (e == hipSuccess) e = e2;
-    (void)hipFree(buf); (void)hipFree(tmp); (void)hipFree(Vdag); (void)hipFree(UA); (void)hipFree(UB);
-    (void)hipFree(tw);
+    if (need <= bytes) return hipSuccess;
+    release();
+    const hipError_t e = hipMalloc(&base, need);
+    if (e == hipSuccess) bytes = need;
+    else base = nullptr;
     return e;
 }
+void ICWorkspace::release()
+{
+    (void)hipFree(base);
+    base = nullptr;
+    bytes = 0;
+}
+
+template <typename T>
+hipError_t ic_glasma(const ICArgs& a, ICWorkspace& ws, const Fields<T>& out, int* d_fails, hipStream_t st)
+{
+    constexpr bool own = std::is_same<T, double>::value;  // the links are solved in place
+    const int N = a.N, V = N * N;
+    ICWork w{};
+    CK(wilson_lines<3>(a, ws, !own, w, st));
+    double* U = w.U;
+    if constexpr (own) U = out.U;
+    hipLaunchKernelGGL(links_kernel, dim3((2 * V + 127) / 128), dim3(128), 0, st, w.VA, w.VB, N, a.tol, a.maxit, U,
+                       d_fails);
+    hipLaunchKernelGGL(pi0_kernel<T>, dim3((V + 127) / 128), dim3(128), 0, st, w.VA, w.VB, U, N, out.pi);
+    const size_t nz = (size_t)24 * V;  // phi (8V) and E (16V) are adjacent
+    hipLaunchKernelGGL(zero_kernel<T>, dim3((unsigned)((nz + 255) / 256)), dim3(256), 0, st, out.phi, nz);
+    if constexpr (!own) CK(convert_to_float(U, out.U, (size_t)36 * V, st));
+    return hipGetLastError();
+}
+template hipError_t ic_glasma<double>(const ICArgs&, ICWorkspace&, const Fields<double>&, int*, hipStream_t);
+template hipError_t ic_glasma<float>(const ICArgs&, ICWorkspace&, const Fields<float>&, int*, hipStream_t);
 
 // ------------------------------------------------------------------ SU(2)
-// U^X_i(x) = V(x) V(x+i)^+ on quaternions [2][4][V]
-__global__ void pure_gauge2_kernel(const double* __restrict__ Vdag, int N, double* UX)
-{
-    const int V = N * N;
-    const int s = blockIdx.x * blockDim.x + threadIdx.x;
-    if (s >= V) return;
-    const int x = s % N, y = s / N;
-    const int sx = y * N + (x + 1 == N ? 0 : x + 1), sy = (y + 1 == N ? 0 : y + 1) * N + x;
-    const q4<double> here = qadj(ldQ(Vdag, s, V));
-    stQ(UX, s, V, qmul(here, ldQ(Vdag, sx, V)));
-    stQ(UX + 4 * (size_t)V, s, V, qmul(here, ldQ(Vdag, sy, V)));
-}
 // tau = 0 links: W = U^A + U^B is a real multiple of an SU(2) element S, and
 // U = S^2 = W W / |W|^2 solves Proj[W (1 + U^+)] = 0 (W (1 + U^+) = W + W^+ |W|^0
 // is then a multiple of 1)
-__global__ void links2_kernel(const double* __restrict__ UA, const double* __restrict__ UB, int V, double* U)
+__global__ void links2_kernel(const double* __restrict__ VA, const double* __restrict__ VB, int N, double* U)
 {
+    const int V = N * N;
     const int k = blockIdx.x * blockDim.x + threadIdx.x;
     if (k >= 2 * V) return;
-    const int i = k / V, s = k - i * V;
+    const int i = k / V, s = k - i * V, si = site_up(s, i, N);
     const size_t o = (size_t)i * 4 * V;
-    const q4<double> W = qadd(ldQ(UA + o, s, V), ldQ(UB + o, s, V));
+    const q4<double> W = qadd(pure_link2(VA, s, si, V), pure_link2(VB, s, si, V));
     const double n2 = W.w * W.w + W.x * W.x + W.y * W.y + W.z * W.z;
     const q4<double> S2 = qmul(W, W);
     stQ(U + o, s, V, {S2.w / n2, S2.x / n2, S2.y / n2, S2.z / n2});
 }
 // pi(0) of the SU(3) kernel on quaternions
-__global__ void pi02_kernel(const double* __restrict__ UA, const double* __restrict__ UB, const double* __restrict__ U,
-                            int N, double* pi)
+template <typename T>
+__global__ void pi02_kernel(const double* __restrict__ VA, const double* __restrict__ VB, const double* __restrict__ U,
+                            int N, T* pi)
 {
     const int V = N * N;
     const int s = blockIdx.x * blockDim.x + threadIdx.x;
     if (s >= V) return;
-    const int x = s % N, y = s / N;
     q4<double> acc = {0, 0, 0, 0};
     for (int i = 0; i < 2; i++) {
-        const int sm = i == 0 ? y * N + (x == 0 ? N - 1 : x - 1) : (y == 0 ? N - 1 : y - 1) * N + x;
+        const int sm = site_down(s, i, N), sp = site_up(s, i, N);
         const size_t o = (size_t)i * 4 * V;
         const q4<double> P1 = qmul(qsub(ldQ(U + o, s, V), qone<double>()),
-                                   qsub(qadj(ldQ(UB + o, s, V)), qadj(ldQ(UA + o, s, V))));
+                                   qsub(qadj(pure_link2(VB, s, sp, V)), qadj(pure_link2(VA, s, sp, V))));
         const q4<double> P2 = qmul(qsub(qadj(ldQ(U + o, sm, V)), qone<double>()),
-                                   qsub(ldQ(UB + o, sm, V), ldQ(UA + o, sm, V)));
+                                   qsub(pure_link2(VB, sm, s, V), pure_link2(VA, sm, s, V)));
         acc = qadd(acc, qadd(P1, P2));
     }
     const v3<double> p = qproj(acc);
-    for (int a = 0; a < 3; a++) pi[(size_t)a * V + s] = 0.5 * p.v[a];
+    for (int a = 0; a < 3; a++) pi[(size_t)a * V + s] = (T)(0.5 * p.v[a]);
 }
 
-hipError_t ic_glasma2(const ICArgs& a, Fields2<double> out, hipStream_t st)
+template <typename T>
+hipError_t ic_glasma2(const ICArgs& a, ICWorkspace& ws, const Fields2<T>& out, hipStream_t st)
 {
+    constexpr bool own = std::is_same<T, double>::value;
     const int N = a.N, V = N * N;
-    const Radices R = radices_of(N);
-    if (R.n < 0 || N > kMaxFFT || N < 4) return hipErrorInvalidValue;
-    const size_t per_sheet = (size_t)2 * V * sizeof(d2);
-    int chunk = (int)((size_t)256 << 20) / (int)(per_sheet > 0 ? per_sheet : 1);
-    chunk = chunk < 1 ? 1 : (chunk > a.n_sheets ? a.n_sheets : chunk);
-    d2 *buf = nullptr, *tmp = nullptr;
-    d2* tw = nullptr;
-    double *Vdag = nullptr, *UA = nullptr, *UB = nullptr;
-    hipError_t e = make_twiddles(&tw, N, R, st);
-    if (e == hipSuccess) e = hipMalloc(&buf, per_sheet * chunk);
-    if (e == hipSuccess) e = hipMalloc(&tmp, per_sheet * chunk);
-    if (e == hipSuccess) e = hipMalloc(&Vdag, sizeof(double) * 4 * V);
-    if (e == hipSuccess) e = hipMalloc(&UA, sizeof(double) * 8 * V);
-    if (e == hipSuccess) e = hipMalloc(&UB, sizeof(double) * 8 * V);
-    if (e == hipSuccess) e = nucleus_wilson(a, 0, buf, tmp, chunk, Vdag, R, tw, st, 2);
-    if (e == hipSuccess) {
-        hipLaunchKernelGGL(pure_gauge2_kernel, dim3((V + 255) / 256), dim3(256), 0, st, Vdag, N, UA);
-        e = nucleus_wilson(a, 1, buf, tmp, chunk, Vdag, R, tw, st, 2);
-    }
-    if (e == hipSuccess) {
-        hipLaunchKernelGGL(pure_gauge2_kernel, dim3((V + 255) / 256), dim3(256), 0, st, Vdag, N, UB);
-        hipLaunchKernelGGL(links2_kernel, dim3((2 * V + 255) / 256), dim3(256), 0, st, UA, UB, V, out.U);
-        hipLaunchKernelGGL(pi02_kernel, dim3((V + 255) / 256), dim3(256), 0, st, UA, UB, out.U, N, out.pi);
-        const size_t nz = (size_t)9 * V;  // phi (3V) and E (6V) are adjacent
-        hipLaunchKernelGGL(zero_kernel, dim3((unsigned)((nz + 255) / 256)), dim3(256), 0, st, out.phi, nz);
-        e = hipGetLastError();
-    }
-    hipError_t e2 = hipStreamSynchronize(st);
-    if (e == hipSuccess) e = e2;
-    (void)hipFree(buf); (void)hipFree(tmp); (void)hipFree(Vdag); (void)hipFree(UA); (void)hipFree(UB);
-    (void)hipFree(tw);
-    return e;
+    ICWork w{};
+    CK(wilson_lines<2>(a, ws, !own, w, st));
+    double* U = w.U;
+    if constexpr (own) U = out.U;
+    hipLaunchKernelGGL(links2_kernel, dim3((2 * V + 255) / 256), dim3(256), 0, st, w.VA, w.VB, N, U);
+    hipLaunchKernelGGL(pi02_kernel<T>, dim3((V + 255) / 256), dim3(256), 0, st, w.VA, w.VB, U, N, out.pi);
+    const size_t nz = (size_t)9 * V;  // phi (3V) and E (6V) are adjacent
+    hipLaunchKernelGGL(zero_kernel<T>, dim3((unsigned)((nz + 255) / 256)), dim3(256), 0, st, out.phi, nz);
+    if constexpr (!own) CK(convert_to_float(U, out.U, (size_t)8 * V, st));
+    return hipGetLastError();
 }
+template hipError_t ic_glasma2<double>(const ICArgs&, ICWorkspace&, const Fields2<double>&, hipStream_t);
+template hipError_t ic_glasma2<float>(const ICArgs&, ICWorkspace&, const Fields2<float>&, hipStream_t);
 
 // SU(2) particles: block 0 as for SU(3); the charge from the Darboux
 // parametrisation (Sec. IV.A) with J^2 = q2: words 0, 1 of block 1 give
 // phi = 2 pi u and xi = J (2 u' - 1), Q = (cos phi rho, sin phi rho, xi),
 // rho = sqrt(J^2 - xi^2).  Records keep the SU(3) layout (Q^4..Q^8 = 0).
-__global__ void particles2_kernel(PartICArgs a, double J, double* r, int* cell)
+template <typename T> __global__ void particles2_kernel(PartICArgs a, double J, T* r, int* cell)
 {
     const int p = blockIdx.x * blockDim.x + threadIdx.x;
     const int np = a.np, N = a.N;
@@ -659,37 +933,35 @@ __global__ void particles2_kernel(PartICArgs a, double J, double* r, int* cell)
     const double ph = 2.0 * M_PI * u01_co(v.v[0]), xi = J * (2.0 * u01_co(v.v[1]) - 1.0);
     const double rho = sqrt(J * J - xi * xi);
     const double cph = cos(phi0), sph = sin(phi0);
-    auto col = [&](int c) -> double& { return r[(size_t)c * np + p]; };
-    col(PX_) = x; col(PY_) = y; col(PETA_) = 0;
-    col(PPX) = pt * cph; col(PPY) = pt * sph; col(PPETA) = 0; col(PDETA) = 0;
-    col(PUX0) = cph; col(PUY0) = sph; col(PPT0) = pt;
-    col(PPTAU) = 0.0;  // set by the push at the formation step
-    col(PQ0) = cos(ph) * rho; col(PQ0 + 1) = sin(ph) * rho; col(PQ0 + 2) = xi;
-    for (int c = 3; c < 8; c++) col(PQ0 + c) = 0.0;
+    auto col = [&](int c) -> T& { return r[(size_t)c * np + p]; };
+    col(PX_) = T(x); col(PY_) = T(y); col(PETA_) = T(0);
+    col(PPX) = T(pt * cph); col(PPY) = T(pt * sph); col(PPETA) = T(0); col(PDETA) = T(0);
+    col(PUX0) = T(cph); col(PUY0) = T(sph); col(PPT0) = T(pt);
+    col(PPTAU) = T(0.0);  // set by the push at the formation step
+    col(PQ0) = T(cos(ph) * rho); col(PQ0 + 1) = T(sin(ph) * rho); col(PQ0 + 2) = T(xi);
+    for (int c = 3; c < 8; c++) col(PQ0 + c) = T(0.0);
     int nx = (int)floor(x + 0.5), ny = (int)floor(y + 0.5);
     cell[p] = nx >= N ? nx - N : nx;
     cell[np + p] = ny >= N ? ny - N : ny;
 }
 
-hipError_t ic_particles2(const PartICArgs& a, double q2, double* r, int* cell, hipStream_t st)
+template <typename T>
+hipError_t ic_particles2(const PartICArgs& a, double q2, T* r, int* cell, hipStream_t st)
 {
     if (a.np <= 0) return hipSuccess;
-    hipLaunchKernelGGL(particles2_kernel, dim3((a.np + 127) / 128), dim3(128), 0, st, a, sqrt(q2), r, cell);
+    hipLaunchKernelGGL(particles2_kernel<T>, dim3((a.np + 127) / 128), dim3(128), 0, st, a, sqrt(q2), r, cell);
     return hipGetLastError();
 }
+template hipError_t ic_particles2<double>(const PartICArgs&, double, double*, int*, hipStream_t);
+template hipError_t ic_particles2<float>(const PartICArgs&, double, float*, int*, hipStream_t);
 
-hipError_t ic_particles(const PartICArgs& a, double* r, int* cell, hipStream_t st)
+template <typename T> hipError_t ic_particles(const PartICArgs& a, T* r, int* cell, hipStream_t st)
 {
     if (a.np <= 0) return hipSuccess;
-    hipLaunchKernelGGL(particles_kernel, dim3((a.np + 127) / 128), dim3(128), 0, st, a, r, cell);
+    hipLaunchKernelGGL(particles_kernel<T>, dim3((a.np + 127) / 128), dim3(128), 0, st, a, r, cell);
     return hipGetLastError();
 }
-
-hipError_t convert_to_float(const double* src, float* dst, size_t n, hipStream_t st)
-{
-    if (!n) return hipSuccess;
-    hipLaunchKernelGGL(convert_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, src, dst, n);
-    return hipGetLastError();
-}
+template hipError_t ic_particles<double>(const PartICArgs&, double*, int*, hipStream_t);
+template hipError_t ic_particles<float>(const PartICArgs&, float*, int*, hipStream_t);
 
 }  // namespace cpic

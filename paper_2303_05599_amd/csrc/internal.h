@@ -294,6 +294,7 @@ struct SortBufs {
     void* r2 = nullptr;  // [19][np] scratch records
     int *cell2 = nullptr, *pid2 = nullptr;
 };
+hipError_t launch_iota(int* p, int n, hipStream_t st);  // p[i] = i
 // keys of an N x N lattice lie below key_capacity(N) for every tile shape
 int key_capacity(int N);
 size_t sort_temp_bytes(int N);
@@ -321,18 +322,30 @@ struct ICArgs {
     double tol;
     int maxit;
 };
-// builds U, pi (phi = E = 0) into a double buffer set; returns failures in *fails (device int)
-hipError_t ic_glasma(const ICArgs& a, Fields<double> out, int* d_fails, hipStream_t st);
+// Device memory the initial condition works in, kept by its owner (a context, or
+// a batch for all its events) from one initial condition to the next: releasing
+// a block of this size costs about 230 us.  One initial condition at a time.
+struct ICWorkspace {
+    void* base = nullptr;
+    size_t bytes = 0;
+    hipError_t reserve(size_t need);  // the block may move: its contents are not kept
+    void release();
+};
+// builds U, pi (phi = E = 0) into a buffer set; counts failures in *d_fails (device int); asynchronous
+template <typename T>
+hipError_t ic_glasma(const ICArgs& a, ICWorkspace& ws, const Fields<T>& out, int* d_fails, hipStream_t st);
 struct PartICArgs {
     int N, np, azimuth_uniform;
     uint64_t seed;
     double pt_min, pt_max;
     double q0[8];
 };
-hipError_t ic_particles(const PartICArgs& a, double* r /*[19][np]*/, int* cell, hipStream_t st);
-// SU(2) variant: links, pi(0) into a double Fields2 set; Darboux charges with |Q|^2 = q2
-hipError_t ic_glasma2(const ICArgs& a, Fields2<double> out, hipStream_t st);
-hipError_t ic_particles2(const PartICArgs& a, double q2, double* r, int* cell, hipStream_t st);
-hipError_t convert_to_float(const double* src, float* dst, size_t n, hipStream_t st);
+template <typename T>
+hipError_t ic_particles(const PartICArgs& a, T* r /*[19][np]*/, int* cell, hipStream_t st);
+// SU(2) variant: links, pi(0); Darboux charges with |Q|^2 = q2
+template <typename T>
+hipError_t ic_glasma2(const ICArgs& a, ICWorkspace& ws, const Fields2<T>& out, hipStream_t st);
+template <typename T>
+hipError_t ic_particles2(const PartICArgs& a, double q2, T* r, int* cell, hipStream_t st);
 
 }  // namespace cpic

@@ -35,9 +35,10 @@ __device__ __forceinline__ double u01_oc(uint64_t r) { return (double)((r >> 11)
 __device__ __forceinline__ void box_muller(uint64_t ra, uint64_t rb, double& z0, double& z1)
 {
     const double rad = sqrt(-2.0 * log(u01_oc(ra)));
-    const double ang = 2.0 * M_PI * u01_co(rb);
-    z0 = rad * cos(ang);
-    z1 = rad * sin(ang);
+    double sn, cs;
+    sincospi(2.0 * u01_co(rb), &sn, &cs);  // the angle 2 pi u, without a range reduction
+    z0 = rad * cs;
+    z1 = rad * sn;
 }
 
 }  // namespace cpic

@@ -161,6 +161,18 @@ __global__ void order_runs_kernel(int* count, const int* __restrict__ ends, int 
     }
 }
 
+__global__ void iota_kernel(int* p, int n)
+{
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < n) p[i] = i;
+}
+hipError_t launch_iota(int* p, int n, hipStream_t st)
+{
+    if (n <= 0) return hipSuccess;
+    hipLaunchKernelGGL(iota_kernel, dim3((n + 255) / 256), dim3(256), 0, st, p, n);
+    return hipGetLastError();
+}
+
 int key_capacity(int N)
 {
     // the largest key bound of any tile shape (tiles of at most 64 x 64 cells)
