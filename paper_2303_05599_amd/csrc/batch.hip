@@ -71,6 +71,7 @@ struct cpic_batch {
     std::vector<EventDesc> desc;  // host copy (kept alive for the asynchronous upload)
     std::map<std::vector<int>, Plan> plans;
     ICWorkspace icw{};  // of the events' initial conditions, made one after the other
+    ExchangeBuffers xb{};  // of the events' state exchange, likewise
     std::string err;
 };
 
@@ -278,6 +279,7 @@ extern "C" cpic_status cpic_batch_create(int32_t n_events, const cpic_glasma_par
         // records keep the gather push's order
         if (c->cfg.split == 4) c->cfg.split = 3;
         c->icw = &b->icw;
+        c->xb = &b->xb;
         b->ev.push_back(c);
     }
     // compressed-link LDS tiles of 64 x 4 sites (cpic_batch_tune picks among the shapes)
@@ -653,6 +655,7 @@ extern "C" void cpic_batch_destroy(cpic_batch* b)
     if (b->ev_fork) (void)hipEventDestroy(b->ev_fork);
     for (auto c : b->ev) cpic_destroy(c);
     b->icw.release();
+    b->xb.release();
     if (b->own_stream) (void)hipStreamDestroy(b->st);
     delete b;
 }

@@ -110,6 +110,7 @@ static void free_all(cpic_ctx* c)
     (void)hipFree(c->tile_start); (void)hipFree(c->strag); (void)hipFree(c->strag_count);
     (void)hipFree(c->d_strag_total);
     c->icw_own.release();
+    c->xb_own.release();
     if (c->own_stream && c->st) (void)hipStreamDestroy(c->st);
 }
 
@@ -973,207 +974,6 @@ static size_t state_bytes(const cpic_ctx* c, int which)
     }
 }
 
-// device SoA (type T) <-> host interchange (double, site-major)
-template <typename T> static void soa_to_host(const std::vector<T>& d, double* h, int which, int V)
-{
-    if (which == CPIC_STATE_U) {
-        // the device keeps the first two rows of each link; the third is their
-        // conjugate cross product, formed here as the kernels form it
-        for (int i = 0; i < 2; i++)
-            for (int s = 0; s < V; s++) {
-                double* m = h + ((size_t)i * V + s) * 18;
-                for (int c = 0; c < 12; c++) m[c] = (double)d[((size_t)i * 18 + c) * V + s];
-                for (int j = 0; j < 3; j++) {
-                    const int j1 = (j + 1) % 3, j2 = (j + 2) % 3;
-                    const double* a = m + 2 * j1; const double* b = m + 6 + 2 * j2;  // r1[j1], r2[j2]
-                    const double* e = m + 2 * j2; const double* f = m + 6 + 2 * j1;  // r1[j2], r2[j1]
-                    const double pre = a[0] * b[0] - a[1] * b[1], pim = a[0] * b[1] + a[1] * b[0];
-                    const double qre = e[0] * f[0] - e[1] * f[1], qim = e[0] * f[1] + e[1] * f[0];
-                    m[12 + 2 * j] = pre - qre;
-                    m[13 + 2 * j] = qim - pim;
-                }
-            }
-    } else {
-        const int blocks = which == CPIC_STATE_E ? 2 : 1;
-        for (int i = 0; i < blocks; i++)
-            for (int s = 0; s < V; s++)
-                for (int a = 0; a < 8; a++) h[((size_t)i * V + s) * 8 + a] = (double)d[((size_t)i * 8 + a) * V + s];
-    }
-}
-template <typename T> static void host_to_soa(const double* h, std::vector<T>& d, int which, int V)
-{
-    if (which == CPIC_STATE_U) {
-        for (int i = 0; i < 2; i++)
-            for (int s = 0; s < V; s++)
-                for (int c = 0; c < 18; c++) d[((size_t)i * 18 + c) * V + s] = (T)h[((size_t)i * V + s) * 18 + c];
-    } else {
-        const int blocks = which == CPIC_STATE_E ? 2 : 1;
-        for (int i = 0; i < blocks; i++)
-            for (int s = 0; s < V; s++)
-                for (int a = 0; a < 8; a++) d[((size_t)i * 8 + a) * V + s] = (T)h[((size_t)i * V + s) * 8 + a];
-    }
-}
-static size_t field_offset(int which, int V)
-{
-    switch (which) {
-    case CPIC_STATE_U: return 0;
-    case CPIC_STATE_PHI: return 36 * (size_t)V;
-    case CPIC_STATE_E: return 44 * (size_t)V;
-    default: return 60 * (size_t)V;  // PI
-    }
-}
-// SU(2) buffer set: U [2][4][V] quaternions (w, a1, a2, a3) for
-// U = w + i a.sigma = [[w + i a3, a2 + i a1], [-a2 + i a1, w - i a3]];
-// phi [3][V], E [2][3][V], pi [3][V]
-static size_t field_offset2(int which, int V)
-{
-    switch (which) {
-    case CPIC_STATE_U: return 0;
-    case CPIC_STATE_PHI: return 8 * (size_t)V;
-    case CPIC_STATE_E: return 11 * (size_t)V;
-    default: return 17 * (size_t)V;
-    }
-}
-template <typename T> static void su2_to_host(const std::vector<T>& d, double* h, int which, int V)
-{
-    if (which == CPIC_STATE_U) {
-        for (int i = 0; i < 2; i++)
-            for (int s = 0; s < V; s++) {
-                const double w = d[((size_t)i * 4 + 0) * V + s], a1 = d[((size_t)i * 4 + 1) * V + s],
-                             a2 = d[((size_t)i * 4 + 2) * V + s], a3 = d[((size_t)i * 4 + 3) * V + s];
-                double* m = h + ((size_t)i * V + s) * 8;  // 2x2 complex, row-major, re/im
-                m[0] = w;   m[1] = a3;
-                m[2] = a2;  m[3] = a1;
-                m[4] = -a2; m[5] = a1;
-                m[6] = w;   m[7] = -a3;
-            }
-    } else {
-        const int blocks = which == CPIC_STATE_E ? 2 : 1;
-        for (int i = 0; i < blocks; i++)
-            for (int s = 0; s < V; s++)
-                for (int a = 0; a < 3; a++) h[((size_t)i * V + s) * 3 + a] = (double)d[((size_t)i * 3 + a) * V + s];
-    }
-}
-template <typename T> static void host_to_su2(const double* h, std::vector<T>& d, int which, int V)
-{
-    if (which == CPIC_STATE_U) {
-        for (int i = 0; i < 2; i++)
-            for (int s = 0; s < V; s++) {
-                const double* m = h + ((size_t)i * V + s) * 8;
-                d[((size_t)i * 4 + 0) * V + s] = (T)m[0];
-                d[((size_t)i * 4 + 1) * V + s] = (T)m[3];
-                d[((size_t)i * 4 + 2) * V + s] = (T)m[2];
-                d[((size_t)i * 4 + 3) * V + s] = (T)m[1];
-            }
-    } else {
-        const int blocks = which == CPIC_STATE_E ? 2 : 1;
-        for (int i = 0; i < blocks; i++)
-            for (int s = 0; s < V; s++)
-                for (int a = 0; a < 3; a++) d[((size_t)i * 3 + a) * V + s] = (T)h[((size_t)i * V + s) * 3 + a];
-    }
-}
-// interchange particle columns: x y eta px py peta Q1..Q8 cx cy deta ux0 uy0 pt0
-static const int kXchgToDev[20] = {PX_, PY_, PETA_, PPX, PPY, PPETA, PQ0, PQ0 + 1, PQ0 + 2, PQ0 + 3, PQ0 + 4,
-                                   PQ0 + 5, PQ0 + 6, PQ0 + 7, -1, -2, PDETA, PUX0, PUY0, PPT0};
-
-template <typename T> static cpic_status get_t(cpic_ctx* c, int which, double* h)
-{
-    if (which == CPIC_STATE_JET_W || which == CPIC_STATE_JET_F) {
-        const int nc = which == CPIC_STATE_JET_W ? 18 : 24;
-        std::vector<T> d((size_t)nc * c->V);
-        HIPCHK(c, hipMemcpy(d.data(), which == CPIC_STATE_JET_W ? c->jW : c->jF, sizeof(T) * d.size(),
-                            hipMemcpyDeviceToHost), "get paths");
-        for (int s = 0; s < c->V; s++)
-            for (int k = 0; k < nc; k++) h[(size_t)s * nc + k] = (double)d[(size_t)k * c->V + s];
-        return CPIC_OK;
-    }
-    if (which == CPIC_STATE_PTAU) {
-        // p^tau from the constraint at step n beside the integrated value
-        const size_t np = c->np;
-        std::vector<T> r(kPartReals * np);
-        std::vector<int> pid(np);
-        HIPCHK(c, hipMemcpy(r.data(), c->pr, sizeof(T) * r.size(), hipMemcpyDeviceToHost), "get p^tau");
-        HIPCHK(c, hipMemcpy(pid.data(), c->pid, sizeof(int) * np, hipMemcpyDeviceToHost), "get p^tau");
-        const double t = c->n * c->sc.dt;
-        for (size_t p = 0; p < np; p++) {
-            const size_t row = (size_t)pid[p];
-            if (row >= np) return fail(c, CPIC_E_INVALID, "get_state: corrupt particle index");
-            const double px = r[PPX * np + p], py = r[PPY * np + p], pe = r[PPETA * np + p];
-            h[2 * row] = std::sqrt(px * px + py * py + (t * pe) * (t * pe) + c->mhat * c->mhat);
-            h[2 * row + 1] = (double)r[(size_t)PPTAU * np + p];
-        }
-        return CPIC_OK;
-    }
-    if (which == CPIC_STATE_PARTICLES) {
-        const size_t np = c->np;
-        std::vector<T> r(kPartReals * np);
-        std::vector<int> cell(2 * np), pid(np);
-        HIPCHK(c, hipMemcpy(r.data(), c->pr, sizeof(T) * r.size(), hipMemcpyDeviceToHost), "get particles");
-        HIPCHK(c, hipMemcpy(cell.data(), c->pcell, sizeof(int) * cell.size(), hipMemcpyDeviceToHost), "get particles");
-        HIPCHK(c, hipMemcpy(pid.data(), c->pid, sizeof(int) * np, hipMemcpyDeviceToHost), "get particles");
-        for (size_t p = 0; p < np; p++) {
-            const size_t row = (size_t)pid[p];
-            if (row >= np) return fail(c, CPIC_E_INVALID, "get_state: corrupt particle index");
-            for (int k = 0; k < 20; k++) {
-                const int d = kXchgToDev[k];
-                h[row * 20 + k] = d >= 0 ? (double)r[(size_t)d * np + p] : (double)cell[(size_t)(-d - 1) * np + p];
-            }
-        }
-        return CPIC_OK;
-    }
-    if (c->nc == 2) {
-        const size_t cnt = which == CPIC_STATE_U ? 8 : (which == CPIC_STATE_E ? 6 : 3);
-        std::vector<T> d(cnt * c->V);
-        const T* src = static_cast<const T*>(c->fbuf[c->cur]) + field_offset2(which, c->V);
-        HIPCHK(c, hipMemcpy(d.data(), src, sizeof(T) * d.size(), hipMemcpyDeviceToHost), "get state");
-        su2_to_host(d, h, which, c->V);
-        return CPIC_OK;
-    }
-    const size_t cnt = which == CPIC_STATE_U ? 36 : (which == CPIC_STATE_E ? 16 : 8);
-    std::vector<T> d(cnt * c->V);
-    const T* src = static_cast<const T*>(c->fbuf[c->cur]) + field_offset(which, c->V);
-    HIPCHK(c, hipMemcpy(d.data(), src, sizeof(T) * d.size(), hipMemcpyDeviceToHost), "get state");
-    soa_to_host(d, h, which, c->V);
-    return CPIC_OK;
-}
-template <typename T> static cpic_status set_t(cpic_ctx* c, int which, const double* h)
-{
-    if (which == CPIC_STATE_PARTICLES) {
-        const size_t np = c->np;
-        std::vector<T> r(kPartReals * np);
-        std::vector<int> cell(2 * np);
-        for (size_t p = 0; p < np; p++)
-            for (int k = 0; k < 20; k++) {
-                const int d = kXchgToDev[k];
-                if (d >= 0) r[(size_t)d * np + p] = (T)h[p * 20 + k];
-                else cell[(size_t)(-d - 1) * np + p] = (int)h[p * 20 + k];
-            }
-        // the integrated p^tau restarts from the constraint at the current step
-        const double t = c->n * c->sc.dt;
-        for (size_t p = 0; p < np; p++) {
-            const double px = h[p * 20 + 3], py = h[p * 20 + 4], pe = h[p * 20 + 5];
-            r[(size_t)PPTAU * np + p] = (T)std::sqrt(px * px + py * py + (t * pe) * (t * pe) + c->mhat * c->mhat);
-        }
-        HIPCHK(c, hipMemcpy(c->pr, r.data(), sizeof(T) * r.size(), hipMemcpyHostToDevice), "set particles");
-        HIPCHK(c, hipMemcpy(c->pcell, cell.data(), sizeof(int) * cell.size(), hipMemcpyHostToDevice), "set particles");
-        return reset_pid(c);
-    }
-    if (c->nc == 2) {
-        const size_t cnt = which == CPIC_STATE_U ? 8 : (which == CPIC_STATE_E ? 6 : 3);
-        std::vector<T> d(cnt * c->V);
-        host_to_su2(h, d, which, c->V);
-        T* dst = static_cast<T*>(c->fbuf[c->cur]) + field_offset2(which, c->V);
-        HIPCHK(c, hipMemcpy(dst, d.data(), sizeof(T) * d.size(), hipMemcpyHostToDevice), "set state");
-        return CPIC_OK;
-    }
-    const size_t cnt = which == CPIC_STATE_U ? 36 : (which == CPIC_STATE_E ? 16 : 8);
-    std::vector<T> d(cnt * c->V);
-    host_to_soa(h, d, which, c->V);
-    T* dst = static_cast<T*>(c->fbuf[c->cur]) + field_offset(which, c->V);
-    HIPCHK(c, hipMemcpy(dst, d.data(), sizeof(T) * d.size(), hipMemcpyHostToDevice), "set state");
-    return CPIC_OK;
-}
-
 extern "C" cpic_status cpic_get_state(cpic_ctx* c, int32_t which, void* dst, size_t bytes)
 {
     if (!c || !dst) return fail(c, CPIC_E_INVALID, "cpic_get_state: NULL argument");
@@ -1189,7 +989,8 @@ extern "C" cpic_status cpic_get_state(cpic_ctx* c, int32_t which, void* dst, siz
         return CPIC_OK;
     }
     if (which == CPIC_STATE_PARTICLES && c->np == 0) return CPIC_OK;
-    return c->prec == CPIC_FP64 ? get_t<double>(c, which, (double*)dst) : get_t<float>(c, which, (double*)dst);
+    HIPCHK(c, exchange_get(c, which, static_cast<double*>(dst)), "get state");
+    return CPIC_OK;
 }
 
 extern "C" cpic_status cpic_set_state(cpic_ctx* c, int32_t which, const void* src, size_t bytes)
@@ -1221,7 +1022,9 @@ extern "C" cpic_status cpic_set_state(cpic_ctx* c, int32_t which, const void* sr
         }
     }
     c->watch_base_due = true;  // the watchdog's baseline is the installed state
-    return c->prec == CPIC_FP64 ? set_t<double>(c, which, (const double*)src) : set_t<float>(c, which, (const double*)src);
+    HIPCHK(c, exchange_set(c, which, static_cast<const double*>(src)), "set state");
+    // rows and records coincide again
+    return which == CPIC_STATE_PARTICLES ? reset_pid(c) : CPIC_OK;
 }
 
 // ------------------------------------------------------------------ checkpoints

@@ -11,6 +11,16 @@
 #include "internal.h"
 
 namespace cpic {
+// Staging of the state exchange (exchange.hip): two chunks in device and in
+// pinned host memory, allocated by the first exchange and kept by the owner (a
+// context, or a batch for all its events)
+struct ExchangeBuffers {
+    void *dev[2] = {nullptr, nullptr}, *pin[2] = {nullptr, nullptr};
+    hipEvent_t ev[2] = {nullptr, nullptr};
+    size_t bytes = 0;
+    hipError_t reserve(size_t need);
+    void release();
+};
 constexpr int kGraphSteps = 16;  // steps per captured graph (even: buffers return to their parity)
 }
 
@@ -56,6 +66,8 @@ struct cpic_ctx {
     int* d_fails = nullptr;
     cpic::ICWorkspace icw_own{};             // of a single event
     cpic::ICWorkspace* icw = &icw_own;       // an event of a batch uses the batch's
+    cpic::ExchangeBuffers xb_own{};
+    cpic::ExchangeBuffers* xb = &xb_own;     // likewise
     double* dpart = nullptr;  // diagnostics partials
     double* dout = nullptr;   // diagnostics results [8 + 2]
     int dcap = 0;
@@ -118,6 +130,10 @@ cpic_status watch_prepare(cpic_ctx* c);
 bool fused_ok(const cpic_ctx* c);
 // the fused step is the current launch
 bool fused_active(const cpic_ctx* c);
+// state exchange: a part of the state (CPIC_STATE_*, except the step) to or from
+// caller host memory in the interchange layout; ends with the stream idle
+hipError_t exchange_get(cpic_ctx* c, int which, double* host);
+hipError_t exchange_set(cpic_ctx* c, int which, const double* host);
 // device address of the allocation-free entry point's scratch array on the
 // current device (resolved once per device; noalloc.hip)
 cpic_status noalloc_scratch(double** out);
