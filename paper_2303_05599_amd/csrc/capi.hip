@@ -99,7 +99,8 @@ static void free_all(cpic_ctx* c)
     for (auto e : c->ev_table) (void)hipEventDestroy(e);
     (void)hipFree(c->ftab);
     (void)hipFree(c->jW); (void)hipFree(c->jF); (void)hipFree(c->jpartials); (void)hipFree(c->jobs);
-    (void)hipFree(c->fbuf[0]); (void)hipFree(c->fbuf[1]); (void)hipFree(c->pr); (void)hipFree(c->pcell); (void)hipFree(c->gpl);
+    (void)hipFree(c->fbuf[0]); (void)hipFree(c->fbuf[1]); (void)hipFree(c->fbuf[2]);
+    (void)hipFree(c->pr); (void)hipFree(c->pcell); (void)hipFree(c->gpl);
     (void)hipFree(c->partials); (void)hipFree(c->obs); (void)hipFree(c->d_step); (void)hipFree(c->d_err); (void)hipFree(c->d_fails);
     (void)hipFree(c->d_watchv); (void)hipFree(c->d_watchbase);
     if (c->h_stage) (void)hipHostFree(c->h_stage);
@@ -480,12 +481,12 @@ PushArgs cpic::push_args(const cpic_ctx* c, int tpp)
     return pa;
 }
 
-// one step: field update (cur -> cur^1), push (advances the step counter),
+// one step: field update (cur -> next_buffer(cur)), push (advances the step counter),
 // light-like paths
 // SU(2) step: field update, push (or the step advance without particles)
-template <typename T> static cpic_status launch_one_su2(cpic_ctx* c, int parity, bool with_events)
+template <typename T> static cpic_status launch_one_su2(cpic_ctx* c, int from, bool with_events)
 {
-    const Fields2<T> A = F2<T>(c, parity), B = F2<T>(c, parity ^ 1);
+    const Fields2<T> A = F2<T>(c, from), B = F2<T>(c, next_buffer(from));
     KTimer tf, tp;
     if (with_events) {
         HIPCHK(c, hipEventCreate(&tf.start), "event"); HIPCHK(c, hipEventCreate(&tf.stop), "event");
@@ -518,10 +519,10 @@ static Schedule table_schedule(const cpic_ctx* c)
     return s;
 }
 
-template <typename T> static cpic_status launch_one(cpic_ctx* c, int parity, bool with_events)
+template <typename T> static cpic_status launch_one(cpic_ctx* c, int from, bool with_events)
 {
-    if (c->nc == 2) return launch_one_su2<T>(c, parity, with_events);
-    const Fields<T> A = F<T>(c, parity), B = F<T>(c, parity ^ 1);
+    if (c->nc == 2) return launch_one_su2<T>(c, from, with_events);
+    const Fields<T> A = F<T>(c, from), B = F<T>(c, next_buffer(from));
     auto timer = [&](std::vector<hipEvent_t>& evs, KTimer& tm) -> hipError_t {
         if (!with_events) return hipSuccess;
         hipError_t e = hipEventCreate(&tm.start);
@@ -578,7 +579,7 @@ static int sample_groups_now(const cpic_ctx* c)
     return fused_active(c) ? fused_groups(c->N, c->cfg.bx, c->cfg.by) : obs_groups((int)c->np);
 }
 
-cpic_status cpic::host_advance(cpic_ctx* c, int k)
+cpic_status cpic::host_advance(cpic_ctx* c, int k, bool pipelined)
 {
     const int n0 = c->n;
     for (int j = 0; j < k; j++) {
@@ -589,8 +590,9 @@ cpic_status cpic::host_advance(cpic_ctx* c, int k)
         if (c->jets && is_record_step(c->ja.sc, c->n))
             c->jsamples.push_back({record_slot_of(c->ja.sc, c->n), c->n});
         c->n++;
-        c->cur ^= 1;
     }
+    if (pipelined) c->cur = stretch_buffer(c->cur, k);
+    else for (int j = 0; j < k; j++) c->cur = next_buffer(c->cur);
     // the drift watchdog after every multiple of watch_every steps
     if (c->watch_every > 0 && c->n / c->watch_every > n0 / c->watch_every) return enqueue_watch(c, false);
     return CPIC_OK;
@@ -611,9 +613,53 @@ static cpic_status eager_steps(cpic_ctx* c, int k)
     return CPIC_OK;
 }
 
-// a graph of k steps from buffer `parity`
+// Whether a stretch of k steps runs pipelined (step.hip): SU(3) particles with
+// the gather push on four wavefronts per group, no table or light-like paths
+// between the push and the next field update.  The third buffer set and the
+// second plaquette field are made here, once cpic_evolve has `steps` steps
+// behind and before it that pay for them (allocating and freeing 28 MB at 216^2
+// took 0.2 ms, the gain of 40 steps there; 8 steps after a restart are faster
+// without); without memory for them the steps stay separate launches.
+constexpr int64_t kPipelinePays = 32;
+static bool pipelined(cpic_ctx* c, int k, int64_t steps)
+{
+    if (!c->cfg.pipe || c->cfg.split != 3 || !pipeline_fits(c->N, (int)c->tsz) || k < 2) return false;
+    if (c->nc != 3 || c->np <= 0 || c->tpp != 4 || c->push_table || c->jets) return false;
+    if (c->fbuf[2]) return true;
+    if (steps < kPipelinePays) return false;
+    // graphs of separate steps from earlier calls are captured again
+    if (c->evolved > 0) {
+        if (hipStreamSynchronize(c->st) != hipSuccess) return false;
+        drop_graphs(c);
+    }
+    // one allocation: the fields, then the plaquettes
+    const size_t fbytes = (size_t)c->rps * c->V * c->tsz;
+    if (hipMalloc(&c->fbuf[2], fbytes + (size_t)kPlaqReals * c->V * c->tsz) == hipSuccess) {
+        c->gpl2 = static_cast<char*>(c->fbuf[2]) + fbytes;
+        return true;
+    }
+    (void)hipGetLastError();
+    c->fbuf[2] = nullptr;
+    c->cfg.pipe = 0;
+    return false;
+}
+template <typename T> static cpic_status launch_pipelined(cpic_ctx* c, int from, int k)
+{
+    T* const G[2] = {static_cast<T*>(c->gpl), static_cast<T*>(c->gpl2)};
+    auto S = [&](int j) { return F<T>(c, stretch_buffer(from, j)); };
+    const PushArgs a = push_args(c, 4);
+    HIPCHK(c, launch_field_step<T>(S(0), S(1), G[0], c->N, c->sc, c->d_step, c->cfg, c->st), "field step");
+    for (int j = 0; j + 1 < k; j++)
+        HIPCHK(c, launch_step<T>(S(j), S(j + 1), S(j + 2), G[j & 1], G[(j + 1) & 1], c->cfg, P<T>(c), a, j, c->d_step,
+                                 c->partials, c->d_err, c->st), "pipelined step");
+    HIPCHK(c, launch_push<T>(S(k - 1), S(k), G[(k - 1) & 1], P<T>(c), a, c->d_step, c->partials, c->d_err, c->st,
+                             KTimer{}, k - 1), "push");
+    return CPIC_OK;
+}
+
+// a graph of k steps from buffer `from`
 // sorted: the graph starts with the reordering of the records by tx x ty tiles
-static cpic_status build_graph(cpic_ctx* c, int parity, int k, bool sorted, int tx, int ty)
+static cpic_status build_graph(cpic_ctx* c, int from, int k, bool sorted, int tx, int ty, bool piped)
 {
     hipGraph_t g = nullptr;
     HIPCHK(c, hipStreamBeginCapture(c->st, hipStreamCaptureModeThreadLocal), "capture");
@@ -622,13 +668,17 @@ static cpic_status build_graph(cpic_ctx* c, int parity, int k, bool sorted, int 
         const hipError_t e = enqueue_sort(c, tx, ty);
         if (e != hipSuccess) s = hip_fail(c, e, "particle sort");
     }
-    for (int j = 0; j < k && s == CPIC_OK; j++)
-        s = c->prec == CPIC_FP64 ? launch_one<double>(c, parity ^ (j & 1), false)
-                                 : launch_one<float>(c, parity ^ (j & 1), false);
+    const bool dbl = c->prec == CPIC_FP64;
+    if (piped) {
+        if (s == CPIC_OK) s = dbl ? launch_pipelined<double>(c, from, k) : launch_pipelined<float>(c, from, k);
+    } else {
+        for (int j = 0, b = from; j < k && s == CPIC_OK; j++, b = next_buffer(b))
+            s = dbl ? launch_one<double>(c, b, false) : launch_one<float>(c, b, false);
+    }
     hipError_t e = hipStreamEndCapture(c->st, &g);
     if (s) { if (g) (void)hipGraphDestroy(g); return s; }
     if (e != hipSuccess) return hip_fail(c, e, "end capture");
-    e = hipGraphInstantiate(&c->gexec[sorted ? 1 : 0][parity][k], g, nullptr, nullptr, 0);
+    e = hipGraphInstantiate(&c->gexec[sorted ? 1 : 0][from][k], g, nullptr, nullptr, 0);
     (void)hipGraphDestroy(g);
     if (e != hipSuccess) return hip_fail(c, e, "graph instantiate");
     return CPIC_OK;
@@ -667,16 +717,18 @@ extern "C" cpic_status cpic_evolve(cpic_ctx* c, double tau_target_fm)
             if (so) return so;
         }
         // one graph up to the next reordering point, at most kGraphSteps steps
-        // (graphs of each length are captured once per buffer parity)
+        // (graphs of each length are captured once per buffer they start from)
         const int k = std::min(std::min(left, kGraphSteps), std::max(1, next_sort_point(c, c->n) - c->n));
-        const int parity = c->cur, sg = in_graph ? 1 : 0;
-        if (!c->gexec[sg][parity][k]) {
-            cpic_status s = build_graph(c, parity, k, in_graph, tx, ty);
+        const int from = c->cur, sg = in_graph ? 1 : 0;
+        const bool piped = pipelined(c, k, c->evolved + left);
+        if (!c->gexec[sg][from][k]) {
+            cpic_status s = build_graph(c, from, k, in_graph, tx, ty, piped);
             if (s) return s;
         }
-        HIPCHK(c, hipGraphLaunch(c->gexec[sg][parity][k], c->st), "graph launch");
+        HIPCHK(c, hipGraphLaunch(c->gexec[sg][from][k], c->st), "graph launch");
         if (in_graph) mark_sorted(c, tx, ty);
-        host_advance(c, k);
+        host_advance(c, k, piped);
+        c->evolved += k;
         left -= k;
     }
     return CPIC_OK;
@@ -1267,6 +1319,7 @@ extern "C" cpic_status cpic_set_launch(cpic_ctx* c, int32_t bx, int32_t by, int3
     c->cfg.xcd_remap = remap ? 1 : 0;
     c->cfg.waves = waves;
     c->cfg.roles = 0;  // the shape as given
+    c->cfg.pipe = 0;
     drop_graphs(c);
     return CPIC_OK;
 }
@@ -1334,7 +1387,7 @@ template <typename T> static cpic_status tune_t(cpic_ctx* c, int reps, std::stri
     int err0 = 0;
     HIPCHK(c, hipMemcpy(&err0, c->d_err, sizeof(int), hipMemcpyDeviceToHost), "tune");
     const LaunchCfg orig = c->cfg;  // the configuration before tuning (default or set by the caller)
-    const Fields<T> A = F<T>(c, c->cur), B = F<T>(c, c->cur ^ 1);
+    const Fields<T> A = F<T>(c, c->cur), B = F<T>(c, next_buffer(c->cur));
     T* const G = static_cast<T*>(c->gpl);
     hipEvent_t e0, e1;
     HIPCHK(c, hipEventCreate(&e0), "tune");
@@ -1540,13 +1593,14 @@ template <typename T> static cpic_status tune_t(cpic_ctx* c, int reps, std::stri
             for (const LaunchCfg& t : trials) have_orig = have_orig || same(t, orig);
             if (!have_orig) trials.push_back(orig);
             // two real steps from the saved state, per step (reps pairs after a warm-up pair)
-            auto time_pair = [&](double& per) -> cpic_status {
+            // piped: a pipelined stretch of four instead, the ends of a stretch included
+            auto time_pair = [&](double& per, bool piped = false) -> cpic_status {
                 double tot = 0;
                 for (int r = 0; r <= reps && te == hipSuccess; r++) {
                     te = hipEventRecord(e0, c->st);
                     cpic_status ls = CPIC_OK;
-                    if (te == hipSuccess) ls = launch_one<T>(c, c->cur, false);
-                    if (te == hipSuccess && !ls) ls = launch_one<T>(c, c->cur ^ 1, false);
+                    if (te == hipSuccess) ls = piped ? launch_pipelined<T>(c, c->cur, 4) : launch_one<T>(c, c->cur, false);
+                    if (te == hipSuccess && !ls && !piped) ls = launch_one<T>(c, next_buffer(c->cur), false);
                     if (ls) return ls;
                     if (te == hipSuccess) te = hipEventRecord(e1, c->st);
                     if (te == hipSuccess) te = hipEventSynchronize(e1);
@@ -1555,7 +1609,7 @@ template <typename T> static cpic_status tune_t(cpic_ctx* c, int reps, std::stri
                     if (te == hipSuccess) te = restore();
                     if (r > 0) tot += ms;
                 }
-                per = tot / reps / 2;
+                per = tot / reps / (piped ? 4 : 2);
                 return CPIC_OK;
             };
             LaunchCfg best_step = keep;
@@ -1622,6 +1676,23 @@ template <typename T> static cpic_status tune_t(cpic_ctx* c, int reps, std::stri
                 c->tpp = lanes[pick];
                 c->pblocks = push_blocks((int)c->np, c->tpp);
                 best_pair = step_t[pick];
+            }
+            // pipelined stretches, if that is how the steps ran before
+            // (kept on equality), against the best pair of separate steps
+            const int pair_tpp = c->tpp;
+            if (te == hipSuccess && orig.pipe && tpp0 == 4 && !c->push_table && c->n + 4 <= c->sc.n_max) {
+                double per = 1e300;
+                c->cfg = orig;
+                c->tpp = tpp0;
+                cpic_status ls = pipelined(c, 4, kPipelinePays) ? time_pair(per, true) : CPIC_OK;
+                if (ls) { c->cfg = keep; c->tpp = pair_tpp; (void)restore(); release(); return ls; }
+                if (per < 1e300) {
+                    std::snprintf(line, sizeof line, "step pipelined, four in a stretch: %.2f us\n", per * 1e3);
+                    rep += line;
+                }
+                if (per <= best_pair) { best_step = orig; best_pair = per; }
+                else { c->cfg = best_step; c->tpp = pair_tpp; }
+                c->pblocks = push_blocks((int)c->np, c->tpp);
             }
             release();
             if (te != hipSuccess) { c->cfg = keep; return hip_fail(c, te, "tune"); }

@@ -36,14 +36,16 @@ struct cpic_ctx {
     double a_fm = 0, a_gev = 0;
     cpic::Schedule sc{};
     int n = 0;    // host mirror of the device step counter
-    int cur = 0;  // buffer holding the state at step n
+    int64_t evolved = 0;  // steps cpic_evolve has launched
+    int cur = 0;  // buffer holding the state at step n (2 only after pipelined stretches)
     int64_t np = 0;
     bool is_static = false;
     double mhat = 0;
     double q0[8]{}, q0eig[3]{}, q2ref = 0, q3ref = 0;
-    void* fbuf[2] = {nullptr, nullptr};
+    void* fbuf[3] = {nullptr, nullptr, nullptr};  // the third from the first pipelined stretch on
     void* pr = nullptr;   // particle reals [19][np]
     void* gpl = nullptr;  // plaquette field G = Proj U_12 [8][V] for the push, force table and light-like paths
+    void* gpl2 = nullptr; // a second plaquette field (pipelined stretches; behind fbuf[2])
     int* pcell = nullptr;  // [2][np]
     int pblocks = 0, nslots = 0;
     double* partials = nullptr;  // [nslots][particle groups of 64][4]
@@ -76,12 +78,12 @@ struct cpic_ctx {
     int push_table = 0;   // 1: fields from a per-site force table (dense ensembles)
     void* ftab = nullptr; // [48][V] force table (table push, light-like paths)
     bool initialised = false;
-    // graphs: [sorted][parity][k] -> executable graph of k steps starting from
-    // buffer `parity` (k = kGraphSteps between reordering points, shorter ones
+    // graphs: [sorted][buffer][k] -> executable graph of k steps starting from
+    // buffer `cur` (k = kGraphSteps between reordering points, shorter ones
     // up to the next reordering point or the end of an evolve); sorted = 1:
     // the graph starts with the reordering of the records (moving particles
     // at a reordering point)
-    hipGraphExec_t gexec[2][2][cpic::kGraphSteps + 1] = {};
+    hipGraphExec_t gexec[2][3][cpic::kGraphSteps + 1] = {};
     // light-like paths (cpic_jets_enable)
     bool jets = false;
     cpic::JetArgs ja{};
@@ -120,8 +122,14 @@ cpic_status hip_fail(cpic_ctx* c, hipError_t e, const char* where);
 cpic_status maybe_sort(cpic_ctx* c);
 // first reordering point after step n (1 << 30 if none)
 int next_sort_point(const cpic_ctx* c, int n);
-// host bookkeeping of k launched steps (sample list, step counter, buffer parity)
-cpic_status host_advance(cpic_ctx* c, int k);
+// the buffer a step from buffer b writes: 0 and 1 alternate
+inline int next_buffer(int b) { return b == 0 ? 1 : 0; }
+// the buffer that holds step j of a pipelined stretch that starts from buffer b
+// (downwards from 1, so that stretches of 16 alternate between two buffers, and
+// so between two graphs)
+inline int stretch_buffer(int b, int j) { return (b + (b == 1 ? 2 : 1) * j) % 3; }
+// host bookkeeping of k launched steps (sample list, step counter, buffer)
+cpic_status host_advance(cpic_ctx* c, int k, bool pipelined = false);
 PushArgs push_args(const cpic_ctx* c, int tpp);
 // the drift watchdog's baseline of a newly installed state, before its first step
 cpic_status watch_prepare(cpic_ctx* c);

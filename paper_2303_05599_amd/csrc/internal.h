@@ -88,6 +88,7 @@ struct LaunchCfg {
                           // 3 as 2 with two rows per link in LDS and the scalars from global memory,
                           // 4 as 3 with the particle push of the tile in the same kernel (fused.hip)
     int nt_store = 0;     // variant 3 with particles: the new links and phi stored non-temporal
+    int pipe = 0;         // the default tiles: steps inside a graph may be pipelined (step.hip)
     int roles = 0;        // variant 3: four wavefronts per 64 sites instead of one (small lattices; bx, by unused)
 };
 // The field update of a new context, by lattice size (both precisions).  Up to
@@ -106,6 +107,7 @@ inline void default_field_launch(int N, LaunchCfg* cfg)
     cfg->split = 3;
     cfg->bx = 64;
     cfg->by = 4;
+    cfg->pipe = 1;
     if (N <= 384) {
         cfg->roles = 1;
         return;
@@ -216,7 +218,8 @@ hipError_t launch_fused(const Fields<T>& A, const Fields<T>& B, const LaunchCfg&
 // (gpl: the plaquette field of step n, see launch_field_step)
 template <typename T>
 hipError_t launch_push(const Fields<T>& A, const Fields<T>& B, const T* gpl, const Parts<T>& P, const PushArgs& a,
-                       int* d_step, double* partials, int* err, hipStream_t st, const KTimer& tm = KTimer{});
+                       int* d_step, double* partials, int* err, hipStream_t st, const KTimer& tm = KTimer{},
+                       int off = 0);
 int push_blocks(int np, int tpp);
 // the six field vectors of every site at t_n into table [48][V] (job order,
 // zero where a field is inactive at step n or, with electric_only, magnetic),
@@ -282,6 +285,18 @@ hipError_t launch_su2_push(const Fields2<T>& A, const Fields2<T>& B, const Parts
 template <typename T>
 hipError_t launch_su2_diag(const Fields2<T>& f, int N, double dt, int n, double* partials, int nblk_cap,
                            int* nblk_out, hipStream_t st);
+
+// ---- pipelined step (step.hip)
+// The push of step n beside the field update of step n + 1, in one launch: S0,
+// S1 the buffer sets of steps n and n + 1 (as A and B for the push), S2 receives
+// step n + 2; g0 the plaquette field of step n, g1 receives that of n + 1.  n =
+// d_step[1] + off, which no launch of the stretch changes.  a.tpp must be 4.
+// (three buffer sets within 224 MB: the measured line, see step.hip)
+inline bool pipeline_fits(int N, int bytes_per_real) { return 3ll * 56 * N * N * bytes_per_real <= 224ll << 20; }
+template <typename T>
+hipError_t launch_step(const Fields<T>& S0, const Fields<T>& S1, const Fields<T>& S2, const T* g0, T* g1,
+                       const LaunchCfg& cfg, const Parts<T>& P, const PushArgs& a, int off, int* d_step,
+                       double* partials, int* err, hipStream_t st);
 
 // ---- particle ordering (sort.hip)
 struct SortBufs {

@@ -1,0 +1,103 @@
+// step.hip -- the pipelined step: the particle push of step n and the field
+// update of step n + 1 in one launch.
+//
+// The field update needs nothing from the particles, so inside a stretch of
+// steps (one HIP graph) only the first field update and the last push run by
+// themselves.  Every launch between holds the workgroups of both: a lattice
+// that leaves most of the chip idle in either kernel (both wait for memory and
+// for serial chains of products there) runs them beside each other, the last
+// wave of the push is filled with tiles, and a step is one launch instead of
+// two.  It takes a third field buffer set (the update of step n + 1 may not
+// overwrite the state of step n, which the push reads) and a second plaquette
+// field.  The step counter does not move inside a stretch: the launches take
+// their offset from its first step as an argument.
+//
+// Each XCD starts with its share of the push, then takes its share of the tiles.
+// Spread evenly among each other instead they were slower wherever the chip is
+// full (both codes in one CU's instruction cache): 216^2 32.1 against 24.0 us
+// a step, 324^2 60.6 against 46.0; tiles first 26.5 and 49.2 (FP64, 0.35
+// particles per site).  Per step, two launches -> one, at that density:
+//   FP64: 32^2 17.2 -> 11.7 us, 96^2 19.7 -> 13.6, 216^2 28.9 -> 24.0,
+//         324^2 53.5 -> 46.0, 384^2 67.3 -> 59.7; 432^2 76.0 -> 76.6,
+//         512^2 108.7 -> 112.9
+//   FP32: 32^2 15.3 -> 10.5, 216^2 21.6 -> 15.5, 384^2 44.4 -> 36.0,
+//         432^2 48.6 -> 45.0, 512^2 61.1 -> 55.6; 648^2 96.9 -> 106.4
+//   with the colour log (FP64): 96^2 29.8 -> 23.8, 324^2 66.9 -> 55.5
+// The line (pipeline_fits) lies where three buffer sets stop fitting into the
+// 256 MB Infinity Cache beside the rest: 198 MB at 384^2 and 251 MB at 432^2 in
+// FP64, 176 MB at 512^2 and 282 MB at 648^2 in FP32.
+// The arithmetic is that of the separate kernels, bit for bit (fieldbody.h,
+// pushbody.h).
+#include <type_traits>
+
+#include "fieldbody.h"
+#include "pushbody.h"
+
+namespace cpic {
+
+template <typename T, bool ROLES, int CP, bool LOGQ>
+__global__ __launch_bounds__(256, 2) void step_kernel(Fields<T> S0, Fields<T> S1, Fields<T> S2, const T* g0, T* g1,
+                                                      Parts<T> P, PushArgs a, int off, int* d_step, double* partials,
+                                                      int* err)
+{
+    constexpr int BX = ROLES ? 16 : 64, BY = 4;
+    constexpr size_t field_lds = ROLES ? kRolesLds<T, 16, 4> : kCtileLds<T, 64, 4>, push_lds = sizeof(T) * 64 * kPushRows<4>;
+    __shared__ __align__(16) char smem[field_lds > push_lds ? field_lds : push_lds];
+    const int N = a.N, tiles = ((N + BX - 1) / BX) * ((N + BY - 1) / BY), blocks = (a.np + 63) / 64;
+    // entry i of XCD x: its push blocks, then its tiles
+    const int pt = (tiles + 7) / 8, pb = (blocks + 7) / 8, x = (int)blockIdx.x & 7, i = (int)blockIdx.x >> 3;
+    if (i < pb) {
+        const int blk = x * pb + i;
+        if (blk >= blocks) return;
+        const int n = __builtin_amdgcn_readfirstlane(d_step[1] + off);
+        push_body<T, 4, LOGQ>(S0, S1, g0, P, a, n, partials, err, blk, reinterpret_cast<T(*)[64]>(smem));
+    } else {
+        const int tile = x * pt + (i - pb);
+        if (tile >= tiles) return;
+        const StepSource step{d_step + 1, off + 1, nullptr};
+        if constexpr (ROLES) field_roles_body<T, BX, BY, CP>(S1, S2, g1, N, tile, a.sc, step, smem);
+        else field_ctile_body<T, BX, BY, CP>(S1, S2, g1, N, tile, a.sc, step, smem);
+    }
+}
+
+template <typename T, bool ROLES, int CP>
+static void launch_step_t(const Fields<T>& S0, const Fields<T>& S1, const Fields<T>& S2, const T* g0, T* g1,
+                          const Parts<T>& P, const PushArgs& a, int off, int* d_step, double* partials, int* err,
+                          hipStream_t st)
+{
+    const int N = a.N, bx = ROLES ? 16 : 64, tiles = ((N + bx - 1) / bx) * ((N + 3) / 4), blocks = (a.np + 63) / 64;
+    const dim3 g(8 * ((tiles + 7) / 8 + (blocks + 7) / 8)), b(256);
+    if (a.color_log)
+        hipLaunchKernelGGL((step_kernel<T, ROLES, CP, true>), g, b, 0, st, S0, S1, S2, g0, g1, P, a, off, d_step, partials, err);
+    else
+        hipLaunchKernelGGL((step_kernel<T, ROLES, CP, false>), g, b, 0, st, S0, S1, S2, g0, g1, P, a, off, d_step, partials, err);
+}
+
+template <typename T>
+hipError_t launch_step(const Fields<T>& S0, const Fields<T>& S1, const Fields<T>& S2, const T* g0, T* g1,
+                       const LaunchCfg& cfg, const Parts<T>& P, const PushArgs& a, int off, int* d_step,
+                       double* partials, int* err, hipStream_t st)
+{
+    if (a.np <= 0 || a.tpp != 4 || !g0 || !g1 || !S2.U || cfg.split != 3) return hipErrorInvalidValue;
+    auto go = [&](auto roles, auto cp) {
+        launch_step_t<T, decltype(roles)::value, decltype(cp)::value>(S0, S1, S2, g0, g1, P, a, off, d_step, partials, err, st);
+    };
+    using NT = std::integral_constant<int, kStoreNT>;
+    using Plain = std::integral_constant<int, 0>;
+    if (cfg.roles) {
+        if (cfg.nt_store) go(std::true_type{}, NT{}); else go(std::true_type{}, Plain{});
+    } else if constexpr (sizeof(T) == 4) {  // above 384^2 (default_field_launch), where only FP32 is pipelined
+        if (cfg.nt_store) go(std::false_type{}, NT{}); else go(std::false_type{}, Plain{});
+    } else {
+        return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+}
+template hipError_t launch_step<double>(const Fields<double>&, const Fields<double>&, const Fields<double>&,
+                                        const double*, double*, const LaunchCfg&, const Parts<double>&, const PushArgs&,
+                                        int, int*, double*, int*, hipStream_t);
+template hipError_t launch_step<float>(const Fields<float>&, const Fields<float>&, const Fields<float>&, const float*,
+                                       float*, const LaunchCfg&, const Parts<float>&, const PushArgs&, int, int*,
+                                       double*, int*, hipStream_t);
+
+}  // namespace cpic

@@ -28,6 +28,20 @@ template <typename T> __device__ __forceinline__ Nbr neighbours(int x, int y, in
             (uint32_t)(yp * N + xm) * b};
 }
 
+// Where a field update finds its step: n = *at + off; copy (may be NULL)
+// receives n for the step's push.
+struct StepSource {
+    const int* at;
+    int off;
+    int* copy;
+    __device__ __forceinline__ int read(bool first) const
+    {
+        const int n = at[0] + off;
+        if (first && copy) *copy = n;
+        return n;
+    }
+};
+
 // Workgroups are dealt round-robin to the 8 XCDs; with remapping, logical
 // block g of `total` goes to XCD g / per, so each XCD works on a contiguous
 // band of tiles and their shared halos stay in its L2.
