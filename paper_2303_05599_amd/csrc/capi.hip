@@ -613,8 +613,8 @@ static cpic_status eager_steps(cpic_ctx* c, int k)
     return CPIC_OK;
 }
 
-// Whether a stretch of k steps runs pipelined (step.hip): SU(3) particles with
-// the gather push on four wavefronts per group, no table or light-like paths
+// Whether a stretch of k steps runs pipelined (step.hip): SU(2), or SU(3) particles
+// with the gather push on four wavefronts per group, no table or light-like paths
 // between the push and the next field update.  The third buffer set and the
 // second plaquette field are made here, once cpic_evolve has `steps` steps
 // behind and before it that pay for them (allocating and freeing 28 MB at 216^2
@@ -623,8 +623,10 @@ static cpic_status eager_steps(cpic_ctx* c, int k)
 constexpr int64_t kPipelinePays = 32;
 static bool pipelined(cpic_ctx* c, int k, int64_t steps)
 {
-    if (!c->cfg.pipe || c->cfg.split != 3 || !pipeline_fits(c->N, (int)c->tsz) || k < 2) return false;
-    if (c->nc != 3 || c->np <= 0 || c->tpp != 4 || c->push_table || c->jets) return false;
+    // the two-row links, or quaternions, and scalars that a step reads and writes
+    const int site = (c->nc == 3 ? 56 : 20) * (int)c->tsz;
+    if (!c->cfg.pipe || !pipeline_fits(c->N, site) || k < 2 || c->np <= 0) return false;
+    if (c->nc == 3 && (c->cfg.split != 3 || c->tpp != 4 || c->push_table || c->jets)) return false;
     if (c->fbuf[2]) return true;
     if (steps < kPipelinePays) return false;
     // graphs of separate steps from earlier calls are captured again
@@ -634,7 +636,7 @@ static bool pipelined(cpic_ctx* c, int k, int64_t steps)
     }
     // one allocation: the fields, then the plaquettes
     const size_t fbytes = (size_t)c->rps * c->V * c->tsz;
-    if (hipMalloc(&c->fbuf[2], fbytes + (size_t)kPlaqReals * c->V * c->tsz) == hipSuccess) {
+    if (hipMalloc(&c->fbuf[2], fbytes + (c->nc == 3 ? (size_t)kPlaqReals * c->V * c->tsz : 0)) == hipSuccess) {
         c->gpl2 = static_cast<char*>(c->fbuf[2]) + fbytes;
         return true;
     }
@@ -645,6 +647,17 @@ static bool pipelined(cpic_ctx* c, int k, int64_t steps)
 }
 template <typename T> static cpic_status launch_pipelined(cpic_ctx* c, int from, int k)
 {
+    if (c->nc == 2) {
+        auto S = [&](int j) { return F2<T>(c, stretch_buffer(from, j)); };
+        const PushArgs a = push_args(c, 1);
+        HIPCHK(c, launch_su2_field<T>(S(0), S(1), c->N, c->sc, c->d_step, c->st), "field step");
+        for (int j = 0; j + 1 < k; j++)
+            HIPCHK(c, launch_su2_step<T>(S(j), S(j + 1), S(j + 2), P<T>(c), a, j, c->d_step, c->partials, c->d_err,
+                                         c->st), "pipelined step");
+        HIPCHK(c, launch_su2_push<T>(S(k - 1), S(k), P<T>(c), a, c->d_step, c->partials, c->d_err, c->st, KTimer{},
+                                     k - 1), "push");
+        return CPIC_OK;
+    }
     T* const G[2] = {static_cast<T*>(c->gpl), static_cast<T*>(c->gpl2)};
     auto S = [&](int j) { return F<T>(c, stretch_buffer(from, j)); };
     const PushArgs a = push_args(c, 4);

@@ -281,7 +281,10 @@ hipError_t launch_su2_field(const Fields2<T>& in, const Fields2<T>& out, int N, 
                             hipStream_t st, const KTimer& tm = KTimer{});
 template <typename T>
 hipError_t launch_su2_push(const Fields2<T>& A, const Fields2<T>& B, const Parts<T>& P, const PushArgs& a,
-                           int* d_step, double* partials, int* err, hipStream_t st, const KTimer& tm = KTimer{});
+                           int* d_step, double* partials, int* err, hipStream_t st, const KTimer& tm = KTimer{}, int off = 0);
+template <typename T>
+hipError_t launch_su2_step(const Fields2<T>& S0, const Fields2<T>& S1, const Fields2<T>& S2, const Parts<T>& P,
+                           const PushArgs& a, int off, const int* d_step, double* partials, int* err, hipStream_t st);
 template <typename T>
 hipError_t launch_su2_diag(const Fields2<T>& f, int N, double dt, int n, double* partials, int nblk_cap,
                            int* nblk_out, hipStream_t st);
@@ -292,7 +295,7 @@ hipError_t launch_su2_diag(const Fields2<T>& f, int N, double dt, int n, double*
 // step n + 2; g0 the plaquette field of step n, g1 receives that of n + 1.  n =
 // d_step[1] + off, which no launch of the stretch changes.  a.tpp must be 4.
 // (three buffer sets within 224 MB: the measured line, see step.hip)
-inline bool pipeline_fits(int N, int bytes_per_real) { return 3ll * 56 * N * N * bytes_per_real <= 224ll << 20; }
+inline bool pipeline_fits(int N, int bytes_per_site) { return 3ll * bytes_per_site * N * N <= 224ll << 20; }
 template <typename T>
 hipError_t launch_step(const Fields<T>& S0, const Fields<T>& S1, const Fields<T>& S2, const T* g0, T* g1,
                        const LaunchCfg& cfg, const Parts<T>& P, const PushArgs& a, int off, int* d_step,

@@ -25,7 +25,8 @@
 //   with the colour log (FP64): 96^2 29.8 -> 23.8, 324^2 66.9 -> 55.5
 // The line (pipeline_fits) lies where three buffer sets stop fitting into the
 // 256 MB Infinity Cache beside the rest: 198 MB at 384^2 and 251 MB at 432^2 in
-// FP64, 176 MB at 512^2 and 282 MB at 648^2 in FP32.
+// FP64, 176 MB at 512^2 and 282 MB at 648^2 in FP32.  SU(2) has its own kernel
+// (su2.hip) under the same rule.
 // The arithmetic is that of the separate kernels, bit for bit (fieldbody.h,
 // pushbody.h).
 #include <type_traits>

@@ -106,13 +106,10 @@ __device__ void kick2(const L2<T>& L, const T* phi, int V, const Nb2& c, T t, T 
 // one thread per site: kick at t_n (skipped at n = 0), drift at t_{n+1/2};
 // FP32 runs renormalise the link quaternions on reunitarisation steps
 template <typename T>
-__global__ __launch_bounds__(256) void su2_field_kernel(Fields2<T> in, Fields2<T> out, int N, Schedule sc, int* d_step)
+__device__ __forceinline__ void su2_field_body(const Fields2<T>& in, const Fields2<T>& out, int N, const Schedule& sc,
+                                               int n, int blk)
 {
-    const int V = N * N, nb = (V + 255) / 256;
-    const int blk = remap_block(nb);
-    if (blk >= nb) return;
-    const int n = d_step[0];
-    if (blk == 0 && threadIdx.x == 0) d_step[1] = n;
+    const int V = N * N;
     const int s = blk * 256 + (int)threadIdx.x;
     if (s >= V) return;
     const Nb2 c = nbrs(s % N, s / N, N);
@@ -149,6 +146,17 @@ __global__ __launch_bounds__(256) void su2_field_kernel(Fields2<T> in, Fields2<T
 }
 
 template <typename T>
+__global__ __launch_bounds__(256) void su2_field_kernel(Fields2<T> in, Fields2<T> out, int N, Schedule sc, int* d_step)
+{
+    const int nb = (N * N + 255) / 256;
+    const int blk = remap_block(nb);
+    if (blk >= nb) return;
+    const int n = d_step[0];
+    if (blk == 0 && threadIdx.x == 0) d_step[1] = n;
+    su2_field_body<T>(in, out, N, sc, n, blk);
+}
+
+template <typename T>
 hipError_t launch_su2_field(const Fields2<T>& in, const Fields2<T>& out, int N, const Schedule& sc, int* d_step,
                             hipStream_t st, const KTimer& tm)
 {
@@ -169,15 +177,10 @@ hipError_t launch_su2_field(const Fields2<T>& in, const Fields2<T>& out, int N, 
 // would leave about one and a half wavefronts per SIMD at 1e5 particles, too
 // few to cover the chains of dependent gathers.
 template <typename T>
-__global__ __launch_bounds__(256) void su2_push_kernel(Fields2<T> Af, Fields2<T> Bf, Parts<T> P, PushArgs a,
-                                                       int* d_step, double* partials, int* err)
+__device__ __forceinline__ void su2_push_body(const Fields2<T>& Af, const Fields2<T>& Bf, const Parts<T>& P,
+                                              const PushArgs& a, int n, int blk, double* partials, int* err)
 {
     const int np = a.np, N = a.N, V = N * N;
-    const int nb = (np + 63) / 64;
-    const int blk = remap_block(nb);
-    if (blk >= nb) return;
-    const int n = d_step[1];
-    if (blk == 0 && threadIdx.x == 0) d_step[0] = n + 1;
     if (n < a.sc.n_form || n >= a.sc.n_max) return;  // uniform over the grid
     __shared__ T shF[3][6][64];
     const int lane = (int)threadIdx.x & 63, role = (int)threadIdx.x >> 6;
@@ -362,12 +365,60 @@ __global__ __launch_bounds__(256) void su2_push_kernel(Fields2<T> Af, Fields2<T>
 }
 
 template <typename T>
+__global__ __launch_bounds__(256) void su2_push_kernel(Fields2<T> Af, Fields2<T> Bf, Parts<T> P, PushArgs a,
+                                                       int* d_step, int off, double* partials, int* err)
+{
+    const int nb = (a.np + 63) / 64;
+    const int blk = remap_block(nb);
+    if (blk >= nb) return;
+    const int n = d_step[1] + off;
+    if (blk == 0 && threadIdx.x == 0) d_step[0] = n + 1;
+    su2_push_body<T>(Af, Bf, P, a, n, blk, partials, err);
+}
+
+template <typename T>
 hipError_t launch_su2_push(const Fields2<T>& A, const Fields2<T>& B, const Parts<T>& P, const PushArgs& a,
-                           int* d_step, double* partials, int* err, hipStream_t st, const KTimer& tm)
+                           int* d_step, double* partials, int* err, hipStream_t st, const KTimer& tm, int off)
 {
     if (a.np <= 0) return hipSuccess;
     const int nb = (a.np + 63) / 64;
-    klaunch(tm, su2_push_kernel<T>, dim3(8 * ((nb + 7) / 8)), dim3(256), st, A, B, P, a, d_step, partials, err);
+    klaunch(tm, su2_push_kernel<T>, dim3(8 * ((nb + 7) / 8)), dim3(256), st, A, B, P, a, d_step, off, partials, err);
+    return hipGetLastError();
+}
+
+// ------------------------------------------------------------------ pipelined step
+// The push of step n and the field update of step n + 1 in one launch (step.hip
+// has the reasons and the protocol): each XCD's push blocks, then its sites.
+// A site holds 20 reals, so both kernels are short and the second launch and the
+// idle ends of each weigh more than in SU(3).  Per step with 0.35 particles per
+// site, two launches -> one, FP64: 32^2 12.9 -> 8.4 us, 216^2 15.5 -> 12.3, 432^2
+// 32.4 -> 29.2, 648^2 60.3 -> 55.7; FP32: 32^2 10.9 -> 7.1, 216^2 12.7 -> 8.8,
+// 432^2 21.6 -> 18.1, 648^2 39.3 -> 33.2, 1024^2 73.1 -> 72.4.  1024^2 in FP64 (three
+// buffer sets of 503 MB against the 256 MB last-level cache) stays with two.
+template <typename T>
+__global__ __launch_bounds__(256) void su2_step_kernel(Fields2<T> S0, Fields2<T> S1, Fields2<T> S2, Parts<T> P,
+                                                       PushArgs a, int off, const int* d_step, double* partials, int* err)
+{
+    const int sites = (a.N * a.N + 255) / 256, blocks = (a.np + 63) / 64;
+    const int ps = (sites + 7) / 8, pb = (blocks + 7) / 8, x = (int)blockIdx.x & 7, i = (int)blockIdx.x >> 3;
+    const int n = d_step[1] + off;
+    if (i < pb) {
+        const int blk = x * pb + i;
+        if (blk < blocks) su2_push_body<T>(S0, S1, P, a, n, blk, partials, err);
+    } else {
+        const int blk = x * ps + (i - pb);
+        if (blk < sites) su2_field_body<T>(S1, S2, a.N, a.sc, n + 1, blk);
+    }
+}
+
+template <typename T>
+hipError_t launch_su2_step(const Fields2<T>& S0, const Fields2<T>& S1, const Fields2<T>& S2, const Parts<T>& P,
+                           const PushArgs& a, int off, const int* d_step, double* partials, int* err, hipStream_t st)
+{
+    if (a.np <= 0 || !S2.U) return hipErrorInvalidValue;
+    const int sites = (a.N * a.N + 255) / 256, blocks = (a.np + 63) / 64;
+    hipLaunchKernelGGL(su2_step_kernel<T>, dim3(8 * ((sites + 7) / 8 + (blocks + 7) / 8)), dim3(256), 0, st, S0, S1, S2,
+                       P, a, off, d_step, partials, err);
     return hipGetLastError();
 }
 
@@ -440,7 +491,10 @@ hipError_t launch_su2_diag(const Fields2<T>& f, int N, double dt, int n, double*
     template hipError_t launch_su2_field<T>(const Fields2<T>&, const Fields2<T>&, int, const Schedule&, int*,      \
                                             hipStream_t, const KTimer&);                                           \
     template hipError_t launch_su2_push<T>(const Fields2<T>&, const Fields2<T>&, const Parts<T>&, const PushArgs&, \
-                                           int*, double*, int*, hipStream_t, const KTimer&);                        \
+                                           int*, double*, int*, hipStream_t, const KTimer&, int);                        \
+    template hipError_t launch_su2_step<T>(const Fields2<T>&, const Fields2<T>&, const Fields2<T>&,                  \
+                                           const Parts<T>&, const PushArgs&, int, const int*, double*, int*,         \
+                                           hipStream_t);                                                             \
     template hipError_t launch_su2_diag<T>(const Fields2<T>&, int, double, int, double*, int, int*, hipStream_t);
 CPIC_SU2_INST(double)
 CPIC_SU2_INST(float)

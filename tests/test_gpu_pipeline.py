@@ -22,11 +22,14 @@ def gpu():
     yield
 
 
-def make(N, prec, n, form, log, load=True):
+def make(N, prec, n, form, log, load=True, nc=3):
     L = 6.0 * N / 64
     ctx = cp.Context(dict(N=N, L_fm=L, n_sheets=1, tau_max_fm=256 * L / N / 8, precision=prec, reunit_every=5,
-                          record_every=3, seed=7),
+                          record_every=3, seed=7, n_colors=nc),
                      dict(n=n, mass_GeV=1.27, pT_max_GeV=3.0, tau_form_fm=form, color_update=cp.COLOR_LOG if log else cp.COLOR_ROTATE, seed=8))
+    if nc == 2:
+        ctx.init_mv()
+        return ctx
     ctx.set_push_lanes(4)
     if load:
         ctx.load_state(inputs.random_state(N, 4), 0, inputs.random_particles(n, N, 5))
@@ -59,6 +62,19 @@ def test_same_bits_as_single_steps(N, n, prec):
             ctx = make(N, prec, n, form, log)
             got.append(run(ctx, N, (1, 2, 3, 16, 7, 16, 18), graph))
             got[-1].append(ctx.observables())
+            ctx.close()
+        for a, b in zip(*got):
+            assert np.array_equal(a, b, equal_nan=True)
+
+
+@pytest.mark.parametrize("prec", [cp.FP64, cp.FP32])
+@pytest.mark.parametrize("N,n", [(4, 1), (16, 64), (27, 65), (96, 3001)])
+def test_same_bits_for_two_colours(N, n, prec):
+    for form in (0.0, 4.5 * 6.0 / 64 / 8):
+        got = []
+        for graph in (False, True):
+            ctx = make(N, prec, n, form, 0, nc=2)
+            got.append(run(ctx, N, (1, 2, 3, 16, 7, 16, 18), graph) + [ctx.observables()])
             ctx.close()
         for a, b in zip(*got):
             assert np.array_equal(a, b, equal_nan=True)
