@@ -304,18 +304,17 @@ hipError_t launch_step(const Fields<T>& S0, const Fields<T>& S1, const Fields<T>
 // ---- particle ordering (sort.hip)
 struct SortBufs {
     unsigned *keys = nullptr, *keys2 = nullptr;
-    int* perm = nullptr;
-    int *count = nullptr, *offs = nullptr;  // [key_cap] records per key (zero between reorderings), run ends
+    int* perm = nullptr;   // [2 np] records by key, each record's place among those of its key
+    int* count = nullptr;  // [key_cap + key_chunks] records per key (zero between reorderings), then per chunk of keys
+    int* offs = nullptr;   // [key_cap + 1] first record of every key
     int key_cap = 0;
-    void* temp = nullptr;  // the scan's temporary storage
-    size_t temp_bytes = 0;
     void* r2 = nullptr;  // [19][np] scratch records
     int *cell2 = nullptr, *pid2 = nullptr;
 };
 hipError_t launch_iota(int* p, int n, hipStream_t st);  // p[i] = i
 // keys of an N x N lattice lie below key_capacity(N) for every tile shape
 int key_capacity(int N);
-size_t sort_temp_bytes(int N);
+int key_chunks(int N);
 // Orders the records by tiles of tx x ty cells (keys from the nearest grid
 // point of the position with from_position, else from the cell); with
 // tile_start ([ntiles + 1]) also the range of records of every tile.  The

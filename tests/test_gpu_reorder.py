@@ -1,0 +1,55 @@
+"""The reordering of the particle records on both sides of the number of records
+where its form changes, on ragged lattices and tiles, with many records piled on
+one cell: the permutation of a stable sort, and no record changed on the way."""
+import math
+
+import numpy as np
+import pytest
+
+import inputs
+
+cp = pytest.importorskip("paper_2303_05599_amd")
+torch = pytest.importorskip("torch")
+parity = pytest.importorskip("test_gpu_parity")
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module", autouse=True)
+def gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    torch.cuda.set_device(0)
+    cp.lib()
+    yield
+
+
+@pytest.mark.parametrize("prec", [cp.FP64, cp.FP32])
+@pytest.mark.parametrize("N,n,piled,shape", [(6, 2, 0, None), (27, 15, 0, None), (27, 17, 9, None), (48, 1027, 300, None),
+                                             (81, 4096, 0, None), (81, 4097, 0, None), (96, 8190, 0, (16, 16)),
+                                             (96, 20003, 3000, (16, 16)), (162, 70001, 20000, None)])
+def test_stable_sort(tmp_path, N, n, piled, shape, prec):
+    L = 6.0 * N / 64
+    P = inputs.random_particles(n, N, 92, p_scale=0.6)
+    if piled:
+        sel = np.arange(0, 2 * piled, 2)
+        P[sel, 0], P[sel, 1] = 4.2, 2.4
+        P[sel, 14], P[sel, 15] = 4, 2
+    ctx = cp.Context(dict(N=N, L_fm=L, n_sheets=1, tau_max_fm=40 * L / N / 8, precision=prec),
+                     dict(n=n, mass_GeV=math.inf, tau_form_fm=0.0))
+    if shape:
+        ctx.set_launch(shape[0], shape[1], 1, 1, 4)
+    ctx.load_state(inputs.random_state(N, 91), 0, P)
+    before = ctx.get_state(cp.STATE_PARTICLES)
+    ctx.step(1)            # ordered by the cells of the records
+    after = ctx.get_state(cp.STATE_PARTICLES)
+    ctx.save(str(tmp_path / "o"))
+    ctx.close()
+    h, cell, pid = parity.internal_order(tmp_path / "o")
+    assert np.array_equal(np.sort(pid), np.arange(n))
+    tx, ty = shape or (32, 16)
+    cx, cy = cell.astype(np.int64)
+    key = ((cy // ty) * ((N + tx - 1) // tx) + cx // tx) * (tx * ty) + (cy % ty) * tx + cx % tx
+    assert np.array_equal(np.lexsort((pid, key)), np.arange(n))
+    # static records: all but the momenta stay, in the caller's order
+    keep = [0, 1, 2] + list(range(6, before.shape[1]))
+    assert np.array_equal(before[:, keep], after[:, keep])
