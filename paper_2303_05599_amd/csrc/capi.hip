@@ -387,6 +387,24 @@ cpic_status cpic::maybe_sort(cpic_ctx* c)
     return CPIC_OK;
 }
 
+// Moving particles installed between two reordering points of a run: the records
+// are ordered at once, not up to 15 pushes later, from a particle per 16 sites on
+// (sparser ones share few cache lines in any order).  Install + 1 / 8 steps in the
+// caller's (random) order -> ordered, FP64: 1000 particles at 64^2 102 / 289 -> 98 /
+// 218 us, 20011 at 216^2 329 / 845 -> 298 / 503, 90000 at 512^2 1112 / 3700 -> 881 /
+// 1652; sparse, 4000 at 512^2 217 / 809 -> 222 / 811, 8000 at 1024^2 558 / 2554 ->
+// 579 / 2534.
+constexpr int64_t kOrderInstalled = 256;
+static cpic_status order_installed(cpic_ctx* c)
+{
+    if (c->is_static || c->np < kOrderInstalled || 16 * c->np < (int64_t)c->V) return CPIC_OK;
+    if (c->n <= c->sc.n_form || c->n >= c->sc.n_max || is_sort_point(c, c->n)) return CPIC_OK;
+    int tx, ty;
+    sort_tiles(c, &tx, &ty);
+    HIPCHK(c, enqueue_sort(c, tx, ty), "particle sort");
+    return CPIC_OK;
+}
+
 static void drop_graphs(cpic_ctx* c)
 {
     for (auto& byp : c->gexec)
@@ -1087,8 +1105,10 @@ extern "C" cpic_status cpic_set_state(cpic_ctx* c, int32_t which, const void* sr
     }
     c->watch_base_due = true;  // the watchdog's baseline is the installed state
     HIPCHK(c, exchange_set(c, which, static_cast<const double*>(src)), "set state");
+    if (which != CPIC_STATE_PARTICLES) return CPIC_OK;
     // rows and records coincide again
-    return which == CPIC_STATE_PARTICLES ? reset_pid(c) : CPIC_OK;
+    const cpic_status s = reset_pid(c);
+    return s ? s : order_installed(c);
 }
 
 // ------------------------------------------------------------------ checkpoints

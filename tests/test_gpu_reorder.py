@@ -53,3 +53,20 @@ def test_stable_sort(tmp_path, N, n, piled, shape, prec):
     # static records: all but the momenta stay, in the caller's order
     keep = [0, 1, 2] + list(range(6, before.shape[1]))
     assert np.array_equal(before[:, keep], after[:, keep])
+
+
+@pytest.mark.parametrize("N,n,ordered", [(64, 255, False), (64, 256, True), (72, 323, False), (72, 324, True)])
+def test_installed_records_are_ordered(tmp_path, N, n, ordered):
+    """Moving particles installed between two reorderings: by the cell of the position, from the density of the rule on."""
+    L = 6.0 * N / 64
+    P = inputs.random_particles(n, N, 93, p_scale=0.3)
+    ctx = cp.Context(dict(N=N, L_fm=L, n_sheets=1, tau_max_fm=40 * L / N / 8),
+                     dict(n=n, mass_GeV=1.27, pT_max_GeV=3.0, tau_form_fm=0.0))
+    ctx.load_state(inputs.random_state(N, 91), 5, P)
+    assert np.array_equal(ctx.get_state(cp.STATE_PARTICLES), P)
+    ctx.save(str(tmp_path / "o"))
+    ctx.close()
+    h, cell, pid = parity.internal_order(tmp_path / "o")
+    x, y = np.floor(P[pid, 0] + 0.5).astype(int) % N, np.floor(P[pid, 1] + 0.5).astype(int) % N
+    key = ((y // 16) * ((N + 31) // 32) + x // 32) * 512 + (y % 16) * 32 + x % 32
+    assert np.array_equal(np.lexsort((pid, key)) if ordered else pid, np.arange(n))
