@@ -135,15 +135,16 @@ static void set_store_policy(cpic_ctx* c)
 // rotation at 1024^2 with 4e5 particles 250 / 288 / 327 us, with 1e6 418 / 423 /
 // 436, at 512^2 with 262144 88 / 99 / 96; FP32 at 1024^2 with 1e6 241 / 274 / 282,
 // at 512^2 with 1e6 188 / 217 / 216.  One is ahead in FP64 above a particle per
-// site (512^2, 1e6: 322 / 321 / 301; the default there is the force table), and
-// for the logarithm update, whose owner wavefront has the longest chain, from
-// about half a particle per site (512^2, 262144: 155 / 125 / 119; 1024^2, 4e5: 301 /
-// 320 / 388; below 1e5 particles four cover the latency).
+// site (512^2, 1e6: 322 / 321 / 301; the default there is the force table).  The
+// logarithm update, split over the four (pushbody.h), is faster with them in FP32
+// throughout (step at 512^2, four / one: 1.6e5 particles 61 / 80 us, 7.9e5 177 / 198) and in
+// FP64 up to a particle per site (1.6e5: 123 / 155, 2.6e5: 155 / 165, 7.9e5: 332 / 316;
+// 1024^2, 1e6: 666 / 679, 3.1e6: 1364 / 1228).
 static int default_push_lanes(const cpic_ctx* c)
 {
     if (c->nc == 2) return 1;
-    if (c->pp.color_update == CPIC_COLOR_LOG) return c->np <= (1 << 17) || 2 * c->np <= c->V ? 4 : 1;
-    return c->prec == CPIC_FP64 && c->np > (1 << 18) && c->np > c->V ? 1 : 4;
+    const int64_t few = c->pp.color_update == CPIC_COLOR_LOG ? 1 << 17 : 1 << 18;
+    return c->prec == CPIC_FP64 && c->np > few && c->np > c->V ? 1 : 4;
 }
 
 extern "C" cpic_status cpic_create(const cpic_glasma_params* gp, const cpic_particle_params* pp, void* hip_stream,

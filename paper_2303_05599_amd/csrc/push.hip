@@ -35,7 +35,7 @@ template <typename T, int TPP, bool LOGQ = false>
 __global__ __launch_bounds__(push_block_threads(TPP), (TPP == 8 && !LOGQ) ? 4 : 2) void push_kernel(
     Fields<T> Af, Fields<T> Bf, const T* gpl, Parts<T> P, PushArgs a, int* d_step, int off, double* partials, int* err)
 {
-    __shared__ T shF[kPushRows<TPP>][64];
+    __shared__ T shF[kPushRows<TPP, LOGQ>][64];
     const int nblocks = (a.np + kPushPPB<TPP> - 1) / kPushPPB<TPP>;
     const int blk = xcd_block(nblocks);
     if (blk >= nblocks) return;

@@ -103,8 +103,11 @@ __host__ __device__ constexpr int push_block_threads(int tpp) { return tpp == 8 
 // into LDS; after one barrier it contracts all of them with Q and takes the
 // Euler step.
 template <int TPP> constexpr int kPushPPB = push_block_threads(TPP) / TPP;  // particles per block
-// rows ([64]) of LDS for the helpers' field vectors
-template <int TPP> constexpr int kPushRows = TPP > 1 ? kPushPPB<TPP> / 64 * (TPP - 1) * kSlots<TPP> * 8 : 1;
+// rows ([64]) of LDS for the helpers' field vectors; with four waves and the
+// logarithm update also one gauge field
+template <int TPP> constexpr int kFieldRows = kPushPPB<TPP> / 64 * (TPP - 1) * kSlots<TPP> * 8;
+template <int TPP, bool LOGQ = false>
+constexpr int kPushRows = TPP > 1 ? kFieldRows<TPP> + (TPP == 4 && LOGQ ? 8 : 0) : 1;
 
 // Observables: on recording steps the owner wave of each group of 64 writes
 // the group's four double-precision sums to partials[slot][group][4]; they
@@ -153,9 +156,21 @@ __device__ __forceinline__ void push_particle(const Fields<T>& Af, const Fields<
     particle_cell(R, C, po, pi, N, a.is_static != 0, s);
     const Cell cell = make_cell<T>(s.nx, s.ny, N);
     T f[6] = {0, 0, 0, 0, 0, 0};
+    // The logarithm update's two generators are the longest chain and need
+    // nothing but the position: with four waves the owner takes one while the
+    // helpers evaluate the fields, and the helper with the least to do the other.
+    // Per step at 0.35 particles per site, FP64: 96^2 20.8 -> 13.4 us, 324^2 52.2 ->
+    // 46.5, 512^2 117.8 -> 106.4; FP32: 96^2 34.0 -> 11.4, 512^2 58.9 -> 53.8 (with the
+    // generator's earlier stop, su3.h).
+    constexpr bool SPLIT_LOG = LOGQ && TPP == 4;
+    a8<T> gen[2];
     if (role == 0) {
         particle_load_rotate<T, LOGQ, TPP == 8>(A, R, C, po, pi, cell, a, n, live, renorm, err, s);
         CPIC_PHASE();
+        if constexpr (SPLIT_LOG) {
+            if (live) gen[0] = particle_generator<T>(A, N, s, 0);
+            CPIC_PHASE();
+        }
         if (TABLE && live) {
             // all six table vectors gathered at once (one memory round trip)
             const View<T> TV = make_view<T>(table, 48, V);
@@ -180,6 +195,13 @@ __device__ __forceinline__ void push_particle(const Fields<T>& Af, const Fields<
         }
     } else if constexpr (TPP == 4) {
         helper4<T>(role, A, B, Gv, cell, n, t, eonly, shF, (grp * (TPP - 1) + role - 1) * S * 8, lane, live);
+        if constexpr (SPLIT_LOG)
+            if (role == 3) {
+                CPIC_PHASE();
+                gen[1] = particle_generator<T>(A, N, s, 1);
+#pragma unroll
+                for (int q = 0; q < 8; q++) shF[kFieldRows<TPP> + q][lane] = gen[1].v[q];
+            }
     } else if (TPP > 1) {
         // a helper wave: its sub-jobs, accumulated into its LDS slots (the
         // loop is unrolled, so each sub-job's code is specialised; with eight
@@ -220,7 +242,12 @@ __device__ __forceinline__ void push_particle(const Fields<T>& Af, const Fields<
             }
         }
     }
-    if (role == 0 && live) particle_update<T, LOGQ>(A, R, C, po, pi, cell, a, n, renorm, record, f, s, obs);
+    if constexpr (SPLIT_LOG)
+        if (role == 0)
+#pragma unroll
+            for (int q = 0; q < 8; q++) gen[1].v[q] = shF[kFieldRows<TPP> + q][lane];
+    if (role == 0 && live)
+        particle_update<T, LOGQ>(A, R, C, po, pi, cell, a, n, renorm, record, f, s, obs, SPLIT_LOG ? gen : nullptr);
 }
 
 // one particle per owner lane, particle blk * PPB + grp * 64 + lane; the

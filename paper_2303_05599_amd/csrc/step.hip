@@ -42,7 +42,7 @@ __global__ __launch_bounds__(256, 2) void step_kernel(Fields<T> S0, Fields<T> S1
                                                       int* err)
 {
     constexpr int BX = ROLES ? 16 : 64, BY = 4;
-    constexpr size_t field_lds = ROLES ? kRolesLds<T, 16, 4> : kCtileLds<T, 64, 4>, push_lds = sizeof(T) * 64 * kPushRows<4>;
+    constexpr size_t field_lds = ROLES ? kRolesLds<T, 16, 4> : kCtileLds<T, 64, 4>, push_lds = sizeof(T) * 64 * kPushRows<4, LOGQ>;
     __shared__ __align__(16) char smem[field_lds > push_lds ? field_lds : push_lds];
     const int N = a.N, tiles = ((N + BX - 1) / BX) * ((N + BY - 1) / BY), blocks = (a.np + 63) / 64;
     // entry i of XCD x: its push blocks, then its tiles

@@ -179,15 +179,26 @@ __device__ __forceinline__ void particle_load_rotate(const View<T>& A, const Vie
         if (!a.is_static && renorm && live) s.Q = renorm_charge(s.Q, a.q0eig);
 }
 
+// The gauge field A_i of the logarithm update at a particle: the generator of
+// the link i whose midpoint is nearest.
+template <typename T>
+__device__ __forceinline__ a8<T> particle_generator(const View<T>& A, int N, const Particle<T>& s, int i)
+{
+    const int x = i == 0 ? min((int)floor(s.x), N - 1) : s.nx, y = i == 0 ? s.ny : min((int)floor(s.y), N - 1);
+    constexpr T tol = sizeof(T) == 8 ? T(1e-15) : T(1e-7);
+    return link_generator(vU(A, (uint32_t)(y * N + x) * (uint32_t)sizeof(T), i), tol, 50);
+}
+
 // The Euler step with f[j] = Q . (field j at the cell) (job order E_x, E_y,
 // E_eta, B_x, B_y, B_eta), the stores of the new record, and on recording
 // steps the particle's four broadening terms in double precision (obs).
 // Static particles integrate only the momentum (p^z in the PPETA slot).
+// given: the two gauge fields of the logarithm update, if already evaluated.
 template <typename T, bool LOGQ>
 __device__ __forceinline__ void particle_update(const View<T>& A, const View<T>& R, const View<int>& C, uint32_t po,
                                                 uint32_t pi, const Cell& cell, const PushArgs& a, int n,
                                                 bool renorm, bool record, const T (&f)[6], Particle<T>& s,
-                                                double (&obs)[4])
+                                                double (&obs)[4], const a8<T>* given = nullptr)
 {
     const int N = a.N;
     const T dt = T(a.sc.dt), t = T(n * a.sc.dt);
@@ -213,10 +224,8 @@ __device__ __forceinline__ void particle_update(const View<T>& A, const View<T>&
         if constexpr (LOGQ) {
             // Q_{n+1} = Q_n + dt i[Q_n, M_n]
             CPIC_PHASE();
-            const int lx = min((int)floor(s.x), N - 1), ly = min((int)floor(s.y), N - 1);
-            constexpr T tol = sizeof(T) == 8 ? T(1e-15) : T(1e-7);
-            const a8<T> gx = link_generator(vU(A, (uint32_t)(s.ny * N + lx) * (uint32_t)sizeof(T), 0), tol, 50);
-            const a8<T> gy = link_generator(vU(A, (uint32_t)(ly * N + s.nx) * (uint32_t)sizeof(T), 1), tol, 50);
+            const a8<T> gx = given ? given[0] : particle_generator<T>(A, N, s, 0);
+            const a8<T> gy = given ? given[1] : particle_generator<T>(A, N, s, 1);
             const a8<T> ph = vA(A, cell.s, kCompPhi);
             const T veta = pe / ptau;
             a8<T> M;
