@@ -36,8 +36,12 @@
 
 namespace cpic {
 
+// Three workgroups per CU with the colour log (FP64: 168 registers with 6 spilled,
+// against 201): 384^2 at 0.35 particles per site 61.1 -> 57.2 us, 324^2 45.0 -> 43.4,
+// below 216^2 equal; with the rotation 12 are spilled and it lost up to 7 % (162^2
+// 16.6 -> 17.8, 384^2 57.3 -> 60.0).
 template <typename T, bool ROLES, int CP, bool LOGQ>
-__global__ __launch_bounds__(256, 2) void step_kernel(Fields<T> S0, Fields<T> S1, Fields<T> S2, const T* g0, T* g1,
+__global__ __launch_bounds__(256, LOGQ ? 3 : 2) void step_kernel(Fields<T> S0, Fields<T> S1, Fields<T> S2, const T* g0, T* g1,
                                                       Parts<T> P, PushArgs a, int off, int* d_step, double* partials,
                                                       int* err)
 {
