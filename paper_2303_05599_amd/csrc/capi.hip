@@ -636,25 +636,27 @@ static cpic_status eager_steps(cpic_ctx* c, int k)
 // between the push and the next field update.  The third buffer set and the
 // second plaquette field are made here, once cpic_evolve has `steps` steps
 // behind and before it that pay for them (allocating and freeing 28 MB at 216^2
-// took 0.2 ms, the gain of 40 steps there; 8 steps after a restart are faster
-// without); without memory for them the steps stay separate launches.
-constexpr int64_t kPipelinePays = 32;
+// took 0.2 ms, the gain of 40 steps there, and 0.5 to 0.9 ms from 60 MB on, of 50 to 120;
+// 8 steps after a restart are faster without); without memory for them the steps
+// stay separate launches.
+static int64_t pipeline_steps(size_t bytes) { return bytes <= (size_t)32 << 20 ? 32 : 64; }
 static bool pipelined(cpic_ctx* c, int k, int64_t steps)
 {
     // the two-row links, or quaternions, and scalars that a step reads and writes
     const int site = (c->nc == 3 ? 56 : 20) * (int)c->tsz;
-    if (!c->cfg.pipe || !pipeline_fits(c->N, site) || k < 2 || c->np <= 0) return false;
+    if (!c->cfg.pipe || !pipeline_pays(c->N, site) || k < 2 || c->np <= 0) return false;
     if (c->nc == 3 && (c->cfg.split != 3 || c->tpp != 4 || c->push_table || c->jets)) return false;
     if (c->fbuf[2]) return true;
-    if (steps < kPipelinePays) return false;
+    // one allocation: the fields, then the plaquettes
+    const size_t fbytes = (size_t)c->rps * c->V * c->tsz;
+    const size_t bytes = fbytes + (c->nc == 3 ? (size_t)kPlaqReals * c->V * c->tsz : 0);
+    if (steps < pipeline_steps(bytes)) return false;
     // graphs of separate steps from earlier calls are captured again
     if (c->evolved > 0) {
         if (hipStreamSynchronize(c->st) != hipSuccess) return false;
         drop_graphs(c);
     }
-    // one allocation: the fields, then the plaquettes
-    const size_t fbytes = (size_t)c->rps * c->V * c->tsz;
-    if (hipMalloc(&c->fbuf[2], fbytes + (c->nc == 3 ? (size_t)kPlaqReals * c->V * c->tsz : 0)) == hipSuccess) {
+    if (hipMalloc(&c->fbuf[2], bytes) == hipSuccess) {
         c->gpl2 = static_cast<char*>(c->fbuf[2]) + fbytes;
         return true;
     }
@@ -1717,7 +1719,7 @@ template <typename T> static cpic_status tune_t(cpic_ctx* c, int reps, std::stri
                 double per = 1e300;
                 c->cfg = orig;
                 c->tpp = tpp0;
-                cpic_status ls = pipelined(c, 4, kPipelinePays) ? time_pair(per, true) : CPIC_OK;
+                cpic_status ls = pipelined(c, 4, INT64_MAX) ? time_pair(per, true) : CPIC_OK;
                 if (ls) { c->cfg = keep; c->tpp = pair_tpp; (void)restore(); release(); return ls; }
                 if (per < 1e300) {
                     std::snprintf(line, sizeof line, "step pipelined, four in a stretch: %.2f us\n", per * 1e3);

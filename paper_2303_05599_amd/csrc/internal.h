@@ -294,8 +294,13 @@ hipError_t launch_su2_diag(const Fields2<T>& f, int N, double dt, int n, double*
 // S1 the buffer sets of steps n and n + 1 (as A and B for the push), S2 receives
 // step n + 2; g0 the plaquette field of step n, g1 receives that of n + 1.  n =
 // d_step[1] + off, which no launch of the stretch changes.  a.tpp must be 4.
-// (three buffer sets within 224 MB: the measured line, see step.hip)
-inline bool pipeline_fits(int N, int bytes_per_site) { return 3ll * bytes_per_site * N * N <= 224ll << 20; }
+// Where a pipelined step pays (step.hip): three buffer sets fit the last-level cache
+// beside the rest, or not even two do.
+inline bool pipeline_pays(int N, int bytes_per_site)
+{
+    const long long set = (long long)bytes_per_site * N * N;
+    return 3 * set <= 224ll << 20 || 2 * set > 240ll << 20;
+}
 template <typename T>
 hipError_t launch_step(const Fields<T>& S0, const Fields<T>& S1, const Fields<T>& S2, const T* g0, T* g1,
                        const LaunchCfg& cfg, const Parts<T>& P, const PushArgs& a, int off, int* d_step,

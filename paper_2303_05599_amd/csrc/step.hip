@@ -23,10 +23,14 @@
 //   FP32: 32^2 15.3 -> 10.5, 216^2 21.6 -> 15.5, 384^2 44.4 -> 36.0,
 //         432^2 48.6 -> 45.0, 512^2 61.1 -> 55.6; 648^2 96.9 -> 106.4
 //   with the colour log (FP64): 96^2 29.8 -> 23.8, 324^2 66.9 -> 55.5
-// The line (pipeline_fits) lies where three buffer sets stop fitting into the
-// 256 MB Infinity Cache beside the rest: 198 MB at 384^2 and 251 MB at 432^2 in
-// FP64, 176 MB at 512^2 and 282 MB at 648^2 in FP32.  SU(2) has its own kernel
-// (su2.hip) under the same rule.
+// Between two lines (pipeline_pays) the steps stay separate: where two buffer sets
+// fit into the 256 MB Infinity Cache and three do not, the third one costs more
+// memory traffic than the overlap saves (512^2 FP64, 648^2 FP32 above).  Where two do
+// not fit either, the push and the field update wait for memory in turns and share
+// the state of step n + 1: FP64 768^2 287 -> 275 us, 1024^2 468 -> 457 (with 0.1
+// particles per site 401 -> 384); FP32 768^2 141 -> 140 (134 -> 127), 1024^2 270 -> 262
+// (235 -> 220), at 0.4 particles per site.  SU(2) has its own kernel (su2.hip) under
+// the same rule.
 // The arithmetic is that of the separate kernels, bit for bit (fieldbody.h,
 // pushbody.h).
 #include <type_traits>
@@ -41,7 +45,7 @@ namespace cpic {
 // below 216^2 equal; with the rotation 12 are spilled and it lost up to 7 % (162^2
 // 16.6 -> 17.8, 384^2 57.3 -> 60.0).
 template <typename T, bool ROLES, int CP, bool LOGQ>
-__global__ __launch_bounds__(256, LOGQ ? 3 : 2) void step_kernel(Fields<T> S0, Fields<T> S1, Fields<T> S2, const T* g0, T* g1,
+__global__ __launch_bounds__(256, LOGQ && ROLES ? 3 : 2) void step_kernel(Fields<T> S0, Fields<T> S1, Fields<T> S2, const T* g0, T* g1,
                                                       Parts<T> P, PushArgs a, int off, int* d_step, double* partials,
                                                       int* err)
 {
@@ -91,10 +95,8 @@ hipError_t launch_step(const Fields<T>& S0, const Fields<T>& S1, const Fields<T>
     using Plain = std::integral_constant<int, 0>;
     if (cfg.roles) {
         if (cfg.nt_store) go(std::true_type{}, NT{}); else go(std::true_type{}, Plain{});
-    } else if constexpr (sizeof(T) == 4) {  // above 384^2 (default_field_launch), where only FP32 is pipelined
-        if (cfg.nt_store) go(std::false_type{}, NT{}); else go(std::false_type{}, Plain{});
     } else {
-        return hipErrorInvalidValue;
+        if (cfg.nt_store) go(std::false_type{}, NT{}); else go(std::false_type{}, Plain{});
     }
     return hipGetLastError();
 }

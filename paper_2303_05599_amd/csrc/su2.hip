@@ -393,8 +393,7 @@ hipError_t launch_su2_push(const Fields2<T>& A, const Fields2<T>& B, const Parts
 // idle ends of each weigh more than in SU(3).  Per step with 0.35 particles per
 // site, two launches -> one, FP64: 32^2 12.9 -> 8.4 us, 216^2 15.5 -> 12.3, 432^2
 // 32.4 -> 29.2, 648^2 60.3 -> 55.7; FP32: 32^2 10.9 -> 7.1, 216^2 12.7 -> 8.8,
-// 432^2 21.6 -> 18.1, 648^2 39.3 -> 33.2, 1024^2 73.1 -> 72.4.  1024^2 in FP64 (three
-// buffer sets of 503 MB against the 256 MB last-level cache) stays with two.
+// 432^2 21.6 -> 18.1, 648^2 39.3 -> 33.2; 1024^2 in FP64 191.9 -> 182.4.
 template <typename T>
 __global__ __launch_bounds__(256) void su2_step_kernel(Fields2<T> S0, Fields2<T> S1, Fields2<T> S2, Parts<T> P,
                                                        PushArgs a, int off, const int* d_step, double* partials, int* err)
