@@ -373,8 +373,8 @@ cpic_status cpic_set_push_lanes(cpic_ctx* ctx, int32_t lanes);
  *                     kernel that gathers their fields.  It pays where the
  *                     particles are dense enough that evaluating the fields
  *                     at every site costs less than at every particle.
- * The default is the gather push (the force table with more particles than
- * sites).
+ * The default is the gather push; the force table from 1.5 particles per site
+ * on, and from 16384 particles on when light-like paths are enabled.
  * The three give the same arithmetic per particle up to rounding.  SU(3) with
  * the rotation colour update only for the table and tile modes; cpic_tune
  * times them.  Kernel timing counts the table kernel as push time, the fused

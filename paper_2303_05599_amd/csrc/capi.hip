@@ -147,6 +147,18 @@ static int default_push_lanes(const cpic_ctx* c)
     return c->prec == CPIC_FP64 && c->np > few && c->np > c->V ? 1 : 4;
 }
 
+// Whether the push reads a force table, evaluated once per site: from 1.5 particles
+// per site on (steps, gather / table: FP64 512^2 at 1.1 per site 160 / 191 us, 1.5 178 /
+// 201, 2.5 248 / 234, 324^2 at 1.1 60 / 70, 2.5 105 / 84; FP32 512^2 at 1.1 78 / 86, 1.5 93 /
+// 91, 2.5 140 / 112, 324^2 at 1.1 38 / 42, 2.5 60 / 49).  Beside the light-like paths, which
+// need the table anyway, from 16384 particles on (FP32 96^2, 11060 particles 26.0 / 25.6;
+// 216^2, 23329: 34.0 / 32.1; 512^2, 26215: 106 / 93, 2621: 100 / 103).
+static bool default_push_table(const cpic_ctx* c)
+{
+    if (c->nc != 3 || c->pp.color_update != CPIC_COLOR_ROTATE) return false;
+    return 2 * c->np > 3 * (int64_t)c->V || (c->jets && c->np >= 16384);
+}
+
 extern "C" cpic_status cpic_create(const cpic_glasma_params* gp, const cpic_particle_params* pp, void* hip_stream,
                                    cpic_ctx** out)
 {
@@ -252,8 +264,7 @@ extern "C" cpic_status cpic_create(const cpic_glasma_params* gp, const cpic_part
         }
     }
     c->tpp = default_push_lanes(c);
-    // more particles than sites: evaluate the fields once per site (force table)
-    c->push_table = c->nc == 3 && c->np > c->V && c->pp.color_update == CPIC_COLOR_ROTATE;
+    c->push_table = default_push_table(c);
     if (e == hipSuccess && c->push_table) e = hipMalloc(&c->ftab, (size_t)48 * c->V * c->tsz);
     // field update by lattice size.  The fused step (variant 4) is chosen
     // explicitly: at 512^2 with 1e5 particles it computes the fields at every
@@ -632,8 +643,9 @@ static cpic_status eager_steps(cpic_ctx* c, int k)
 }
 
 // Whether a stretch of k steps runs pipelined (step.hip): SU(2), or SU(3) particles
-// with the gather push on four wavefronts per group, no table or light-like paths
-// between the push and the next field update.  The third buffer set and the
+// with the gather push on four wavefronts per group or with the table push (the
+// force table and the light-like paths run before the push, which the paths do not
+// need).  The third buffer set and the
 // second plaquette field are made here, once cpic_evolve has `steps` steps
 // behind and before it that pay for them (allocating and freeing 28 MB at 216^2
 // took 0.2 ms, the gain of 40 steps there, and 0.5 to 0.9 ms from 60 MB on, of 50 to 120;
@@ -645,7 +657,15 @@ static bool pipelined(cpic_ctx* c, int k, int64_t steps)
     // the two-row links, or quaternions, and scalars that a step reads and writes
     const int site = (c->nc == 3 ? 56 : 20) * (int)c->tsz;
     if (!c->cfg.pipe || !pipeline_pays(c->N, site) || k < 2 || c->np <= 0) return false;
-    if (c->nc == 3 && (c->cfg.split != 3 || c->tpp != 4 || c->push_table || c->jets)) return false;
+    if (c->nc == 3 && (c->cfg.split != 3 || (c->tpp != 4 && !c->push_table))) return false;
+    if (uses_table(c)) {
+        // the table, the paths and the records of a dense ensemble take part in every
+        // step: all of it within the line of step.hip (512^2 FP32, 4e5 particles, 259 MB:
+        // 90.0 -> 92.7 us a step; 324^2 FP64, 1.6e5, 206 MB: 77.3 -> 72.9, 4.2e5, 248 MB:
+        // 103.5 -> 105.3), and no gain above the second line there
+        const int64_t reals = (3 * 56 + 48 + (c->jets ? 42 : 0)) * (int64_t)c->V + (int64_t)kPartReals * c->np;
+        if (reals * (int64_t)c->tsz > (int64_t)224 << 20) return false;
+    }
     if (c->fbuf[2]) return true;
     // one allocation: the fields, then the plaquettes
     const size_t fbytes = (size_t)c->rps * c->V * c->tsz;
@@ -680,13 +700,27 @@ template <typename T> static cpic_status launch_pipelined(cpic_ctx* c, int from,
     }
     T* const G[2] = {static_cast<T*>(c->gpl), static_cast<T*>(c->gpl2)};
     auto S = [&](int j) { return F<T>(c, stretch_buffer(from, j)); };
-    const PushArgs a = push_args(c, 4);
+    const PushArgs a = push_args(c, c->push_table ? 1 : 4);
+    T* const table = static_cast<T*>(c->ftab);
     HIPCHK(c, launch_field_step<T>(S(0), S(1), G[0], c->N, c->sc, c->d_step, c->cfg, c->st), "field step");
-    for (int j = 0; j + 1 < k; j++)
-        HIPCHK(c, launch_step<T>(S(j), S(j + 1), S(j + 2), G[j & 1], G[(j + 1) & 1], c->cfg, P<T>(c), a, j, c->d_step,
-                                 c->partials, c->d_err, c->st), "pipelined step");
-    HIPCHK(c, launch_push<T>(S(k - 1), S(k), G[(k - 1) & 1], P<T>(c), a, c->d_step, c->partials, c->d_err, c->st,
-                             KTimer{}, k - 1), "push");
+    for (int j = 0; j < k; j++) {
+        if (uses_table(c))
+            HIPCHK(c, launch_force_table<T>(S(j), S(j + 1), G[j & 1], table, c->N, table_schedule(c),
+                                            c->is_static && !c->jets, c->d_step, c->st, KTimer{}, j), "force table");
+        if (c->jets)
+            HIPCHK(c, launch_jets<T>(S(j), table, static_cast<T*>(c->jW), static_cast<T*>(c->jF), c->ja, c->d_step,
+                                     c->jpartials, c->st, KTimer{}, j), "light-like paths");
+        if (j + 1 < k)
+            HIPCHK(c, launch_step<T>(S(j), S(j + 1), S(j + 2), G[j & 1], G[(j + 1) & 1], c->cfg, P<T>(c), a,
+                                     c->push_table ? table : nullptr, j, c->d_step, c->partials, c->d_err, c->st),
+                   "pipelined step");
+        else if (c->push_table)
+            HIPCHK(c, launch_push_table<T>(S(j), S(j + 1), table, P<T>(c), a, c->d_step, c->partials, c->d_err, c->st,
+                                           KTimer{}, j), "table push");
+        else
+            HIPCHK(c, launch_push<T>(S(j), S(j + 1), G[j & 1], P<T>(c), a, c->d_step, c->partials, c->d_err, c->st,
+                                     KTimer{}, j), "push");
+    }
     return CPIC_OK;
 }
 
@@ -1715,10 +1749,10 @@ template <typename T> static cpic_status tune_t(cpic_ctx* c, int reps, std::stri
             // pipelined stretches, if that is how the steps ran before
             // (kept on equality), against the best pair of separate steps
             const int pair_tpp = c->tpp;
-            if (te == hipSuccess && orig.pipe && tpp0 == 4 && !c->push_table && c->n + 4 <= c->sc.n_max) {
+            if (te == hipSuccess && orig.pipe && (c->push_table || tpp0 == 4) && c->n + 4 <= c->sc.n_max) {
                 double per = 1e300;
                 c->cfg = orig;
-                c->tpp = tpp0;
+                if (!c->push_table) c->tpp = tpp0;
                 cpic_status ls = pipelined(c, 4, INT64_MAX) ? time_pair(per, true) : CPIC_OK;
                 if (ls) { c->cfg = keep; c->tpp = pair_tpp; (void)restore(); release(); return ls; }
                 if (per < 1e300) {
@@ -1751,6 +1785,7 @@ extern "C" cpic_status cpic_tune(cpic_ctx* c, int32_t reps, char* report, size_t
     if (reps < 1) reps = 1;
     if (c->timing) return fail(c, CPIC_E_INVALID, "cpic_tune: disable timing first");
     HIPCHK(c, hipStreamSynchronize(c->st), "tune");
+    c->push_set = true;
     std::string rep;
     if (c->nc == 2) {
         rep = "SU(2): one launch shape (256 sites or particles per workgroup); nothing to tune\n";
@@ -1780,6 +1815,7 @@ extern "C" cpic_status cpic_set_push_lanes(cpic_ctx* c, int32_t lanes)
         return fail(c, CPIC_E_INVALID, "cpic_set_push_lanes: 1, 2, 4 or 8");
     if (c->nc == 2 && lanes != 1) return fail(c, CPIC_E_INVALID, "cpic_set_push_lanes: the SU(2) push takes 1");
     HIPCHK(c, hipStreamSynchronize(c->st), "set push lanes");
+    c->push_set = true;
     c->tpp = lanes;
     c->pblocks = c->np > 0 ? push_blocks((int)c->np, lanes) : 0;
     drop_graphs(c);
@@ -1845,6 +1881,7 @@ extern "C" cpic_status cpic_jets_enable(cpic_ctx* c, const cpic_jet_params* jp)
     c->jobs_reduced = 0;
     c->jets = true;
     if (c->cfg.split == 4) c->cfg.split = 3;  // the paths read the force table: a separate push
+    if (!c->push_set) c->push_table = default_push_table(c);
     set_store_policy(c);
     drop_graphs(c);
     return CPIC_OK;
@@ -1935,6 +1972,7 @@ extern "C" cpic_status cpic_set_push_mode(cpic_ctx* c, int32_t mode)
                     "cpic_set_push_mode: the tile push needs SU(3) particles with the rotation colour update and no "
                     "light-like paths");
     HIPCHK(c, hipStreamSynchronize(c->st), "set push mode");
+    c->push_set = true;
     if (mode == CPIC_PUSH_TILE) {
         if (c->cfg.split != 4) {
             c->cfg.split = 4;

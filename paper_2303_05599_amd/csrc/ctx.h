@@ -75,6 +75,7 @@ struct cpic_ctx {
     int dcap = 0;
     cpic::LaunchCfg cfg{};
     int tpp = 1;          // wavefronts per particle group in the gather push (1, 2, 4, 8)
+    bool push_set = false;  // push mode or lanes chosen by the caller or the tuner
     int push_table = 0;   // 1: fields from a per-site force table (dense ensembles)
     void* ftab = nullptr; // [48][V] force table (table push, light-like paths)
     bool initialised = false;

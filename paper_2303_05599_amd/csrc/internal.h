@@ -227,7 +227,7 @@ int push_blocks(int np, int tpp);
 template <typename T>
 hipError_t launch_force_table(const Fields<T>& A, const Fields<T>& B, const T* gpl, T* table, int N,
                               const Schedule& sc, bool electric_only, const int* d_step, hipStream_t st,
-                              const KTimer& tm = KTimer{});
+                              const KTimer& tm = KTimer{}, int off = 0);
 // the stragglers of the fused step (A, B as for the push, B_eta from the links)
 template <typename T>
 hipError_t launch_stragglers(const Fields<T>& A, const Fields<T>& B, const Parts<T>& P, const PushArgs& a,
@@ -238,7 +238,7 @@ hipError_t launch_stragglers(const Fields<T>& A, const Fields<T>& B, const Parts
 template <typename T>
 hipError_t launch_push_table(const Fields<T>& A, const Fields<T>& B, const T* table, const Parts<T>& P,
                              const PushArgs& a, int* d_step, double* partials, int* err, hipStream_t st,
-                             const KTimer& tm = KTimer{});
+                             const KTimer& tm = KTimer{}, int off = 0);
 template <typename T>
 hipError_t launch_batch_push(const EventDesc* ev, const int2* map, int total_blocks, int tpp, hipStream_t st);
 hipError_t launch_reduce_rows(const double* partials, int nrows, int ncols, double* out, hipStream_t st);
@@ -271,7 +271,7 @@ struct JetArgs {
 // A holds U(n); table the force table of step n (launch_force_table)
 template <typename T>
 hipError_t launch_jets(const Fields<T>& A, const T* table, T* W, T* F, const JetArgs& a, const int* d_step,
-                       double* partials, hipStream_t st, const KTimer& tm = KTimer{});
+                       double* partials, hipStream_t st, const KTimer& tm = KTimer{}, int off = 0);
 // samples: partials[slot][group of 64 paths][4] (|F_x|^2, |F_y|^2, |F_z|^2, 0)
 __host__ __device__ inline int jet_groups(int V) { return (V + 63) / 64; }
 
@@ -293,7 +293,8 @@ hipError_t launch_su2_diag(const Fields2<T>& f, int N, double dt, int n, double*
 // The push of step n beside the field update of step n + 1, in one launch: S0,
 // S1 the buffer sets of steps n and n + 1 (as A and B for the push), S2 receives
 // step n + 2; g0 the plaquette field of step n, g1 receives that of n + 1.  n =
-// d_step[1] + off, which no launch of the stretch changes.  a.tpp must be 4.
+// d_step[1] + off, which no launch of the stretch changes.  With table (the force
+// table of step n) the table push, else the gather push with a.tpp = 4.
 // Where a pipelined step pays (step.hip): three buffer sets fit the last-level cache
 // beside the rest, or not even two do.
 inline bool pipeline_pays(int N, int bytes_per_site)
@@ -303,8 +304,8 @@ inline bool pipeline_pays(int N, int bytes_per_site)
 }
 template <typename T>
 hipError_t launch_step(const Fields<T>& S0, const Fields<T>& S1, const Fields<T>& S2, const T* g0, T* g1,
-                       const LaunchCfg& cfg, const Parts<T>& P, const PushArgs& a, int off, int* d_step,
-                       double* partials, int* err, hipStream_t st);
+                       const LaunchCfg& cfg, const Parts<T>& P, const PushArgs& a, const T* table, int off,
+                       int* d_step, double* partials, int* err, hipStream_t st);
 
 // ---- particle ordering (sort.hip)
 struct SortBufs {

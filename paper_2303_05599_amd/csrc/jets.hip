@@ -38,13 +38,13 @@ constexpr int kJetRoles = 3;
 
 template <typename T>
 __global__ __launch_bounds__(64 * kJetRoles) void jet_kernel(Fields<T> Af, const T* table, T* Wb, T* Fb, JetArgs a,
-                                                             const int* d_step, double* partials)
+                                                             const int* d_step, int off, double* partials)
 {
     const int N = a.N, V = N * N;
     const int ngroups = jet_groups(V);
     const int group = xcd_block(ngroups);
     if (group >= ngroups) return;
-    const int n = d_step[1];
+    const int n = d_step[1] + off;
     if (n < a.sc.n_form || n >= a.sc.n_max) return;  // uniform over the grid
     const int m = n - a.sc.n_form;
     const int k = path_offset(a.x_off, m, a.sc.dt);
@@ -125,17 +125,17 @@ __global__ __launch_bounds__(64 * kJetRoles) void jet_kernel(Fields<T> Af, const
 
 template <typename T>
 hipError_t launch_jets(const Fields<T>& A, const T* table, T* W, T* F, const JetArgs& a, const int* d_step,
-                       double* partials, hipStream_t st, const KTimer& tm)
+                       double* partials, hipStream_t st, const KTimer& tm, int off)
 {
     if (!table || !W || !F || a.N <= 0 || a.stride < 1 || !(a.sc.dt > 0 && a.sc.dt <= 1)) return hipErrorInvalidValue;
     const int nb = jet_groups(a.N * a.N);
-    klaunch(tm, jet_kernel<T>, dim3(8 * ((nb + 7) / 8)), dim3(64 * kJetRoles), st, A, table, W, F, a, d_step,
+    klaunch(tm, jet_kernel<T>, dim3(8 * ((nb + 7) / 8)), dim3(64 * kJetRoles), st, A, table, W, F, a, d_step, off,
             partials);
     return hipGetLastError();
 }
 template hipError_t launch_jets<double>(const Fields<double>&, const double*, double*, double*, const JetArgs&,
-                                        const int*, double*, hipStream_t, const KTimer&);
+                                        const int*, double*, hipStream_t, const KTimer&, int);
 template hipError_t launch_jets<float>(const Fields<float>&, const float*, float*, float*, const JetArgs&, const int*,
-                                       double*, hipStream_t, const KTimer&);
+                                       double*, hipStream_t, const KTimer&, int);
 
 }  // namespace cpic

@@ -46,12 +46,12 @@ __global__ __launch_bounds__(push_block_threads(TPP), (TPP == 8 && !LOGQ) ? 4 : 
 // one wavefront per group of 64 particles, fields from the force table
 template <typename T>
 __global__ __launch_bounds__(256) void push_table_kernel(Fields<T> Af, Fields<T> Bf, const T* table, Parts<T> P,
-                                                         PushArgs a, int* d_step, double* partials, int* err)
+                                                         PushArgs a, int* d_step, int off, double* partials, int* err)
 {
     const int nblocks = (a.np + 255) / 256;
     const int blk = xcd_block(nblocks);
     if (blk >= nblocks) return;
-    const int n = push_step(d_step, blk);
+    const int n = push_step(d_step, blk, off);
     push_body<T, 1, false, true>(Af, Bf, nullptr, P, a, n, partials, err, blk, nullptr, table);
 }
 
@@ -62,12 +62,13 @@ __global__ __launch_bounds__(256) void push_table_kernel(Fields<T> Af, Fields<T>
 // paths, which read the table at their cells.
 template <typename T>
 __global__ __launch_bounds__(256) void force_table_kernel(Fields<T> Af, Fields<T> Bf, const T* gpl, T* table, int N,
-                                                          Schedule sc, bool electric_only, const int* d_step)
+                                                          Schedule sc, bool electric_only, const int* d_step,
+                                                          int off)
 {
     const int V = N * N, nb = (V + 255) / 256;
     const int blk = xcd_block(nb);
     if (blk >= nb) return;
-    const int n = d_step[1];
+    const int n = d_step[1] + off;
     if (n < sc.n_form || n >= sc.n_max) return;
     const int s = blk * 256 + (int)threadIdx.x;
     if (s >= V) return;
@@ -127,37 +128,37 @@ int push_blocks(int np, int tpp) { return push_blocks_d(np, tpp); }
 template <typename T>
 hipError_t launch_force_table(const Fields<T>& A, const Fields<T>& B, const T* gpl, T* table, int N,
                               const Schedule& sc, bool electric_only, const int* d_step, hipStream_t st,
-                              const KTimer& tm)
+                              const KTimer& tm, int off)
 {
     if (!table || !gpl || N <= 0) return hipErrorInvalidValue;
     const int nbt = (N * N + 255) / 256;
     klaunch(tm, force_table_kernel<T>, dim3(8 * ((nbt + 7) / 8)), dim3(256), st, A, B, gpl, table, N, sc,
-            electric_only, d_step);
+            electric_only, d_step, off);
     return hipGetLastError();
 }
 template hipError_t launch_force_table<double>(const Fields<double>&, const Fields<double>&, const double*, double*,
-                                               int, const Schedule&, bool, const int*, hipStream_t, const KTimer&);
+                                               int, const Schedule&, bool, const int*, hipStream_t, const KTimer&, int);
 template hipError_t launch_force_table<float>(const Fields<float>&, const Fields<float>&, const float*, float*, int,
-                                              const Schedule&, bool, const int*, hipStream_t, const KTimer&);
+                                              const Schedule&, bool, const int*, hipStream_t, const KTimer&, int);
 
 template <typename T>
 hipError_t launch_push_table(const Fields<T>& A, const Fields<T>& B, const T* table, const Parts<T>& P,
                              const PushArgs& a, int* d_step, double* partials, int* err, hipStream_t st,
-                             const KTimer& tm)
+                             const KTimer& tm, int off)
 {
     if (a.np <= 0) return hipSuccess;
     if (!table) return hipErrorInvalidValue;
     const int nb = (a.np + 255) / 256;
-    klaunch(tm, push_table_kernel<T>, dim3(8 * ((nb + 7) / 8)), dim3(256), st, A, B, table, P, a, d_step, partials,
-            err);
+    klaunch(tm, push_table_kernel<T>, dim3(8 * ((nb + 7) / 8)), dim3(256), st, A, B, table, P, a, d_step, off,
+            partials, err);
     return hipGetLastError();
 }
 template hipError_t launch_push_table<double>(const Fields<double>&, const Fields<double>&, const double*,
                                               const Parts<double>&, const PushArgs&, int*, double*, int*, hipStream_t,
-                                              const KTimer&);
+                                              const KTimer&, int);
 template hipError_t launch_push_table<float>(const Fields<float>&, const Fields<float>&, const float*,
                                              const Parts<float>&, const PushArgs&, int*, double*, int*, hipStream_t,
-                                             const KTimer&);
+                                             const KTimer&, int);
 
 template <typename T, bool LOGQ>
 static void launch_push_t(const Fields<T>& A, const Fields<T>& B, const T* gpl, const Parts<T>& P, const PushArgs& a,

@@ -31,6 +31,10 @@
 // particles per site 401 -> 384); FP32 768^2 141 -> 140 (134 -> 127), 1024^2 270 -> 262
 // (235 -> 220), at 0.4 particles per site.  SU(2) has its own kernel (su2.hip) under
 // the same rule.
+// With the table push (and the light-like paths) the force table of step n runs before
+// the launch, on lattices where all that a step touches fits the cache (capi.hip):
+// 96^2 at 1.5 particles per site 33.3 -> 26.6 us (FP32 27.9 -> 21.7), 216^2 45.0 -> 41.6
+// (35.2 -> 29.9), 324^2 77.3 -> 72.9 (49.3 -> 43.8).
 // The arithmetic is that of the separate kernels, bit for bit (fieldbody.h,
 // pushbody.h).
 #include <type_traits>
@@ -44,22 +48,26 @@ namespace cpic {
 // against 201): 384^2 at 0.35 particles per site 61.1 -> 57.2 us, 324^2 45.0 -> 43.4,
 // below 216^2 equal; with the rotation 12 are spilled and it lost up to 7 % (162^2
 // 16.6 -> 17.8, 384^2 57.3 -> 60.0).
-template <typename T, bool ROLES, int CP, bool LOGQ>
-__global__ __launch_bounds__(256, LOGQ && ROLES ? 3 : 2) void step_kernel(Fields<T> S0, Fields<T> S1, Fields<T> S2, const T* g0, T* g1,
-                                                      Parts<T> P, PushArgs a, int off, int* d_step, double* partials,
-                                                      int* err)
+// PUSH: 0 the gather push, 1 with the logarithm update, 2 the table push
+template <typename T, bool ROLES, int CP, int PUSH>
+__global__ __launch_bounds__(256, PUSH == 1 && ROLES ? 3 : 2) void step_kernel(Fields<T> S0, Fields<T> S1, Fields<T> S2, const T* g0, T* g1,
+                                                      Parts<T> P, PushArgs a, const T* table, int off,
+                                                      int* d_step, double* partials, int* err)
 {
     constexpr int BX = ROLES ? 16 : 64, BY = 4;
-    constexpr size_t field_lds = ROLES ? kRolesLds<T, 16, 4> : kCtileLds<T, 64, 4>, push_lds = sizeof(T) * 64 * kPushRows<4, LOGQ>;
+    constexpr int TPP = PUSH == 2 ? 1 : 4, PPB = kPushPPB<TPP>;
+    constexpr size_t field_lds = ROLES ? kRolesLds<T, 16, 4> : kCtileLds<T, 64, 4>;
+    constexpr size_t push_lds = sizeof(T) * 64 * kPushRows<TPP, PUSH == 1>;
     __shared__ __align__(16) char smem[field_lds > push_lds ? field_lds : push_lds];
-    const int N = a.N, tiles = ((N + BX - 1) / BX) * ((N + BY - 1) / BY), blocks = (a.np + 63) / 64;
+    const int N = a.N, tiles = ((N + BX - 1) / BX) * ((N + BY - 1) / BY), blocks = (a.np + PPB - 1) / PPB;
     // entry i of XCD x: its push blocks, then its tiles
     const int pt = (tiles + 7) / 8, pb = (blocks + 7) / 8, x = (int)blockIdx.x & 7, i = (int)blockIdx.x >> 3;
     if (i < pb) {
         const int blk = x * pb + i;
         if (blk >= blocks) return;
         const int n = __builtin_amdgcn_readfirstlane(d_step[1] + off);
-        push_body<T, 4, LOGQ>(S0, S1, g0, P, a, n, partials, err, blk, reinterpret_cast<T(*)[64]>(smem));
+        push_body<T, TPP, PUSH == 1, PUSH == 2>(S0, S1, g0, P, a, n, partials, err, blk,
+                                                reinterpret_cast<T(*)[64]>(smem), table);
     } else {
         const int tile = x * pt + (i - pb);
         if (tile >= tiles) return;
@@ -69,27 +77,25 @@ __global__ __launch_bounds__(256, LOGQ && ROLES ? 3 : 2) void step_kernel(Fields
     }
 }
 
-template <typename T, bool ROLES, int CP>
-static void launch_step_t(const Fields<T>& S0, const Fields<T>& S1, const Fields<T>& S2, const T* g0, T* g1,
-                          const Parts<T>& P, const PushArgs& a, int off, int* d_step, double* partials, int* err,
-                          hipStream_t st)
-{
-    const int N = a.N, bx = ROLES ? 16 : 64, tiles = ((N + bx - 1) / bx) * ((N + 3) / 4), blocks = (a.np + 63) / 64;
-    const dim3 g(8 * ((tiles + 7) / 8 + (blocks + 7) / 8)), b(256);
-    if (a.color_log)
-        hipLaunchKernelGGL((step_kernel<T, ROLES, CP, true>), g, b, 0, st, S0, S1, S2, g0, g1, P, a, off, d_step, partials, err);
-    else
-        hipLaunchKernelGGL((step_kernel<T, ROLES, CP, false>), g, b, 0, st, S0, S1, S2, g0, g1, P, a, off, d_step, partials, err);
-}
-
 template <typename T>
 hipError_t launch_step(const Fields<T>& S0, const Fields<T>& S1, const Fields<T>& S2, const T* g0, T* g1,
-                       const LaunchCfg& cfg, const Parts<T>& P, const PushArgs& a, int off, int* d_step,
+                       const LaunchCfg& cfg, const Parts<T>& P, const PushArgs& a, const T* table, int off, int* d_step,
                        double* partials, int* err, hipStream_t st)
 {
-    if (a.np <= 0 || a.tpp != 4 || !g0 || !g1 || !S2.U || cfg.split != 3) return hipErrorInvalidValue;
+    if (a.np <= 0 || (!table && a.tpp != 4) || (table && a.color_log) || !g0 || !g1 || !S2.U || cfg.split != 3)
+        return hipErrorInvalidValue;
     auto go = [&](auto roles, auto cp) {
-        launch_step_t<T, decltype(roles)::value, decltype(cp)::value>(S0, S1, S2, g0, g1, P, a, off, d_step, partials, err, st);
+        constexpr bool R = decltype(roles)::value;
+        constexpr int CP = decltype(cp)::value;
+        const int N = a.N, bx = R ? 16 : 64, ppb = table ? kPushPPB<1> : kPushPPB<4>;
+        const int tiles = ((N + bx - 1) / bx) * ((N + 3) / 4), blocks = (a.np + ppb - 1) / ppb;
+        const dim3 g(8 * ((tiles + 7) / 8 + (blocks + 7) / 8)), b(256);
+        if (table)
+            hipLaunchKernelGGL((step_kernel<T, R, CP, 2>), g, b, 0, st, S0, S1, S2, g0, g1, P, a, table, off, d_step, partials, err);
+        else if (a.color_log)
+            hipLaunchKernelGGL((step_kernel<T, R, CP, 1>), g, b, 0, st, S0, S1, S2, g0, g1, P, a, table, off, d_step, partials, err);
+        else
+            hipLaunchKernelGGL((step_kernel<T, R, CP, 0>), g, b, 0, st, S0, S1, S2, g0, g1, P, a, table, off, d_step, partials, err);
     };
     using NT = std::integral_constant<int, kStoreNT>;
     using Plain = std::integral_constant<int, 0>;
@@ -102,9 +108,9 @@ hipError_t launch_step(const Fields<T>& S0, const Fields<T>& S1, const Fields<T>
 }
 template hipError_t launch_step<double>(const Fields<double>&, const Fields<double>&, const Fields<double>&,
                                         const double*, double*, const LaunchCfg&, const Parts<double>&, const PushArgs&,
-                                        int, int*, double*, int*, hipStream_t);
+                                        const double*, int, int*, double*, int*, hipStream_t);
 template hipError_t launch_step<float>(const Fields<float>&, const Fields<float>&, const Fields<float>&, const float*,
-                                       float*, const LaunchCfg&, const Parts<float>&, const PushArgs&, int, int*,
-                                       double*, int*, hipStream_t);
+                                       float*, const LaunchCfg&, const Parts<float>&, const PushArgs&, const float*,
+                                       int, int*, double*, int*, hipStream_t);
 
 }  // namespace cpic

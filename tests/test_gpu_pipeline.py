@@ -51,7 +51,7 @@ def run(ctx, N, steps, graph):
 
 
 @pytest.mark.parametrize("prec", [cp.FP64, cp.FP32])
-@pytest.mark.parametrize("N,n", [(4, 1), (6, 64), (18, 65), (27, 513), (48, 4000), (81, 700), (432, 3001), (768, 2000)])
+@pytest.mark.parametrize("N,n", [(4, 1), (6, 64), (12, 700), (18, 65), (27, 513), (48, 4000), (81, 700), (432, 3001), (768, 2000)])
 def test_same_bits_as_single_steps(N, n, prec):
     log = n % 2
     for form in (0.0, 4.5 * 6.0 / 64 / 8):
@@ -80,6 +80,37 @@ def test_same_bits_for_two_colours(N, n, prec):
             ctx.close()
         for a, b in zip(*got):
             assert np.array_equal(a, b, equal_nan=True)
+
+
+@pytest.mark.parametrize("prec", [cp.FP64, cp.FP32])
+@pytest.mark.parametrize("N,n", [(16, 200), (18, 1000), (432, 190001)])
+def test_same_bits_with_paths(N, n, prec):
+    """The light-like paths beside the gather push and beside the table push."""
+    got = []
+    for graph in (False, True):
+        ctx = make(N, prec, n, 0.0, 0)
+        ctx.enable_jets(x_offset=0.3)
+        run(ctx, N, (16, 18), graph)
+        ctx.load_state(inputs.random_state(N, 4), 0, inputs.random_particles(n, N, 5))
+        got.append(run(ctx, N, (1, 2, 16, 7, 16, 13), graph))
+        got[-1] += [ctx.observables(), ctx.jet_observables(), ctx.get_state(cp.STATE_JET_W), ctx.get_state(cp.STATE_JET_F)]
+        ctx.close()
+    for a, b in zip(*got):
+        assert np.array_equal(a, b, equal_nan=True)
+
+
+@pytest.mark.parametrize("N,n,jets,mode", [(16, 384, False, cp.PUSH_GATHER), (16, 385, False, cp.PUSH_TABLE),
+                                           (162, 16383, True, cp.PUSH_GATHER), (162, 16384, True, cp.PUSH_TABLE)])
+def test_default_push(N, n, jets, mode):
+    """Both lines of the rule, and that a choice of the caller stays."""
+    for chosen in (None, cp.PUSH_GATHER, cp.PUSH_TABLE):
+        ctx = cp.Context(dict(N=N, L_fm=6.0, n_sheets=1, tau_max_fm=0.1), dict(n=n, mass_GeV=1.27))
+        if chosen is not None:
+            ctx.set_push_mode(chosen)
+        if jets:
+            ctx.enable_jets()
+        assert ctx.push_mode() == (mode if chosen is None else chosen)
+        ctx.close()
 
 
 @pytest.mark.parametrize("steps", [1, 2, 3, 4])
