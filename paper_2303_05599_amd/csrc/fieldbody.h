@@ -147,12 +147,12 @@ __device__ __forceinline__ void field_ctile_body(const Fields<T>& in, const Fiel
 // Bound: the latency of one chain (stage, one part of the forces, exchange,
 // one exponential) on the smallest lattices, memory from about 250^2 on.
 // Measured per launch against the thread-per-site tiles (64 x 8 / the best of
-// 64 x 4, 32 x 8 and 32 x 4), FP64: 32^2 6.1 us (19.6 / 11.5), 96^2 7.8 (20.7 /
-// 12.9), 216^2 15.2 (22.5 / 16.5), 384^2 35.3 (46.9 / 37.0), 512^2 69.2 (60.9 /
-// 59.4); FP32: 32^2 5.9 us (12.8 / 10.3), 216^2 10.0 (15.4 / 13.2), 384^2 21.6
-// (26.0 / 23.1), 512^2 33.8 (29.5).  Tiles of 16 x 4 sites: 32 x 2 is equal, 8 x 8
-// up to 10 % slower (half lines), 32 x 4 slower below 300^2 (two wavefronts of a
-// tile on each SIMD).
+// 64 x 4, 32 x 8 and 32 x 4), FP64: 32^2 6.4 us (18.3 / 11.2), 96^2 7.2 (19.1 / 11.9),
+// 216^2 13.0 (21.4 / 15.8), 384^2 32.9 (44.1 / 33.3); FP32: 32^2 5.3 us (12.4 / 10.0),
+// 96^2 6.0 (13.2 / 10.1), 216^2 10.6 (15.3 / 12.5), 384^2 20.9 (25.1 / 22.2).  Before the
+// shorter exponential of su3.h, 512^2: FP64 69.2 us (60.9 / 59.4), FP32 33.8 (29.5).
+// Tiles of 16 x 4 sites: 32 x 2 is equal, 8 x 8 up to 10 % slower (half lines), 32 x 4
+// slower below 300^2 (two wavefronts of a tile on each SIMD).
 template <typename T, int HS> struct LdsLinks3 {
     const cx<T>* l;  // [18][HS]: the nine entries of U_x, then of U_y
     __device__ __forceinline__ m3<T> U(uint32_t h, int i) const

@@ -16,25 +16,26 @@
 // Spread evenly among each other instead they were slower wherever the chip is
 // full (both codes in one CU's instruction cache): 216^2 32.1 against 24.0 us
 // a step, 324^2 60.6 against 46.0; tiles first 26.5 and 49.2 (FP64, 0.35
-// particles per site).  Per step, two launches -> one, at that density:
-//   FP64: 32^2 17.2 -> 11.7 us, 96^2 19.7 -> 13.6, 216^2 28.9 -> 24.0,
-//         324^2 53.5 -> 46.0, 384^2 67.3 -> 59.7; 432^2 76.0 -> 76.6,
-//         512^2 108.7 -> 112.9
-//   FP32: 32^2 15.3 -> 10.5, 216^2 21.6 -> 15.5, 384^2 44.4 -> 36.0,
-//         432^2 48.6 -> 45.0, 512^2 61.1 -> 55.6; 648^2 96.9 -> 106.4
-//   with the colour log (FP64): 96^2 29.8 -> 23.8, 324^2 66.9 -> 55.5
+// particles per site, before the shorter exponential of su3.h).
+// Per step, two launches -> one, at 0.4 particles per site:
+//   FP64: 32^2 15.6 -> 10.4 us, 96^2 18.1 -> 12.8, 216^2 30.2 -> 25.0, 324^2 51.9 ->
+//         45.4, 384^2 63.9 -> 62.6
+//   FP32: 32^2 14.4 -> 9.5, 96^2 15.8 -> 11.0, 216^2 23.3 -> 17.1, 324^2 35.7 -> 28.3,
+//         384^2 42.5 -> 35.1, 432^2 49.7 -> 43.7, 512^2 60.6 -> 54.1
+//   with the colour log: FP64 96^2 19.2 -> 13.5, 324^2 53.8 -> 45.7; FP32 512^2 62.1
+//         -> 55.1
 // Between two lines (pipeline_pays) the steps stay separate: where two buffer sets
 // fit into the 256 MB Infinity Cache and three do not, the third one costs more
-// memory traffic than the overlap saves (512^2 FP64, 648^2 FP32 above).  Where two do
-// not fit either, the push and the field update wait for memory in turns and share
-// the state of step n + 1: FP64 768^2 287 -> 275 us, 1024^2 468 -> 457 (with 0.1
-// particles per site 401 -> 384); FP32 768^2 141 -> 140 (134 -> 127), 1024^2 270 -> 262
-// (235 -> 220), at 0.4 particles per site.  SU(2) has its own kernel (su2.hip) under
-// the same rule.
+// memory traffic than the overlap saves (FP64 432^2, 251 MB in three sets: 76.0 ->
+// 76.6, 512^2 108.7 -> 112.9; FP32 648^2 96.9 -> 106.4).  Where two do not fit either,
+// the push and the field update wait for memory in turns and share the state of
+// step n + 1: FP64 648^2 201 -> 191, 768^2 284 -> 275, 1024^2 466 -> 458 (with 0.1
+// particles per site 401 -> 382); FP32 768^2 137 -> 140 (134 -> 127), 1024^2 269 -> 260
+// (235 -> 219).  SU(2) has its own kernel (su2.hip) under the same rule.
 // With the table push (and the light-like paths) the force table of step n runs before
-// the launch, on lattices where all that a step touches fits the cache (capi.hip):
-// 96^2 at 1.5 particles per site 33.3 -> 26.6 us (FP32 27.9 -> 21.7), 216^2 45.0 -> 41.6
-// (35.2 -> 29.9), 324^2 77.3 -> 72.9 (49.3 -> 43.8).
+// the launch, on lattices where all that a step touches fits the cache (capi.hip): at
+// 1.6 particles per site FP64 96^2 33.3 -> 26.9, 216^2 46.0 -> 42.1, 324^2 80.8 -> 76.1;
+// FP32 96^2 27.5 -> 21.7, 216^2 35.1 -> 30.0, 324^2 49.4 -> 44.9.
 // The arithmetic is that of the separate kernels, bit for bit (fieldbody.h,
 // pushbody.h).
 #include <type_traits>

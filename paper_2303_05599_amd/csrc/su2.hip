@@ -390,10 +390,10 @@ hipError_t launch_su2_push(const Fields2<T>& A, const Fields2<T>& B, const Parts
 // The push of step n and the field update of step n + 1 in one launch (step.hip
 // has the reasons and the protocol): each XCD's push blocks, then its sites.
 // A site holds 20 reals, so both kernels are short and the second launch and the
-// idle ends of each weigh more than in SU(3).  Per step with 0.35 particles per
-// site, two launches -> one, FP64: 32^2 12.9 -> 8.4 us, 216^2 15.5 -> 12.3, 432^2
-// 32.4 -> 29.2, 648^2 60.3 -> 55.7; FP32: 32^2 10.9 -> 7.1, 216^2 12.7 -> 8.8,
-// 432^2 21.6 -> 18.1, 648^2 39.3 -> 33.2; 1024^2 in FP64 191.9 -> 182.4.
+// idle ends of each weigh more than in SU(3).  Per step with 0.4 particles per
+// site, two launches -> one, FP64: 32^2 12.5 -> 8.0 us, 216^2 16.3 -> 11.9, 432^2
+// 33.3 -> 30.1, 648^2 60.7 -> 56.3, 1024^2 191 -> 181; FP32: 32^2 10.7 -> 6.6, 216^2
+// 13.2 -> 9.2, 432^2 22.7 -> 18.6, 648^2 40.8 -> 33.8.
 template <typename T>
 __global__ __launch_bounds__(256) void su2_step_kernel(Fields2<T> S0, Fields2<T> S1, Fields2<T> S2, Parts<T> P,
                                                        PushArgs a, int off, const int* d_step, double* partials, int* err)
