@@ -155,7 +155,11 @@ cpic_status cpic_step(cpic_ctx* ctx, int32_t n_steps);
  * runs from a HIP graph: graphs of up to 16 steps, each ending at the next
  * particle reordering point or at the target, captured once per length and
  * buffer parity and replayed; a graph that starts at a reordering point of
- * moving particles starts with the reordering.  A no-op if already there. */
+ * moving particles starts with the reordering.  With the default launch, the
+ * push of a step and the field update of the next share a launch inside a
+ * graph on lattices where that pays (the same bits); it takes a third field
+ * buffer set, allocated once 32 evolved steps (64 above 32 MB) pay for it.  A
+ * no-op if already there. */
 cpic_status cpic_evolve(cpic_ctx* ctx, double tau_target_fm);
 
 /* Wait for the context's stream; reports CPIC_E_CELL_JUMP if any particle
@@ -346,6 +350,8 @@ cpic_status cpic_load(cpic_ctx* ctx, const char* path);
  *      SU(3) particles with the rotation colour update and no light-like
  *      paths).  The particle records are reordered by these tiles before the
  *      next push step.
+ * A new context uses variant 3, up to 384^2 with four wavefronts sharing 64
+ * sites; a launch set here runs as given, in steps of separate launches.
  * Used by the tuner; takes effect for the next launch. */
 cpic_status cpic_set_launch(cpic_ctx* ctx, int32_t bx, int32_t by, int32_t xcd_remap, int32_t waves,
                             int32_t variant);

@@ -671,12 +671,20 @@ static bool pipelined(cpic_ctx* c, int k, int64_t steps)
     const size_t fbytes = (size_t)c->rps * c->V * c->tsz;
     const size_t bytes = fbytes + (c->nc == 3 ? (size_t)kPlaqReals * c->V * c->tsz : 0);
     if (steps < pipeline_steps(bytes)) return false;
+    // a caller that captures this stream replays the graphs there are
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(c->st, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) return false;
     // graphs of separate steps from earlier calls are captured again
     if (c->evolved > 0) {
         if (hipStreamSynchronize(c->st) != hipSuccess) return false;
         drop_graphs(c);
     }
-    if (hipMalloc(&c->fbuf[2], bytes) == hipSuccess) {
+    // (relaxed: a capture on another stream of the process is left alone)
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+    const hipError_t e = hipMalloc(&c->fbuf[2], bytes);
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+    if (e == hipSuccess) {
         c->gpl2 = static_cast<char*>(c->fbuf[2]) + fbytes;
         return true;
     }

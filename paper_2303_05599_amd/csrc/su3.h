@@ -361,8 +361,7 @@ template <typename T> CPIC_HD m3<T> expi(const a8<T>& x, T eps)
     for (int a = 0; a < 8; a++) y.v[a] = eps * x.v[a];
     T c1 = T(0.25) * dot(y, y);
     int s = 0;
-    constexpr T top = sizeof(T) == 8 ? T(1e300) : T(1e38);
-    while (c1 > T(3) && c1 < top) {  // eigenvalues bounded by sqrt(4 c1 / 3) <= 2
+    while (c1 > T(3) && c1 < T(__builtin_inf())) {  // eigenvalues bounded by sqrt(4 c1 / 3) <= 2
 #pragma unroll
         for (int a = 0; a < 8; a++) y.v[a] *= T(0.5);
         c1 *= T(0.25);
