@@ -207,7 +207,7 @@ def batch_events(precision, n_events=64, seed=5):
 
 def run_batch(fp64_launch):
     """FP32 events batched (one launch per kernel and step over the events of a launch group,
-    graph-replayed; the library's default two launch lanes run groups side by side) against
+    graph-replayed; the library's default launch lanes run groups side by side) against
     FP64 and FP32 events run one at a time; initial conditions untimed."""
     import torch
     import paper_2303_05599_amd as cp

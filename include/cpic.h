@@ -538,10 +538,13 @@ cpic_status cpic_batch_set_launch(cpic_batch* b, int32_t bx, int32_t by, int32_t
  * `bytes` (a larger event forms a group of its own).  A group runs all its
  * steps before the next group of its lane starts, so its fields stay in the
  * last-level cache from one step to the next.  0 = all events in one group,
- * stepped together.  Default 96 MiB (with the default two lanes, the groups
- * running side by side share the 256 MB last-level cache). */
+ * stepped together.  Default 96 MiB with two lanes (the groups running side by
+ * side share the 256 MB last-level cache); in single precision, unless the budget
+ * or the lanes are set, three lanes of 96 MiB, or of 64 MiB beside larger events,
+ * where those do not do a third of the work. */
 cpic_status cpic_batch_set_group_bytes(cpic_batch* b, int64_t bytes);
-/* Launch lanes (1 to 4; default 2): the launch groups are dealt to the
+/* Launch lanes (1 to 4; default 2, in single precision 3 by the rule above):
+ * the launch groups are dealt to the
  * batch stream and up to three streams of the library's own (default
  * priority), by their remaining work (largest first, each to the lane with
  * the least; odd lanes then run theirs smallest first), and the streams run

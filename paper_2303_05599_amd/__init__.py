@@ -412,7 +412,7 @@ class Batch:
         self._chk(lib().cpic_batch_set_launch(self.h, bx, by, xcd_remap, push_lanes))
 
     def set_lanes(self, lanes):
-        """Launch lanes, 1 to 4: the launch groups dealt to that many concurrent streams (default 2)."""
+        """Launch lanes, 1 to 4: the launch groups dealt to that many concurrent streams (default 2; 3 in FP32)."""
         self._chk(lib().cpic_batch_set_lanes(self.h, lanes))
 
     def set_group_bytes(self, nbytes):

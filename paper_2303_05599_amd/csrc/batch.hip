@@ -3,7 +3,7 @@
 // Every event keeps its own context (buffers, step counter, samples); the
 // batch adds a device table of event descriptors.  Events are split into
 // launch groups whose working set fits the last-level cache; the groups are
-// dealt to one or two launch lanes (streams), and each lane runs its groups
+// dealt to up to four launch lanes (streams), and each lane runs its groups
 // one after the other, each to the end of its events.  For every set of
 // still active events of a group there is a plan: the active list and the
 // work maps (event, tile) and (event, particle block), one entry per
@@ -33,9 +33,9 @@ constexpr int kBatchGraphSteps = 16;
 // particle records) stays within about this much, so that from one step to
 // the next (and from a group's field update to its push) the data of the
 // groups the lanes run side by side is served from the 256 MB last-level
-// cache (96 MiB measured best of 64, 96 and 128 with two lanes).
-constexpr size_t kDefaultGroupBytes = (size_t)96 << 20;
-constexpr int kMaxLanes = 4, kDefaultLanes = 2;
+// cache (two lanes of 96 MiB; sharing() has the single-precision rule).
+constexpr size_t kDefaultGroupBytes = (size_t)96 << 20, kMixedGroupBytes = (size_t)64 << 20;
+constexpr int kMaxLanes = 4, kDefaultLanes = 2, kSingleLanes = 3;
 
 struct Plan {
     std::vector<int> act;          // active events (descriptor indices)
@@ -60,11 +60,11 @@ struct cpic_batch {
     // shortens each wave's chain of dependent loads (measured fastest from
     // 5e4 to 3.5e6 particles per launch)
     int tpp = 4;
-    size_t group_bytes = kDefaultGroupBytes;  // working-set budget of a launch group; 0: one group
+    int64_t group_bytes = -1;  // working-set budget of a launch group; 0: one group; -1: not set
     // Launch lanes: the groups are dealt to `lanes` streams that run
     // concurrently, so that groups of small events (whose launches leave most
     // of the chip idle) run beside groups of large ones.
-    int lanes = kDefaultLanes;
+    int lanes = 0;             // 0: not set
     hipStream_t lane_st[kMaxLanes] = {};      // lane 0 is the batch stream; the others the library's own
     hipEvent_t ev_fork = nullptr, ev_join[kMaxLanes] = {};
     EventDesc* d_desc = nullptr;
@@ -143,9 +143,9 @@ static size_t working_set(const cpic_ctx* c)
 }
 
 // Launch groups: events by decreasing working set, packed greedily up to
-// group_bytes (an event larger than the budget forms a group of its own);
-// group_bytes = 0 puts every event in one group.
-static std::vector<std::vector<int>> launch_groups(const cpic_batch* b)
+// the budget (an event larger than that forms a group of its own); a budget of 0
+// puts every event in one group.
+static std::vector<std::vector<int>> launch_groups(const cpic_batch* b, size_t budget)
 {
     std::vector<int> order(b->ev.size());
     for (size_t e = 0; e < order.size(); e++) order[e] = (int)e;
@@ -155,7 +155,7 @@ static std::vector<std::vector<int>> launch_groups(const cpic_batch* b)
     size_t acc = 0;
     for (int e : order) {
         const size_t w = working_set(b->ev[e]);
-        if (groups.empty() || (b->group_bytes && acc + w > b->group_bytes)) {
+        if (groups.empty() || (budget && acc + w > budget)) {
             groups.emplace_back();
             acc = 0;
         }
@@ -304,6 +304,33 @@ extern "C" cpic_status cpic_batch_init_mv(cpic_batch* b)
 // costs about as much as two).
 static double step_cost(const cpic_ctx* c) { return (double)c->V + 2.0 * (double)c->np; }
 
+// Lanes and group budget of a run, where the caller has set neither.  FP32 kernels
+// wait for latency more than for memory, so a third lane pays unless events that
+// exceed the budget by themselves do a third of the work (their groups would not
+// share the last-level cache).  A step of uneven or equal events, FP32, 2 x 96 / 3 x 64 / 3 x
+// 96 MiB: 24 of 128^2 122 / 123 / 107 us, 12 of 256^2 180 / 182 / 161, 9 of 384^2 297 /
+// 257 / 253; 8 uneven ones with one of 512^2 198 / 175 / 179, 24 with three 557 / 546 /
+// 580 (a fourth of the work); 64 with 54 % of the work on 512^2 46.3 / 42.0 events/s; 6
+// of 512^2 319 / 335 / 334 us.  FP64, 8 uneven ones: 377 / 387 / 390.
+struct Sharing {
+    int lanes;
+    size_t budget;
+};
+static Sharing sharing(const cpic_batch* b)
+{
+    const Sharing chosen = {b->lanes ? b->lanes : kDefaultLanes,
+                            b->group_bytes >= 0 ? (size_t)b->group_bytes : kDefaultGroupBytes};
+    if (b->prec != CPIC_FP32 || b->lanes || b->group_bytes >= 0) return chosen;
+    double all = 0, large = 0;
+    for (const cpic_ctx* c : b->ev) {
+        const double work = step_cost(c) * (double)std::max<int64_t>(c->sc.n_max - c->n, 0);
+        all += work;
+        if (working_set(c) > kDefaultGroupBytes) large += work;
+    }
+    if (3 * large > all) return chosen;
+    return {kSingleLanes, large > 0 ? kMixedGroupBytes : kDefaultGroupBytes};
+}
+
 // A launch lane: its stream and the launch groups it runs one after the other.
 struct Lane {
     hipStream_t st = nullptr;
@@ -378,8 +405,9 @@ static cpic_status run_steps(cpic_batch* b, int64_t max_steps)
             return bfail(b, CPIC_E_INVALID, "cpic_batch_run: event " + std::to_string(e) + " has no state");
     cpic_status s = upload_desc(b);
     if (s) return s;
-    const std::vector<std::vector<int>> groups = launch_groups(b);
-    const int nl = std::max(1, std::min<int>(b->lanes, (int)groups.size()));
+    const Sharing sh = sharing(b);
+    const std::vector<std::vector<int>> groups = launch_groups(b, sh.budget);
+    const int nl = std::max(1, std::min<int>(sh.lanes, (int)groups.size()));
     for (int l = 1; l < nl; l++) {
         if (!b->lane_st[l]) BHIP(b, hipStreamCreateWithFlags(&b->lane_st[l], hipStreamNonBlocking), "lane stream");
         if (!b->ev_join[l]) BHIP(b, hipEventCreateWithFlags(&b->ev_join[l], hipEventDisableTiming), "lane event");
@@ -469,7 +497,7 @@ extern "C" cpic_status cpic_batch_sync(cpic_batch* b)
 template <typename T> static cpic_status tune_batch(cpic_batch* b, int reps, std::string& rep)
 {
     std::vector<std::vector<int>> groups;
-    for (const auto& g : launch_groups(b)) {
+    for (const auto& g : launch_groups(b, sharing(b).budget)) {
         std::vector<int> act;
         for (int e : g)
             if (b->ev[e]->n < b->ev[e]->sc.n_max) act.push_back(e);
@@ -579,7 +607,7 @@ extern "C" cpic_status cpic_batch_set_group_bytes(cpic_batch* b, int64_t bytes)
 {
     if (!b) return bfail(nullptr, CPIC_E_INVALID, "cpic_batch_set_group_bytes: NULL");
     if (bytes < 0) return bfail(b, CPIC_E_INVALID, "cpic_batch_set_group_bytes: negative budget");
-    b->group_bytes = (size_t)bytes;
+    b->group_bytes = bytes;
     drop_plans(b);
     return CPIC_OK;
 }
