@@ -620,7 +620,7 @@ cpic_status cpic::host_advance(cpic_ctx* c, int k, bool pipelined)
             c->jsamples.push_back({record_slot_of(c->ja.sc, c->n), c->n});
         c->n++;
     }
-    if (pipelined) c->cur = stretch_buffer(c->cur, k);
+    if (pipelined) c->cur = stretch_buffer(c->cur, k, k);
     else for (int j = 0; j < k; j++) c->cur = next_buffer(c->cur);
     // the drift watchdog after every multiple of watch_every steps
     if (c->watch_every > 0 && c->n / c->watch_every > n0 / c->watch_every) return enqueue_watch(c, false);
@@ -696,7 +696,7 @@ static bool pipelined(cpic_ctx* c, int k, int64_t steps)
 template <typename T> static cpic_status launch_pipelined(cpic_ctx* c, int from, int k)
 {
     if (c->nc == 2) {
-        auto S = [&](int j) { return F2<T>(c, stretch_buffer(from, j)); };
+        auto S = [&](int j) { return F2<T>(c, stretch_buffer(from, j, k)); };
         const PushArgs a = push_args(c, 1);
         HIPCHK(c, launch_su2_field<T>(S(0), S(1), c->N, c->sc, c->d_step, c->st), "field step");
         for (int j = 0; j + 1 < k; j++)
@@ -707,7 +707,7 @@ template <typename T> static cpic_status launch_pipelined(cpic_ctx* c, int from,
         return CPIC_OK;
     }
     T* const G[2] = {static_cast<T*>(c->gpl), static_cast<T*>(c->gpl2)};
-    auto S = [&](int j) { return F<T>(c, stretch_buffer(from, j)); };
+    auto S = [&](int j) { return F<T>(c, stretch_buffer(from, j, k)); };
     const PushArgs a = push_args(c, c->push_table ? 1 : 4);
     T* const table = static_cast<T*>(c->ftab);
     HIPCHK(c, launch_field_step<T>(S(0), S(1), G[0], c->N, c->sc, c->d_step, c->cfg, c->st), "field step");

@@ -37,12 +37,12 @@ struct cpic_ctx {
     cpic::Schedule sc{};
     int n = 0;    // host mirror of the device step counter
     int64_t evolved = 0;  // steps cpic_evolve has launched
-    int cur = 0;  // buffer holding the state at step n (2 only after pipelined stretches)
+    int cur = 0;  // buffer holding the state at step n (0 or 1)
     int64_t np = 0;
     bool is_static = false;
     double mhat = 0;
     double q0[8]{}, q0eig[3]{}, q2ref = 0, q3ref = 0;
-    void* fbuf[3] = {nullptr, nullptr, nullptr};  // the third from the first pipelined stretch on
+    void* fbuf[3] = {nullptr, nullptr, nullptr};  // the third inside pipelined stretches, from the first on
     void* pr = nullptr;   // particle reals [19][np]
     void* gpl = nullptr;  // plaquette field G = Proj U_12 [8][V] for the push, force table and light-like paths
     void* gpl2 = nullptr; // a second plaquette field (pipelined stretches; behind fbuf[2])
@@ -84,7 +84,7 @@ struct cpic_ctx {
     // up to the next reordering point or the end of an evolve); sorted = 1:
     // the graph starts with the reordering of the records (moving particles
     // at a reordering point)
-    hipGraphExec_t gexec[2][3][cpic::kGraphSteps + 1] = {};
+    hipGraphExec_t gexec[2][2][cpic::kGraphSteps + 1] = {};
     // light-like paths (cpic_jets_enable)
     bool jets = false;
     cpic::JetArgs ja{};
@@ -124,11 +124,13 @@ cpic_status maybe_sort(cpic_ctx* c);
 // first reordering point after step n (1 << 30 if none)
 int next_sort_point(const cpic_ctx* c, int n);
 // the buffer a step from buffer b writes: 0 and 1 alternate
-inline int next_buffer(int b) { return b == 0 ? 1 : 0; }
-// the buffer that holds step j of a pipelined stretch that starts from buffer b
-// (downwards from 1, so that stretches of 16 alternate between two buffers, and
-// so between two graphs)
-inline int stretch_buffer(int b, int j) { return (b + (b == 1 ? 2 : 1) * j) % 3; }
+inline int next_buffer(int b) { return b ^ 1; }
+// the buffer that holds step j of a pipelined stretch of k steps that starts from
+// buffer b (0 or 1).  The three buffers take turns, upwards or downwards: in the
+// direction that ends the stretch in buffer 0 or 1, so that between calls the state
+// never rests in the third one (separate steps captured by the caller return to the
+// buffer they read after every even number, and stretches take two graphs a length).
+inline int stretch_buffer(int b, int j, int k) { return (b + ((b + k) % 3 == 2 ? 2 : 1) * j) % 3; }
 // host bookkeeping of k launched steps (sample list, step counter, buffer)
 cpic_status host_advance(cpic_ctx* c, int k, bool pipelined = false);
 PushArgs push_args(const cpic_ctx* c, int tpp);
