@@ -87,12 +87,21 @@ static bool valid_N(int N)
     return N == 1;
 }
 
+static void drop_graphs(cpic_ctx* c)
+{
+    for (auto& form : c->gexec)
+        for (auto& byp : form)
+            for (auto& byk : byp)
+                for (auto& g : byk)
+                    if (g) {
+                        (void)hipGraphExecDestroy(g);
+                        g = nullptr;
+                    }
+}
+
 static void free_all(cpic_ctx* c)
 {
-    for (auto& byp : c->gexec)
-        for (auto& byk : byp)
-            for (auto& g : byk)
-                if (g) (void)hipGraphExecDestroy(g);
+    drop_graphs(c);
     for (auto e : c->ev_field) (void)hipEventDestroy(e);
     for (auto e : c->ev_push) (void)hipEventDestroy(e);
     for (auto e : c->ev_jets) (void)hipEventDestroy(e);
@@ -417,17 +426,6 @@ static cpic_status order_installed(cpic_ctx* c)
     return CPIC_OK;
 }
 
-static void drop_graphs(cpic_ctx* c)
-{
-    for (auto& byp : c->gexec)
-        for (auto& byk : byp)
-            for (auto& g : byk)
-                if (g) {
-                    (void)hipGraphExecDestroy(g);
-                    g = nullptr;
-                }
-}
-
 static cpic_status reset_counters(cpic_ctx* c, int n)
 {
     c->n = n;
@@ -674,11 +672,6 @@ static bool pipelined(cpic_ctx* c, int k, int64_t steps)
     // a caller that captures this stream replays the graphs there are
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(c->st, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) return false;
-    // graphs of separate steps from earlier calls are captured again
-    if (c->evolved > 0) {
-        if (hipStreamSynchronize(c->st) != hipSuccess) return false;
-        drop_graphs(c);
-    }
     // (relaxed: a capture on another stream of the process is left alone)
     hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
     (void)hipThreadExchangeStreamCaptureMode(&mode);
@@ -753,7 +746,7 @@ static cpic_status build_graph(cpic_ctx* c, int from, int k, bool sorted, int tx
     hipError_t e = hipStreamEndCapture(c->st, &g);
     if (s) { if (g) (void)hipGraphDestroy(g); return s; }
     if (e != hipSuccess) return hip_fail(c, e, "end capture");
-    e = hipGraphInstantiate(&c->gexec[sorted ? 1 : 0][from][k], g, nullptr, nullptr, 0);
+    e = hipGraphInstantiate(&c->gexec[piped][sorted][from][k], g, nullptr, nullptr, 0);
     (void)hipGraphDestroy(g);
     if (e != hipSuccess) return hip_fail(c, e, "graph instantiate");
     return CPIC_OK;
@@ -794,13 +787,13 @@ extern "C" cpic_status cpic_evolve(cpic_ctx* c, double tau_target_fm)
         // one graph up to the next reordering point, at most kGraphSteps steps
         // (graphs of each length are captured once per buffer they start from)
         const int k = std::min(std::min(left, kGraphSteps), std::max(1, next_sort_point(c, c->n) - c->n));
-        const int from = c->cur, sg = in_graph ? 1 : 0;
+        const int from = c->cur;
         const bool piped = pipelined(c, k, c->evolved + left);
-        if (!c->gexec[sg][from][k]) {
+        if (!c->gexec[piped][in_graph][from][k]) {
             cpic_status s = build_graph(c, from, k, in_graph, tx, ty, piped);
             if (s) return s;
         }
-        HIPCHK(c, hipGraphLaunch(c->gexec[sg][from][k], c->st), "graph launch");
+        HIPCHK(c, hipGraphLaunch(c->gexec[piped][in_graph][from][k], c->st), "graph launch");
         if (in_graph) mark_sorted(c, tx, ty);
         host_advance(c, k, piped);
         c->evolved += k;

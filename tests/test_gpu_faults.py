@@ -1,0 +1,75 @@
+"""What the library does when a call of the HIP runtime fails under it, forced from the host
+by a shim in a process of its own (hip_shim.c): it reports the error, and what it does
+next is right."""
+import ctypes
+import os
+import subprocess
+import sys
+
+import numpy as np
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+MALLOC, HOST_MALLOC, GRAPH_LAUNCH, KERNEL, ELAPSED = range(5)
+ALL = 1 << 40
+N, BOX = 48, 4.5
+DT = BOX / N / 8
+
+
+def make(cp, load=False, **glasma):
+    g = dict(N=N, L_fm=BOX, n_sheets=1, tau_max_fm=400 * DT, seed=5)
+    g.update(glasma)
+    ctx = cp.Context(g, dict(n=500, mass_GeV=1.27, tau_form_fm=0.0, pT_max_GeV=3.0, seed=4), stream=None)
+    ctx.init_mv()
+    return ctx
+
+
+def evolve(ctx, steps):
+    ctx.evolve((ctx.n + steps) * DT * (1 - 1e-12))
+
+
+def state(ctx):
+    return [ctx.get_state(k) for k in range(5)]
+
+
+def check_same(ctx, ref):
+    for a, b in zip(state(ctx), state(ref)):
+        assert np.array_equal(a, b)
+
+
+def failed_graph_launch(cp, shim):
+    """A stretch whose launch failed leaves a graph of separate steps; the next call pipelines."""
+    ctx, ref = make(cp), make(cp)
+    shim.shim_fail(GRAPH_LAUNCH, 0, 1, 0)
+    with pytest.raises(cp.CpicError):
+        evolve(ctx, 20)
+    assert ctx.n == 0
+    evolve(ctx, 40)
+    ref.step(40)
+    check_same(ctx, ref)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("scenario", [failed_graph_launch], ids=lambda f: f.__name__)
+def test_forced_failure(scenario, tmp_path):
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    so = str(tmp_path / "hip_shim.so")
+    subprocess.run(["gcc", "-shared", "-fPIC", "-O1", "-o", so, os.path.join(HERE, "hip_shim.c"), "-ldl"], check=True)
+    r = subprocess.run([sys.executable, os.path.abspath(__file__), scenario.__name__, so], capture_output=True, text=True,
+                       timeout=100)
+    assert r.returncode == 0 and r.stdout.strip().endswith("done"), r.stdout[-2000:] + r.stderr[-3000:]
+
+
+if __name__ == "__main__":
+    shim_ = ctypes.CDLL(sys.argv[2], mode=ctypes.RTLD_GLOBAL)   # before anything loads the runtime
+    shim_.shim_fail.argtypes = [ctypes.c_int, ctypes.c_long, ctypes.c_long, ctypes.c_size_t]
+    shim_.shim_elapsed.argtypes = [ctypes.c_float, ctypes.c_long, ctypes.c_float]
+    shim_.shim_calls.argtypes, shim_.shim_calls.restype = [ctypes.c_int], ctypes.c_long
+    sys.path.insert(0, os.path.dirname(HERE))
+    import paper_2303_05599_amd as cp_
+    cp_.lib()
+    globals()[sys.argv[1]](cp_, shim_)
+    assert shim_.shim_calls(KERNEL) > 0, "the shim does not stand between the library and the runtime"
+    print("done")
