@@ -725,12 +725,43 @@ template <typename T> static cpic_status launch_pipelined(cpic_ctx* c, int from,
     return CPIC_OK;
 }
 
+// A stream to capture step graphs on: the context's own, or, while the caller captures
+// that one, a stream made for the purpose (a capture cannot be begun inside another;
+// relaxed, so that the caller's is left alone).
+struct CaptureStream {
+    hipStream_t st = nullptr;
+    bool own = false;
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    hipError_t open(hipStream_t of)
+    {
+        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+        hipError_t e = hipStreamIsCapturing(of, &cap);
+        st = of;
+        if (e != hipSuccess || cap == hipStreamCaptureStatusNone) return e;
+        e = hipThreadExchangeStreamCaptureMode(&mode);
+        if (e != hipSuccess) return e;
+        own = true;
+        st = nullptr;
+        return hipStreamCreateWithFlags(&st, hipStreamNonBlocking);
+    }
+    ~CaptureStream()
+    {
+        if (!own) return;
+        if (st) (void)hipStreamDestroy(st);
+        (void)hipThreadExchangeStreamCaptureMode(&mode);
+    }
+};
+
 // a graph of k steps from buffer `from`
 // sorted: the graph starts with the reordering of the records by tx x ty tiles
 static cpic_status build_graph(cpic_ctx* c, int from, int k, bool sorted, int tx, int ty, bool piped)
 {
     hipGraph_t g = nullptr;
-    HIPCHK(c, hipStreamBeginCapture(c->st, hipStreamCaptureModeThreadLocal), "capture");
+    CaptureStream on;
+    HIPCHK(c, on.open(c->st), "capture");
+    HIPCHK(c, hipStreamBeginCapture(on.st, hipStreamCaptureModeThreadLocal), "capture");
+    const hipStream_t st = c->st;
+    c->st = on.st;
     cpic_status s = CPIC_OK;
     if (sorted) {
         const hipError_t e = enqueue_sort(c, tx, ty);
@@ -743,7 +774,8 @@ static cpic_status build_graph(cpic_ctx* c, int from, int k, bool sorted, int tx
         for (int j = 0, b = from; j < k && s == CPIC_OK; j++, b = next_buffer(b))
             s = dbl ? launch_one<double>(c, b, false) : launch_one<float>(c, b, false);
     }
-    hipError_t e = hipStreamEndCapture(c->st, &g);
+    c->st = st;
+    hipError_t e = hipStreamEndCapture(on.st, &g);
     if (s) { if (g) (void)hipGraphDestroy(g); return s; }
     if (e != hipSuccess) return hip_fail(c, e, "end capture");
     e = hipGraphInstantiate(&c->gexec[piped][sorted][from][k], g, nullptr, nullptr, 0);

@@ -1,6 +1,7 @@
 """Steps that the caller captures on the context's stream: `cpic_step` of an even number
 of steps returns to the buffer it read, so its graph can be replayed, from wherever
-the evolution before it has left the state."""
+the evolution before it has left the state.  `cpic_evolve` replays graphs of its own there, which
+the runtime runs at once, whether it has met the stretch before or not."""
 import ctypes
 
 import numpy as np
@@ -56,5 +57,29 @@ def test_captured_steps_replay(before, nc):
         b.step(4)
         assert same(a, b)
     del g
+    a.close()
+    b.close()
+
+
+@pytest.mark.filterwarnings("ignore:The CUDA Graph is empty")
+@pytest.mark.parametrize("before", [(16,), (16, 16), (32, 16), (20, 12), (64,)])
+def test_evolve_on_a_captured_stream(before):
+    s = torch.cuda.Stream()
+    a, b = make(ctypes.c_void_p(s.cuda_stream)), make(None)
+    for k in before:
+        evolve(a, k)
+        b.step(k)
+    a.sync()
+    for k in (16, 7):
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=s):
+            evolve(a, k)
+        torch.cuda.synchronize()
+        b.step(k)
+        assert a.n == b.n and same(a, b)
+        del g
+    evolve(a, 25)
+    b.step(25)
+    assert same(a, b)
     a.close()
     b.close()
