@@ -417,8 +417,11 @@ cpic_status cpic_set_store_policy(cpic_ctx* ctx, int32_t non_temporal);
  * from a saved copy of the state (one extra field buffer set, allocated for
  * the duration), which is restored afterwards; the fastest step decides, but
  * the configuration before tuning stays unless another is at least 2 %
- * faster per step (timing noise does not flip between equals).  reps launches per candidate.  report
- * (may be NULL) receives a text table whose last line is the choice.
+ * faster per step (timing noise does not flip between equals).  Where the
+ * steps of cpic_evolve share launches (the default launch), a stretch of four
+ * such steps is timed as well, and the steps are separate from then on if it
+ * is the slower form.  reps launches per candidate.  report (may be NULL)
+ * receives a text table whose last line is the choice.
  * Synchronises. */
 cpic_status cpic_tune(cpic_ctx* ctx, int32_t reps, char* report, size_t cap);
 

@@ -1782,6 +1782,7 @@ template <typename T> static cpic_status tune_t(cpic_ctx* c, int reps, std::stri
             // pipelined stretches, if that is how the steps ran before
             // (kept on equality), against the best pair of separate steps
             const int pair_tpp = c->tpp;
+            bool piped_now = false;
             if (te == hipSuccess && orig.pipe && (c->push_table || tpp0 == 4) && c->n + 4 <= c->sc.n_max) {
                 double per = 1e300;
                 c->cfg = orig;
@@ -1792,16 +1793,25 @@ template <typename T> static cpic_status tune_t(cpic_ctx* c, int reps, std::stri
                     std::snprintf(line, sizeof line, "step pipelined, four in a stretch: %.2f us\n", per * 1e3);
                     rep += line;
                 }
-                if (per <= best_pair) { best_step = orig; best_pair = per; }
-                else { c->cfg = best_step; c->tpp = pair_tpp; }
+                if (per <= best_pair) {
+                    best_step = orig;
+                    best_pair = per;
+                    piped_now = true;
+                } else {
+                    // timed and slower: the steps stay separate, also with the launch from before
+                    if (per < 1e300) best_step.pipe = 0;
+                    c->cfg = best_step;
+                    c->tpp = pair_tpp;
+                }
                 c->pblocks = push_blocks((int)c->np, c->tpp);
             }
             release();
             if (te != hipSuccess) { c->cfg = keep; return hip_fail(c, te, "tune"); }
             std::snprintf(line, sizeof line,
-                          "chosen: field %s bx=%d by=%d waves=%d remap=%d nt=%d, push lanes=%d, step %.2f us\n",
+                          "chosen: field %s bx=%d by=%d waves=%d remap=%d nt=%d, push lanes=%d, %s step %.2f us\n",
                           variant_name(best_step), best_step.bx, best_step.by, best_step.waves,
-                          best_step.xcd_remap, best_step.nt_store, c->tpp, best_pair * 1e3);
+                          best_step.xcd_remap, best_step.nt_store, c->tpp, piped_now ? "pipelined" : "separate",
+                          best_pair * 1e3);
             rep += line;
         }
     }

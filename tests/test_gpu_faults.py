@@ -49,8 +49,39 @@ def failed_graph_launch(cp, shim):
     check_same(ctx, ref)
 
 
+def tuned(cp, shim, pair_ms, piped_ms):
+    """Tune with the pipelined trial (the last 1 + 2 timings) answered with piped_ms and all others with pair_ms:
+    the choice, and the kernels in the graph of a stretch of 16 steps."""
+    for turn in (ALL, None):
+        ctx, ref = make(cp), make(cp)
+        ctx.step(3)
+        turn = turn or timings - 3
+        before = shim.shim_calls(ELAPSED)
+        shim.shim_elapsed(pair_ms, turn, piped_ms)
+        report = ctx.tune(2)
+        timings = shim.shim_calls(ELAPSED) - before
+    assert "step pipelined, four in a stretch" in report
+    evolve(ctx, 13)                  # up to the reordering at step 16
+    k0 = shim.shim_calls(KERNEL)
+    evolve(ctx, 16)                  # one graph, captured now
+    kernels = shim.shim_calls(KERNEL) - k0
+    evolve(ctx, 40)
+    ref.step(3 + 13 + 16 + 40)
+    check_same(ctx, ref)
+    return report.strip().splitlines()[-1], kernels
+
+
+def tuner_keeps_the_faster_form(cp, shim):
+    # per step: pairs 1 ms / 2, four pipelined steps 1 ms / 4, or 10 ms / 4
+    piped_line, piped = tuned(cp, shim, 1.0, 1.0)
+    line, separate = tuned(cp, shim, 1.0, 10.0)
+    # 17 launches pipelined and 32 separate, besides the reordering's
+    assert 17 <= piped <= 17 + 8 < 32 <= separate, (piped, separate)
+    assert "pipelined step" in piped_line and "separate step" in line, piped_line + line
+
+
 @pytest.mark.gpu
-@pytest.mark.parametrize("scenario", [failed_graph_launch], ids=lambda f: f.__name__)
+@pytest.mark.parametrize("scenario", [failed_graph_launch, tuner_keeps_the_faster_form], ids=lambda f: f.__name__)
 def test_forced_failure(scenario, tmp_path):
     torch = pytest.importorskip("torch")
     if not torch.cuda.is_available():
