@@ -70,8 +70,7 @@ struct cpic_batch {
     EventDesc* d_desc = nullptr;
     std::vector<EventDesc> desc;  // host copy (kept alive for the asynchronous upload)
     std::map<std::vector<int>, Plan> plans;
-    ICWorkspace icw{};  // of the events' initial conditions, made one after the other
-    ExchangeBuffers xb{};  // of the events' state exchange, likewise
+    ExchangeBuffers xb{};  // of the events' state exchange, one at a time
     std::string err;
 };
 
@@ -278,7 +277,6 @@ extern "C" cpic_status cpic_batch_create(int32_t n_events, const cpic_glasma_par
         // the batch launches its own kernels over all events: the events'
         // records keep the gather push's order
         if (c->cfg.split == 4) c->cfg.split = 3;
-        c->icw = &b->icw;
         c->xb = &b->xb;
         b->ev.push_back(c);
     }
@@ -682,7 +680,6 @@ extern "C" void cpic_batch_destroy(cpic_batch* b)
     }
     if (b->ev_fork) (void)hipEventDestroy(b->ev_fork);
     for (auto c : b->ev) cpic_destroy(c);
-    b->icw.release();
     b->xb.release();
     if (b->own_stream) (void)hipStreamDestroy(b->st);
     delete b;

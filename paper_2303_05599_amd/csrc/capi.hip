@@ -119,7 +119,6 @@ static void free_all(cpic_ctx* c)
     (void)hipFree(c->sb.count); (void)hipFree(c->sb.offs);
     (void)hipFree(c->tile_start); (void)hipFree(c->strag); (void)hipFree(c->strag_count);
     (void)hipFree(c->d_strag_total);
-    c->icw_own.release();
     c->xb_own.release();
     if (c->own_stream && c->st) (void)hipStreamDestroy(c->st);
 }
@@ -236,10 +235,10 @@ extern "C" cpic_status cpic_create(const cpic_glasma_params* gp, const cpic_part
         c->q3ref = 0;
     }
 
-    hipError_t e = hipSuccess;
+    hipError_t e = hipGetDevice(&c->device);
     if (hip_stream) {
         c->st = (hipStream_t)hip_stream;
-    } else {
+    } else if (e == hipSuccess) {
         e = hipStreamCreateWithFlags(&c->st, hipStreamNonBlocking);
         c->own_stream = e == hipSuccess;
     }
@@ -315,6 +314,7 @@ extern "C" cpic_status cpic_create(const cpic_glasma_params* gp, const cpic_part
         delete c;
         return fail(nullptr, oom ? CPIC_E_NOMEM : CPIC_E_HIP, std::string("cpic_create: ") + hipGetErrorString(e));
     }
+    pool_enter();
     *out = c;
     return CPIC_OK;
 }
@@ -325,6 +325,7 @@ extern "C" void cpic_destroy(cpic_ctx* c)
     if (c->st) (void)hipStreamSynchronize(c->st);
     free_all(c);
     delete c;
+    pool_leave();
 }
 
 extern "C" const char* cpic_last_error(const cpic_ctx* c) { return c ? c->err.c_str() : g_static_error.c_str(); }
@@ -443,10 +444,10 @@ static cpic_status reset_counters(cpic_ctx* c, int n)
 }
 
 // the initial condition of the fields (into buffer 0) and the particles
-template <typename T> static cpic_status enqueue_ic(cpic_ctx* c, const ICArgs& a)
+template <typename T> static cpic_status enqueue_ic(cpic_ctx* c, const ICArgs& a, const ICWork& w)
 {
-    hipError_t e = c->nc == 2 ? ic_glasma2<T>(a, *c->icw, F2<T>(c, 0), c->st)
-                              : ic_glasma<T>(a, *c->icw, F<T>(c, 0), c->d_fails, c->st);
+    hipError_t e = c->nc == 2 ? ic_glasma2<T>(a, w, F2<T>(c, 0), c->st)
+                              : ic_glasma<T>(a, w, F<T>(c, 0), c->d_fails, c->st);
     if (e == hipSuccess && c->np > 0) {
         PartICArgs pa{};
         pa.N = c->N;
@@ -463,9 +464,27 @@ template <typename T> static cpic_status enqueue_ic(cpic_ctx* c, const ICArgs& a
     return CPIC_OK;
 }
 
+// the whole new state; ends with the stream idle and the count of failed links in h_stage
+static cpic_status enqueue_init(cpic_ctx* c, const ICArgs& a, const ICWork& w)
+{
+    HIPCHK(c, hipMemsetAsync(c->d_fails, 0, sizeof(int), c->st), "IC");
+    cpic_status s = c->prec == CPIC_FP64 ? enqueue_ic<double>(c, a, w) : enqueue_ic<float>(c, a, w);
+    if (s) return s;
+    HIPCHK(c, hipMemcpyAsync(c->h_stage, c->d_fails, sizeof(int), hipMemcpyDeviceToHost, c->st), "IC");
+    s = reset_pid(c);
+    if (s) return s;
+    c->cur = 0;
+    return reset_counters(c, 0);  // synchronises
+}
+
 extern "C" cpic_status cpic_init_mv(cpic_ctx* c)
 {
     if (!c) return fail(nullptr, CPIC_E_INVALID, "cpic_init_mv: NULL context");
+    {
+        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+        HIPCHK(c, hipStreamIsCapturing(c->st, &cap), "cpic_init_mv");
+        if (cap != hipStreamCaptureStatusNone) return hip_fail(c, hipErrorStreamCaptureUnsupported, "cpic_init_mv");
+    }
     ICArgs a{};
     a.N = c->N;
     a.n_sheets = c->gp.n_sheets;
@@ -475,20 +494,23 @@ extern "C" cpic_status cpic_init_mv(cpic_ctx* c)
     a.uvhat = c->gp.uv_GeV > 0 ? c->gp.uv_GeV * c->a_gev : 0.0;
     a.tol = 1e-14;
     a.maxit = 50;
-    HIPCHK(c, hipMemsetAsync(c->d_fails, 0, sizeof(int), c->st), "IC");
-    cpic_status s = c->prec == CPIC_FP64 ? enqueue_ic<double>(c, a) : enqueue_ic<float>(c, a);
+    // It works in the buffer sets, whose state it replaces (the new one goes to the
+    // first, from the links on), and allocates only what does not fit there.
+    const size_t fbytes = (size_t)c->rps * c->V * c->tsz;
+    ICScratch mem(c->device);
+    ICWork w{};
+    mem.lend(c->fbuf[2], fbytes, true);
+    mem.lend(c->fbuf[1], fbytes, true);
+    mem.lend(c->fbuf[0], fbytes, false);
+    HIPCHK(c, ic_reserve(a, c->nc, c->prec == CPIC_FP32, mem, &w), "cpic_init_mv");
+    c->initialised = false;  // until the new state is there
+    const cpic_status s = enqueue_init(c, a, w);
     if (s) {
         (void)hipStreamSynchronize(c->st);
         return s;
     }
-    int* fails = static_cast<int*>(c->h_stage);
-    HIPCHK(c, hipMemcpyAsync(fails, c->d_fails, sizeof(int), hipMemcpyDeviceToHost, c->st), "IC");
-    s = reset_pid(c);
-    if (s) return s;
-    c->cur = 0;
     c->initialised = true;
-    s = reset_counters(c, 0);  // synchronises
-    if (s) return s;
+    const int* fails = static_cast<const int*>(c->h_stage);
     if (*fails) return fail(c, CPIC_E_IC_NEWTON, "cpic_init_mv: initial-link Newton solve failed on " +
                                                      std::to_string(*fails) + " links");
     return CPIC_OK;

@@ -29,6 +29,7 @@ struct cpic_ctx {
     cpic_particle_params pp{};
     hipStream_t st = nullptr;
     bool own_stream = false;
+    int device = 0;  // current when the context was made: its memory is there
     int N = 0, V = 0, prec = 0;
     int nc = 3;     // SU(N_c): 3, or 2 for the SU(2) variant
     int rps = 68;   // reals per site of a field buffer set (68 for SU(3), 20 for SU(2))
@@ -66,10 +67,8 @@ struct cpic_ctx {
     int* d_step = nullptr;
     int* d_err = nullptr;
     int* d_fails = nullptr;
-    cpic::ICWorkspace icw_own{};             // of a single event
-    cpic::ICWorkspace* icw = &icw_own;       // an event of a batch uses the batch's
     cpic::ExchangeBuffers xb_own{};
-    cpic::ExchangeBuffers* xb = &xb_own;     // likewise
+    cpic::ExchangeBuffers* xb = &xb_own;     // an event of a batch uses the batch's
     double* dpart = nullptr;  // diagnostics partials
     double* dout = nullptr;   // diagnostics results [8 + 2]
     int dcap = 0;

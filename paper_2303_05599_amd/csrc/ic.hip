@@ -411,18 +411,22 @@ __device__ __forceinline__ void stQ(double* p, int s, int V, const q4<double>& q
     p[3 * (size_t)V + s] = q.z;
 }
 
+struct Segments {
+    double* p[kMaxSegments];
+};
+
 // The inverse transform along x and the Wilson lines: a workgroup owns RB whole
 // rows (one thread per site, SPT where a row is longer than the workgroup) and
 // takes the sheets of its segment (blockIdx.y) in order.  Per sheet it reads the
 // kept columns of the planes, transforms them in LDS, and every thread
-// multiplies V^+(x) <- V^+(x) exp(-i alpha_n(x)), kept in registers.  out[segment]
+// multiplies V^+(x) <- V^+(x) exp(-i alpha_n(x)), kept in registers.  segs.p[segment]
 // receives the product of the segment's sheets.  Bound: the FP64 arithmetic of
 // the exponentials and the LDS traffic of the transforms, about equal.
 template <int NC, int SITES>
 __global__ __launch_bounds__(SITES > 512 ? 512 : SITES, SITES > 512 ? 2 : 4) void rows_wilson_kernel(
-    const d2* __restrict__ spec, int N, int nk, int kc, int RB, int nsh, int seg_len, double* __restrict__ out, Fft f)
+    const d2* __restrict__ spec, int N, int nk, int kc, int RB, int nsh, int seg_len, Segments segs, Fft f)
 {
-    constexpr int PAIRS = NC == 2 ? 2 : 4, SPT = SITES > 512 ? 2 : 1, MW = NC == 2 ? 4 : 18;
+    constexpr int PAIRS = NC == 2 ? 2 : 4, SPT = SITES > 512 ? 2 : 1;
     __shared__ d2 lds[2][PAIRS * SITES];
     const int V = N * N, y0 = (int)blockIdx.x * RB, rows = min(RB, N - y0), ns = rows * N;
     const int first = (int)blockIdx.y * seg_len, last = min(nsh, first + seg_len);
@@ -474,7 +478,7 @@ __global__ __launch_bounds__(SITES > 512 ? 512 : SITES, SITES > 512 ? 2 : 4) voi
         }
         __syncthreads();  // the next sheet's first stage overwrites a buffer
     }
-    out += (size_t)blockIdx.y * MW * V;
+    double* const out = segs.p[blockIdx.y];
 #pragma unroll
     for (int k = 0; k < SPT; k++) {
         const int t = (int)threadIdx.x + k * (int)blockDim.x;
@@ -486,17 +490,17 @@ __global__ __launch_bounds__(SITES > 512 ? 512 : SITES, SITES > 512 ? 2 : 4) voi
 
 // Vdag <- [Vdag] seg_0 seg_1 ... (with Vdag in front unless `fresh`)
 template <int NC>
-__global__ void join_segments_kernel(const double* __restrict__ seg, int nseg, int V, int fresh, double* Vdag)
+__global__ void join_segments_kernel(Segments seg, int nseg, int V, int fresh, double* Vdag)
 {
     const int s = blockIdx.x * blockDim.x + threadIdx.x;
     if (s >= V) return;
     if constexpr (NC == 2) {
-        q4<double> q = fresh ? ldQ(seg, s, V) : ldQ(Vdag, s, V);
-        for (int k = fresh ? 1 : 0; k < nseg; k++) q = qmul(q, ldQ(seg + (size_t)k * 4 * V, s, V));
+        q4<double> q = ldQ(fresh ? seg.p[0] : Vdag, s, V);
+        for (int k = fresh ? 1 : 0; k < nseg; k++) q = qmul(q, ldQ(seg.p[k], s, V));
         stQ(Vdag, s, V, q);
     } else {
-        m3<double> m = fresh ? ldM(seg, s, V) : ldM(Vdag, s, V);
-        for (int k = fresh ? 1 : 0; k < nseg; k++) m = mul(m, ldM(seg + (size_t)k * 18 * V, s, V));
+        m3<double> m = ldM(fresh ? seg.p[0] : Vdag, s, V);
+        for (int k = fresh ? 1 : 0; k < nseg; k++) m = mul(m, ldM(seg.p[k], s, V));
         stM(Vdag, s, V, m);
     }
 }
@@ -807,24 +811,59 @@ static hipError_t convert_to_float(const double* src, float* dst, size_t n, hipS
 // to the next.
 constexpr size_t kChunkBytes = (size_t)64 << 20;
 
-// The parts of the workspace of an initial condition
-struct ICWork {
-    d2 *tw, *spec;             // twiddle tables [3][N], spectral planes of a chunk
-    double *K, *seg, *VA, *VB; // Poisson factors, segment products, Wilson lines
-    double* U;                 // links in double precision (single-precision runs)
-};
-
-// The Wilson lines V^+ of both nuclei (SU(3): [18][V] matrices; SU(2): [4][V]
-// quaternions).
-template <int NC>
-static hipError_t wilson_lines(const ICArgs& a, ICWorkspace& ws, bool double_links, ICWork& w, hipStream_t st)
+void ICScratch::lend(void* base, size_t bytes, bool to_end)
 {
-    constexpr int pairs = NC == 2 ? 2 : 4, MW = NC == 2 ? 4 : 18;
-    const int N = a.N, V = N * N;
-    const Radices R = radices_of(N);
-    if (R.n < 0 || N > kMaxFFT || N < 4) return hipErrorInvalidValue;
-    Radices B = R;  // the opposite order
-    for (int s = 0; s < R.n; s++) B.r[s] = R.r[R.n - 1 - s];
+    if (base) ranges[nranges++] = {static_cast<char*>(base), bytes / 256 * 256, to_end};
+}
+int ICScratch::want(size_t bytes, bool to_end)
+{
+    Part& p = parts[nparts++];
+    p = {(bytes + 255) / 256 * 256, nullptr};
+    for (int k = 0; k < nranges && !p.at; k++) {
+        Range& r = ranges[k];
+        if (p.bytes > r.left || (to_end && !r.to_end)) continue;
+        p.at = r.base;
+        r.base += p.bytes;
+        r.left -= p.bytes;
+    }
+    return nparts - 1;
+}
+hipError_t ICScratch::make()
+{
+    for (;;) {
+        // the largest part left starts a block, the others that fit into it follow
+        int first = -1;
+        for (int k = 0; k < nparts; k++)
+            if (!parts[k].at && (first < 0 || parts[k].bytes > parts[first].bytes)) first = k;
+        if (first < 0) return hipSuccess;
+        bool in[32] = {};
+        size_t total = parts[first].bytes;
+        in[first] = true;
+        for (int k = 0; k < nparts; k++)
+            if (!parts[k].at && !in[k] && total + parts[k].bytes <= kPoolBlockBytes) {
+                in[k] = true;
+                total += parts[k].bytes;
+            }
+        CK(pool_take(device, total, &blocks[nblocks]));
+        char* at = static_cast<char*>(blocks[nblocks++].p);
+        for (int k = 0; k < nparts; k++)
+            if (in[k]) {
+                parts[k].at = at;
+                at += parts[k].bytes;
+            }
+    }
+}
+ICScratch::~ICScratch()
+{
+    for (int k = 0; k < nblocks; k++) pool_give(device, blocks[k]);
+}
+
+hipError_t ic_reserve(const ICArgs& a, int n_colors, bool double_links, ICScratch& mem, ICWork* w)
+{
+    const int pairs = n_colors == 2 ? 2 : 4, MW = n_colors == 2 ? 4 : 18, N = a.N;
+    const size_t V = (size_t)N * N;
+    if (N > kMaxFFT || N < 4 || radices_of(N).n < 0) return hipErrorInvalidValue;
+    *w = ICWork{};
     const Band bd = band_of(N, a.uvhat);
     const size_t per_sheet = (size_t)pairs * N * bd.nk * sizeof(d2);
     // (and of at most 16383 sheets: four planes each in a grid dimension of 65535)
@@ -838,7 +877,7 @@ static hipError_t wilson_lines(const ICArgs& a, ICWorkspace& ws, bool double_lin
     const int RB = std::max(1, 256 / N), groups = (N + RB - 1) / RB;
     const int sites = RB * N, wt = std::min(512, (sites + 63) / 64 * 64), slots = 256 * (16 / (wt / 64));
     int seg_len = chunk;
-    for (double best = 1e300, k = 1; k <= std::min(chunk, 16); k++) {
+    for (double best = 1e300, k = 1; k <= std::min(chunk, kMaxSegments); k++) {
         const int len = (chunk + (int)k - 1) / (int)k, nseg = (chunk + len - 1) / len;
         const double cost = ((groups * nseg + slots - 1) / slots) * (len + 0.7) + 0.1 * nseg;
         if (cost < best) {
@@ -846,30 +885,39 @@ static hipError_t wilson_lines(const ICArgs& a, ICWorkspace& ws, bool double_lin
             seg_len = len;
         }
     }
-    const int max_seg = (chunk + seg_len - 1) / seg_len;
-    const bool direct = max_seg == 1 && chunk >= a.n_sheets;  // one segment: no joining
-    {
-        // one block of memory, every part on a 256-byte boundary
-        size_t at = 0;
-        auto part = [&](size_t bytes) {
-            const size_t p = at;
-            at += (bytes + 255) / 256 * 256;
-            return p;
-        };
-        const size_t mw = sizeof(double) * MW * V;
-        const size_t o_tw = part(sizeof(d2) * 3 * N), o_K = part(sizeof(double) * bd.nk * N);
-        const size_t o_spec = part(per_sheet * chunk), o_A = part(mw), o_B = part(mw);
-        const size_t o_seg = part(direct ? 0 : mw * max_seg), o_U = part(double_links ? 2 * mw : 0);
-        CK(ws.reserve(at));
-        char* base = static_cast<char*>(ws.base);
-        w.tw = (d2*)(base + o_tw);
-        w.K = (double*)(base + o_K);
-        w.spec = (d2*)(base + o_spec);
-        w.VA = (double*)(base + o_A);
-        w.VB = (double*)(base + o_B);
-        w.seg = (double*)(base + o_seg);
-        w.U = (double*)(base + o_U);
-    }
+    const int nseg = (chunk + seg_len - 1) / seg_len;
+    w->chunk = chunk;
+    w->seg_len = seg_len;
+    w->direct = nseg == 1 && chunk >= a.n_sheets;  // one segment: no joining
+    const size_t mw = sizeof(double) * MW * V;
+    const int va = mem.want(mw, true), vb = mem.want(mw, true), u = double_links ? mem.want(2 * mw, true) : -1;
+    int seg[kMaxSegments];
+    for (int k = 0; k < nseg && !w->direct; k++) seg[k] = mem.want(mw, false);
+    const int K = mem.want(sizeof(double) * bd.nk * N, false), tw = mem.want(sizeof(d2) * 3 * N, false);
+    const int spec = mem.want(per_sheet * chunk, false);
+    CK(mem.make());
+    w->VA = mem.at<double>(va);
+    w->VB = mem.at<double>(vb);
+    if (double_links) w->U = mem.at<double>(u);
+    for (int k = 0; k < nseg && !w->direct; k++) w->seg[k] = mem.at<double>(seg[k]);
+    w->K = mem.at<double>(K);
+    w->tw = mem.at<d2>(tw);
+    w->spec = mem.at<d2>(spec);
+    return hipSuccess;
+}
+
+// The Wilson lines V^+ of both nuclei (SU(3): [18][V] matrices; SU(2): [4][V]
+// quaternions).
+template <int NC> static hipError_t wilson_lines(const ICArgs& a, const ICWork& w, hipStream_t st)
+{
+    constexpr int pairs = NC == 2 ? 2 : 4;
+    const int N = a.N, V = N * N, chunk = w.chunk, seg_len = w.seg_len;
+    const Radices R = radices_of(N);
+    Radices B = R;  // the opposite order
+    for (int s = 0; s < R.n; s++) B.r[s] = R.r[R.n - 1 - s];
+    const Band bd = band_of(N, a.uvhat);
+    const int RB = std::max(1, 256 / N), groups = (N + RB - 1) / RB;
+    const int sites = RB * N, wt = std::min(512, (sites + 63) / 64 * 64);
     hipLaunchKernelGGL(twiddle_kernel, dim3(3), dim3(256), 0, st, w.tw, N, R.n, radix_code(R), radix_code(B));
     hipLaunchKernelGGL(poisson_kernel, dim3((bd.nk * N + 255) / 256), dim3(256), 0, st, w.K, N, bd.nk, bd.kc, a.mhat,
                        a.uvhat);
@@ -888,13 +936,14 @@ static hipError_t wilson_lines(const ICArgs& a, ICWorkspace& ws, bool double_lin
             const dim3 cg(col_groups, nsh * pairs);
             if (N > 512) hipLaunchKernelGGL(columns_kernel<512>, cg, dim3(512), 0, st, w.spec, N, bd.nk, bsh, w.K, scale, fwd, back);
             else hipLaunchKernelGGL(columns_kernel<256>, cg, dim3(256), 0, st, w.spec, N, bd.nk, bsh, w.K, scale, fwd, back);
-            double* dst = direct ? Vdag : w.seg;
+            Segments dst{};
+            for (int k = 0; k < nseg; k++) dst.p[k] = w.direct ? Vdag : w.seg[k];
             const dim3 wg(groups, nseg);
             if (sites <= 256) hipLaunchKernelGGL((rows_wilson_kernel<NC, 256>), wg, dim3(wt), 0, st, w.spec, N, bd.nk, bd.kc, RB, nsh, seg_len, dst, inv);
             else if (sites <= 512) hipLaunchKernelGGL((rows_wilson_kernel<NC, 512>), wg, dim3(wt), 0, st, w.spec, N, bd.nk, bd.kc, RB, nsh, seg_len, dst, inv);
             else hipLaunchKernelGGL((rows_wilson_kernel<NC, 1024>), wg, dim3(wt), 0, st, w.spec, N, bd.nk, bd.kc, RB, nsh, seg_len, dst, inv);
-            if (!direct)
-                hipLaunchKernelGGL(join_segments_kernel<NC>, dim3((V + 255) / 256), dim3(256), 0, st, w.seg, nseg, V,
+            if (!w.direct)
+                hipLaunchKernelGGL(join_segments_kernel<NC>, dim3((V + 255) / 256), dim3(256), 0, st, dst, nseg, V,
                                    s0 == 0 ? 1 : 0, Vdag);
             CK(hipGetLastError());
         }
@@ -902,29 +951,12 @@ static hipError_t wilson_lines(const ICArgs& a, ICWorkspace& ws, bool double_lin
     return hipSuccess;
 }
 
-hipError_t ICWorkspace::reserve(size_t need)
-{
-    if (need <= bytes) return hipSuccess;
-    release();
-    const hipError_t e = hipMalloc(&base, need);
-    if (e == hipSuccess) bytes = need;
-    else base = nullptr;
-    return e;
-}
-void ICWorkspace::release()
-{
-    (void)hipFree(base);
-    base = nullptr;
-    bytes = 0;
-}
-
 template <typename T>
-hipError_t ic_glasma(const ICArgs& a, ICWorkspace& ws, const Fields<T>& out, int* d_fails, hipStream_t st)
+hipError_t ic_glasma(const ICArgs& a, const ICWork& w, const Fields<T>& out, int* d_fails, hipStream_t st)
 {
     constexpr bool own = std::is_same<T, double>::value;  // the links are solved in place
     const int N = a.N, V = N * N;
-    ICWork w{};
-    CK(wilson_lines<3>(a, ws, !own, w, st));
+    CK(wilson_lines<3>(a, w, st));
     double* U = w.U;
     if constexpr (own) U = out.U;
     hipLaunchKernelGGL(links_kernel, dim3((2 * V + 127) / 128), dim3(128), 0, st, w.VA, w.VB, N, a.tol, a.maxit, U,
@@ -935,8 +967,8 @@ hipError_t ic_glasma(const ICArgs& a, ICWorkspace& ws, const Fields<T>& out, int
     if constexpr (!own) CK(convert_to_float(U, out.U, (size_t)36 * V, st));
     return hipGetLastError();
 }
-template hipError_t ic_glasma<double>(const ICArgs&, ICWorkspace&, const Fields<double>&, int*, hipStream_t);
-template hipError_t ic_glasma<float>(const ICArgs&, ICWorkspace&, const Fields<float>&, int*, hipStream_t);
+template hipError_t ic_glasma<double>(const ICArgs&, const ICWork&, const Fields<double>&, int*, hipStream_t);
+template hipError_t ic_glasma<float>(const ICArgs&, const ICWork&, const Fields<float>&, int*, hipStream_t);
 
 // ------------------------------------------------------------------ SU(2)
 // tau = 0 links: W = U^A + U^B is a real multiple of an SU(2) element S, and
@@ -977,12 +1009,11 @@ __global__ void pi02_kernel(const double* __restrict__ VA, const double* __restr
 }
 
 template <typename T>
-hipError_t ic_glasma2(const ICArgs& a, ICWorkspace& ws, const Fields2<T>& out, hipStream_t st)
+hipError_t ic_glasma2(const ICArgs& a, const ICWork& w, const Fields2<T>& out, hipStream_t st)
 {
     constexpr bool own = std::is_same<T, double>::value;
     const int N = a.N, V = N * N;
-    ICWork w{};
-    CK(wilson_lines<2>(a, ws, !own, w, st));
+    CK(wilson_lines<2>(a, w, st));
     double* U = w.U;
     if constexpr (own) U = out.U;
     hipLaunchKernelGGL(links2_kernel, dim3((2 * V + 255) / 256), dim3(256), 0, st, w.VA, w.VB, N, U);
@@ -992,8 +1023,8 @@ hipError_t ic_glasma2(const ICArgs& a, ICWorkspace& ws, const Fields2<T>& out, h
     if constexpr (!own) CK(convert_to_float(U, out.U, (size_t)8 * V, st));
     return hipGetLastError();
 }
-template hipError_t ic_glasma2<double>(const ICArgs&, ICWorkspace&, const Fields2<double>&, hipStream_t);
-template hipError_t ic_glasma2<float>(const ICArgs&, ICWorkspace&, const Fields2<float>&, hipStream_t);
+template hipError_t ic_glasma2<double>(const ICArgs&, const ICWork&, const Fields2<double>&, hipStream_t);
+template hipError_t ic_glasma2<float>(const ICArgs&, const ICWork&, const Fields2<float>&, hipStream_t);
 
 // SU(2) particles: block 0 as for SU(3); the charge from the Darboux
 // parametrisation (Sec. IV.A) with J^2 = q2: words 0, 1 of block 1 give

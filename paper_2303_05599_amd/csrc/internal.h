@@ -336,6 +336,18 @@ hipError_t launch_tile_start(const unsigned* sorted_keys, int np, int N, int tx,
 constexpr int kGatherSortTileX = 32, kGatherSortTileY = 16;
 constexpr int kSortEvery = 16;  // steps between reorderings of moving particles (measured best of 8, 16, 32, 64)
 
+// ---- memory for the time of one call (pool.hip)
+constexpr size_t kPoolBlockBytes = (size_t)64 << 20;  // larger blocks are not kept
+struct PoolBlock {
+    void* p = nullptr;
+    size_t bytes = 0;
+};
+hipError_t pool_take(int device, size_t bytes, PoolBlock* out);  // device: the current one
+void pool_give(int device, PoolBlock b);                         // the work that used it has ended
+// every context, from its creation to its end
+void pool_enter();
+void pool_leave();
+
 // ---- initial condition (ic.hip), always double precision
 struct ICArgs {
     int N;
@@ -345,18 +357,47 @@ struct ICArgs {
     double tol;
     int maxit;
 };
-// Device memory the initial condition works in, kept by its owner (a context, or
-// a batch for all its events) from one initial condition to the next: releasing
-// a block of this size costs about 230 us.  One initial condition at a time.
-struct ICWorkspace {
-    void* base = nullptr;
-    size_t bytes = 0;
-    hipError_t reserve(size_t need);  // the block may move: its contents are not kept
-    void release();
+// Device memory an initial condition works in, for the time of one call: ranges lent
+// to it (buffer sets whose contents the call replaces or does not need) and blocks of
+// the pool for what does not fit there, at most 64 MiB each where the parts allow.
+struct ICScratch {
+    struct Range {
+        char* base;
+        size_t left;
+        bool to_end;  // free until the call's last kernel, not only until the links are solved
+    };
+    struct Part {
+        size_t bytes;
+        char* at;
+    };
+    int device;
+    Range ranges[3];
+    Part parts[32];
+    PoolBlock blocks[32];
+    int nranges = 0, nparts = 0, nblocks = 0;
+    explicit ICScratch(int dev) : device(dev) {}
+    ICScratch(const ICScratch&) = delete;
+    ~ICScratch();  // (the stream has to be idle)
+    void lend(void* base, size_t bytes, bool to_end);
+    int want(size_t bytes, bool to_end);  // a part's number
+    hipError_t make();                    // the parts have their places (256-byte aligned) from here on
+    template <typename T> T* at(int part) const { return reinterpret_cast<T*>(parts[part].at); }
 };
+// Where the parts of an initial condition lie and how its sheets are split
+constexpr int kMaxSegments = 16;
+struct ICWork {
+    double2 *tw, *spec;        // twiddle tables [3][N], spectral planes of a chunk
+    double *K, *VA, *VB;       // Poisson factors, Wilson lines of the nuclei
+    double* U;                 // links in double precision (single-precision runs)
+    double* seg[kMaxSegments]; // products of a segment's sheets
+    int chunk, seg_len;
+    bool direct;               // one segment, which is the Wilson line
+};
+// plans the work and finds its memory; launches nothing
+hipError_t ic_reserve(const ICArgs& a, int n_colors, bool double_links, ICScratch& mem, ICWork* w);
 // builds U, pi (phi = E = 0) into a buffer set; counts failures in *d_fails (device int); asynchronous
 template <typename T>
-hipError_t ic_glasma(const ICArgs& a, ICWorkspace& ws, const Fields<T>& out, int* d_fails, hipStream_t st);
+hipError_t ic_glasma(const ICArgs& a, const ICWork& w, const Fields<T>& out, int* d_fails, hipStream_t st);
 struct PartICArgs {
     int N, np, azimuth_uniform;
     uint64_t seed;
@@ -367,7 +408,7 @@ template <typename T>
 hipError_t ic_particles(const PartICArgs& a, T* r /*[19][np]*/, int* cell, hipStream_t st);
 // SU(2) variant: links, pi(0); Darboux charges with |Q|^2 = q2
 template <typename T>
-hipError_t ic_glasma2(const ICArgs& a, ICWorkspace& ws, const Fields2<T>& out, hipStream_t st);
+hipError_t ic_glasma2(const ICArgs& a, const ICWork& w, const Fields2<T>& out, hipStream_t st);
 template <typename T>
 hipError_t ic_particles2(const PartICArgs& a, double q2, T* r, int* cell, hipStream_t st);
 

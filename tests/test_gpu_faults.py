@@ -16,11 +16,12 @@ N, BOX = 48, 4.5
 DT = BOX / N / 8
 
 
-def make(cp, load=False, **glasma):
+def make(cp, init=True, **glasma):
     g = dict(N=N, L_fm=BOX, n_sheets=1, tau_max_fm=400 * DT, seed=5)
     g.update(glasma)
     ctx = cp.Context(g, dict(n=500, mass_GeV=1.27, tau_form_fm=0.0, pT_max_GeV=3.0, seed=4), stream=None)
-    ctx.init_mv()
+    if init:
+        ctx.init_mv()
     return ctx
 
 
@@ -80,8 +81,27 @@ def tuner_keeps_the_faster_form(cp, shim):
     assert "pipelined step" in piped_line and "separate step" in line, piped_line + line
 
 
+def failed_workspace(cp, shim):
+    """No memory for the initial condition's work: an error, the state and the next launches untouched."""
+    small, ctx, ref = make(cp), make(cp, n_sheets=40, init=False), make(cp, init=False)
+    for c in (ctx, ref):
+        c.load_state(small.state(), 0, small.get_state(cp.STATE_PARTICLES))
+    evolve(ctx, 40)
+    ref.step(40)
+    shim.shim_fail(MALLOC, 0, ALL, 1 << 20)
+    with pytest.raises(cp.CpicError):
+        ctx.init_mv()
+    shim.shim_fail(MALLOC, 0, 0, 0)
+    check_same(ctx, ref)
+    evolve(ctx, 20)
+    ref.step(20)
+    check_same(ctx, ref)
+    ctx.init_mv()
+    check_same(ctx, make(cp, n_sheets=40))
+
+
 @pytest.mark.gpu
-@pytest.mark.parametrize("scenario", [failed_graph_launch, tuner_keeps_the_faster_form], ids=lambda f: f.__name__)
+@pytest.mark.parametrize("scenario", [failed_graph_launch, tuner_keeps_the_faster_form, failed_workspace], ids=lambda f: f.__name__)
 def test_forced_failure(scenario, tmp_path):
     torch = pytest.importorskip("torch")
     if not torch.cuda.is_available():

@@ -1,0 +1,61 @@
+"""Device memory that a context holds: what a call needs only while it runs is released again."""
+import ctypes
+
+import pytest
+
+cp = pytest.importorskip("paper_2303_05599_amd")
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+SLACK = 4 << 20   # the allocator's granularity (2 MiB), at two places
+stream = None     # one for all: the runtime keeps spill memory of its own per hardware queue
+
+
+@pytest.fixture(scope="module", autouse=True)
+def gpu():
+    global stream
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    torch.cuda.set_device(0)
+    own = torch.cuda.Stream()
+    stream = ctypes.c_void_p(own.cuda_stream)
+    yield
+
+
+def free():
+    torch.cuda.synchronize()
+    return torch.cuda.mem_get_info()[0]
+
+
+def make(N, sheets, prec, nc):
+    L = 6.0 * min(1.0, N / 64)
+    return cp.Context(dict(N=N, L_fm=L, n_sheets=sheets, tau_max_fm=400 * L / N / 8, precision=prec, seed=5, n_colors=nc),
+                      dict(n=N * N // 3, mass_GeV=1.27, tau_form_fm=0.0, seed=4), stream=stream)
+
+
+def held_by_calls(call, *args):
+    """What the first of four contexts' calls leaves allocated, and what those of the others add; all is gone with the last one."""
+    warm = make(*args)      # the runtime's own memory
+    call(warm)
+    warm.close()
+    at_first = free()
+    ctxs = [make(*args) for _ in range(4)]
+    made = free()
+    call(ctxs[0])
+    first = made - free()
+    for c in ctxs[1:]:
+        call(c)
+    others = made - free() - first
+    for c in ctxs:
+        c.close()
+    assert at_first - free() <= SLACK
+    return first, others
+
+
+KEPT = 2 * (64 << 20)  # blocks that wait for the next call, whatever the number of contexts
+
+
+@pytest.mark.parametrize("N,sheets,prec,nc", [(96, 50, cp.FP64, 3), (96, 50, cp.FP32, 3), (324, 20, cp.FP64, 2),
+                                              (576, 10, cp.FP64, 3), (576, 10, cp.FP32, 3)])
+def test_initial_condition(N, sheets, prec, nc):
+    first, others = held_by_calls(lambda c: c.init_mv(), N, sheets, prec, nc)
+    assert first <= KEPT + SLACK and others <= SLACK
