@@ -11,8 +11,9 @@
  *     failure; nothing aborts.  cpic_last_error() gives a message.
  *   - A context owns all device memory it allocates and frees it in
  *     cpic_destroy().  Memory that a call needs only while it runs is shared by
- *     all contexts of the process: up to two blocks of 64 MiB stay allocated
- *     between calls, until the last context is destroyed.  Host buffers passed in are owned by the caller; the
+ *     all contexts of the process: up to two blocks of 64 MiB, and 32 MiB of
+ *     pinned host memory, stay allocated between calls, until the last context
+ *     is destroyed.  Host buffers passed in are owned by the caller; the
  *     library reads/writes them only during the call, after synchronising
  *     its stream.
  *   - All device work of a context is enqueued on the HIP stream given to

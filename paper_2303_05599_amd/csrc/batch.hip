@@ -70,7 +70,6 @@ struct cpic_batch {
     EventDesc* d_desc = nullptr;
     std::vector<EventDesc> desc;  // host copy (kept alive for the asynchronous upload)
     std::map<std::vector<int>, Plan> plans;
-    ExchangeBuffers xb{};  // of the events' state exchange, one at a time
     std::string err;
 };
 
@@ -277,7 +276,6 @@ extern "C" cpic_status cpic_batch_create(int32_t n_events, const cpic_glasma_par
         // the batch launches its own kernels over all events: the events'
         // records keep the gather push's order
         if (c->cfg.split == 4) c->cfg.split = 3;
-        c->xb = &b->xb;
         b->ev.push_back(c);
     }
     // compressed-link LDS tiles of 64 x 4 sites (cpic_batch_tune picks among the shapes)
@@ -680,7 +678,6 @@ extern "C" void cpic_batch_destroy(cpic_batch* b)
     }
     if (b->ev_fork) (void)hipEventDestroy(b->ev_fork);
     for (auto c : b->ev) cpic_destroy(c);
-    b->xb.release();
     if (b->own_stream) (void)hipStreamDestroy(b->st);
     delete b;
 }

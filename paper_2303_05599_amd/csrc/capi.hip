@@ -119,7 +119,6 @@ static void free_all(cpic_ctx* c)
     (void)hipFree(c->sb.count); (void)hipFree(c->sb.offs);
     (void)hipFree(c->tile_start); (void)hipFree(c->strag); (void)hipFree(c->strag_count);
     (void)hipFree(c->d_strag_total);
-    c->xb_own.release();
     if (c->own_stream && c->st) (void)hipStreamDestroy(c->st);
 }
 

@@ -11,16 +11,6 @@
 #include "internal.h"
 
 namespace cpic {
-// Staging of the state exchange (exchange.hip): two chunks in device and in
-// pinned host memory, allocated by the first exchange and kept by the owner (a
-// context, or a batch for all its events)
-struct ExchangeBuffers {
-    void *dev[2] = {nullptr, nullptr}, *pin[2] = {nullptr, nullptr};
-    hipEvent_t ev[2] = {nullptr, nullptr};
-    size_t bytes = 0;
-    hipError_t reserve(size_t need);
-    void release();
-};
 constexpr int kGraphSteps = 16;  // steps per captured graph (even: buffers return to their parity)
 }
 
@@ -67,8 +57,6 @@ struct cpic_ctx {
     int* d_step = nullptr;
     int* d_err = nullptr;
     int* d_fails = nullptr;
-    cpic::ExchangeBuffers xb_own{};
-    cpic::ExchangeBuffers* xb = &xb_own;     // an event of a batch uses the batch's
     double* dpart = nullptr;  // diagnostics partials
     double* dout = nullptr;   // diagnostics results [8 + 2]
     int dcap = 0;

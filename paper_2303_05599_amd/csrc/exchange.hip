@@ -5,7 +5,9 @@
 // The layouts are converted on the device, in chunks that pass through pinned
 // host memory: a kernel gathers a chunk into interchange order, a copy brings
 // it to a pinned buffer, and the host copies it to the caller's memory (or the
-// other way round) while the next chunk is on its way.  The caller's memory is
+// other way round) while the next chunk is on its way.  The device's chunks lie in
+// memory that is idle between steps (the field buffer set that does not hold the
+// state, the scratch records), the pinned ones are shared by all contexts.  The caller's memory is
 // pageable and often untouched, so its page faults bound a single host thread
 // (about 12 GB/s); a few threads share the host copies.
 // Measured (384^2, FP64, all four fields, 80 MB): get 23.0 -> 4.6 ms, of which the page
@@ -224,6 +226,46 @@ template <typename T> bool describe(const cpic_ctx* c, int which, Part* p, T** a
     }
 }
 
+// The chunks of one call, two on each side: on the device in the buffer set that does
+// not hold the state or, for particles, in the scratch records where those are
+// larger (both idle between steps); pinned from the pool.
+struct Staging {
+    cpic_ctx* c;
+    PoolPins pins{};
+    double* dev[2] = {nullptr, nullptr};
+    size_t bytes = 0;
+    bool done = false;  // the stream is idle
+    explicit Staging(cpic_ctx* ctx) : c(ctx) {}
+    Staging(const Staging&) = delete;
+    hipError_t open(bool particles, size_t total)
+    {
+        char* base = static_cast<char*>(c->fbuf[next_buffer(c->cur)]);
+        size_t room = (size_t)c->rps * c->V * c->tsz;
+        const size_t records = (size_t)kPartReals * (size_t)c->np * c->tsz;
+        if (particles && records > room) {
+            base = static_cast<char*>(c->sb.r2);
+            room = records;
+        }
+        // (half of it on a 256-byte boundary; up to kDirectBytes no device chunk is used)
+        bytes = std::min(total, kChunkBytes);
+        if (total > kDirectBytes) bytes = std::min(bytes, room / 512 * 256);
+        dev[0] = reinterpret_cast<double*>(base);
+        dev[1] = reinterpret_cast<double*>(base + room / 512 * 256);
+        return pool_take_pins(c->device, bytes, &pins);
+    }
+    hipError_t finish()
+    {
+        const hipError_t e = hipStreamSynchronize(c->st);
+        done = e == hipSuccess;
+        return done ? hipGetLastError() : e;
+    }
+    ~Staging()
+    {
+        // after an error part way a chunk may be in flight; pinned memory that cannot be waited for is left
+        if (pins.bytes && (done || hipStreamSynchronize(c->st) == hipSuccess)) pool_give_pins(c->device, pins);
+    }
+};
+
 template <typename T> hipError_t get_part(cpic_ctx* c, int which, double* host)
 {
     Part p;
@@ -232,16 +274,15 @@ template <typename T> hipError_t get_part(cpic_ctx* c, int which, double* host)
     if (!describe<T>(c, which, &p, &src, &comps)) return hipErrorInvalidValue;
     if (p.kind == kRecords || p.kind == kPtau)
         hipLaunchKernelGGL(invert_kernel, dim3((p.V + 255) / 256), dim3(256), 0, c->st, c->pid, p.V, c->sb.perm);
-    ExchangeBuffers& x = *c->xb;
     const size_t total = p.count * p.width * sizeof(double);
-    hipError_t e = x.reserve(std::min(total, kChunkBytes));
+    Staging x(c);
+    hipError_t e = x.open(p.kind == kRecords || p.kind == kPtau, total);
     if (e != hipSuccess) return e;
     if (total <= kDirectBytes) {
         hipLaunchKernelGGL(pack_kernel<T>, dim3((unsigned)((p.count * p.width + 255) / 256)), dim3(256), 0, c->st, p, src,
-                           static_cast<double*>(x.pin[0]), (size_t)0, p.count);
-        e = hipStreamSynchronize(c->st);
-        if (e == hipSuccess) e = hipGetLastError();
-        if (e == hipSuccess) std::memcpy(host, x.pin[0], total);
+                           static_cast<double*>(x.pins.pin[0]), (size_t)0, p.count);
+        e = x.finish();
+        if (e == hipSuccess) std::memcpy(host, x.pins.pin[0], total);
         return e;
     }
     const size_t per = std::max<size_t>(1, x.bytes / (p.width * sizeof(double)));
@@ -257,19 +298,20 @@ template <typename T> hipError_t get_part(cpic_ctx* c, int which, double* host)
             range(k, &first, &n);
             const int b = (int)(k & 1);
             hipLaunchKernelGGL(pack_kernel<T>, dim3((unsigned)((n * p.width + 255) / 256)), dim3(256), 0, c->st, p, src,
-                               static_cast<double*>(x.dev[b]), first, n);
-            e = hipMemcpyAsync(x.pin[b], x.dev[b], n * p.width * sizeof(double), hipMemcpyDeviceToHost, c->st);
-            if (e == hipSuccess) e = hipEventRecord(x.ev[b], c->st);
+                               x.dev[b], first, n);
+            e = hipMemcpyAsync(x.pins.pin[b], x.dev[b], n * p.width * sizeof(double), hipMemcpyDeviceToHost, c->st);
+            if (e == hipSuccess) e = hipEventRecord(x.pins.ev[b], c->st);
             if (e != hipSuccess) return e;
         }
         if (k > 0) {
             range(k - 1, &first, &n);
             const int b = (int)((k - 1) & 1);
-            e = hipEventSynchronize(x.ev[b]);
+            e = hipEventSynchronize(x.pins.ev[b]);
             if (e != hipSuccess) return e;
-            host_copy(host + first * p.width, x.pin[b], n * p.width * sizeof(double));
+            host_copy(host + first * p.width, x.pins.pin[b], n * p.width * sizeof(double));
         }
     }
+    x.done = true;  // the last chunk's event was the stream's last work
     return hipGetLastError();
 }
 
@@ -279,64 +321,34 @@ template <typename T> hipError_t set_part(cpic_ctx* c, int which, const double* 
     T* dst = nullptr;
     int comps = 0;
     if (!describe<T>(c, which, &p, &dst, &comps)) return hipErrorInvalidValue;
-    ExchangeBuffers& x = *c->xb;
     const size_t total = p.count * p.width * sizeof(double);
-    hipError_t e = x.reserve(std::min(total, kChunkBytes));
+    Staging x(c);
+    hipError_t e = x.open(p.kind == kRecords || p.kind == kPtau, total);
     if (e != hipSuccess) return e;
     if (total <= kDirectBytes) {
-        std::memcpy(x.pin[0], host, total);
+        std::memcpy(x.pins.pin[0], host, total);
         hipLaunchKernelGGL(unpack_kernel<T>, dim3((unsigned)((p.count * comps + 255) / 256)), dim3(256), 0, c->st, p,
-                           static_cast<const double*>(x.pin[0]), dst, c->pcell, (size_t)0, p.count, comps);
-        e = hipStreamSynchronize(c->st);
-        return e == hipSuccess ? hipGetLastError() : e;
+                           static_cast<const double*>(x.pins.pin[0]), dst, c->pcell, (size_t)0, p.count, comps);
+        return x.finish();
     }
     const size_t per = std::max<size_t>(1, x.bytes / (p.width * sizeof(double)));
     for (size_t k = 0, first = 0; first < p.count; k++, first += per) {
         const size_t n = std::min(per, p.count - first);
         const int b = (int)(k & 1);
         // (the copy that last read this pinned buffer, two chunks ago, is over)
-        if (k >= 2) e = hipEventSynchronize(x.ev[b]);
+        if (k >= 2) e = hipEventSynchronize(x.pins.ev[b]);
         if (e != hipSuccess) return e;
-        host_copy(x.pin[b], host + first * p.width, n * p.width * sizeof(double));
-        e = hipMemcpyAsync(x.dev[b], x.pin[b], n * p.width * sizeof(double), hipMemcpyHostToDevice, c->st);
-        if (e == hipSuccess) e = hipEventRecord(x.ev[b], c->st);
+        host_copy(x.pins.pin[b], host + first * p.width, n * p.width * sizeof(double));
+        e = hipMemcpyAsync(x.dev[b], x.pins.pin[b], n * p.width * sizeof(double), hipMemcpyHostToDevice, c->st);
+        if (e == hipSuccess) e = hipEventRecord(x.pins.ev[b], c->st);
         if (e != hipSuccess) return e;
         hipLaunchKernelGGL(unpack_kernel<T>, dim3((unsigned)((n * comps + 255) / 256)), dim3(256), 0, c->st, p,
-                           static_cast<const double*>(x.dev[b]), dst, c->pcell, first, n, comps);
+                           x.dev[b], dst, c->pcell, first, n, comps);
     }
-    // the pinned buffers are free again for the next call
-    e = hipStreamSynchronize(c->st);
-    return e == hipSuccess ? hipGetLastError() : e;
+    return x.finish();
 }
 
 }  // namespace
-
-hipError_t cpic::ExchangeBuffers::reserve(size_t need)
-{
-    if (need <= bytes) return hipSuccess;
-    release();
-    need = (need + 65535) / 65536 * 65536;
-    hipError_t e = hipSuccess;
-    for (int b = 0; b < 2 && e == hipSuccess; b++) {
-        e = hipMalloc(&dev[b], need);
-        if (e == hipSuccess) e = hipHostMalloc(&pin[b], need);
-        if (e == hipSuccess) e = hipEventCreateWithFlags(&ev[b], hipEventDisableTiming);
-    }
-    if (e == hipSuccess) bytes = need;
-    else release();
-    return e;
-}
-void cpic::ExchangeBuffers::release()
-{
-    for (int b = 0; b < 2; b++) {
-        (void)hipFree(dev[b]);
-        if (pin[b]) (void)hipHostFree(pin[b]);
-        if (ev[b]) (void)hipEventDestroy(ev[b]);
-        dev[b] = pin[b] = nullptr;
-        ev[b] = nullptr;
-    }
-    bytes = 0;
-}
 
 hipError_t cpic::exchange_get(cpic_ctx* c, int which, double* host)
 {

@@ -344,6 +344,14 @@ struct PoolBlock {
 };
 hipError_t pool_take(int device, size_t bytes, PoolBlock* out);  // device: the current one
 void pool_give(int device, PoolBlock b);                         // the work that used it has ended
+// two chunks of pinned host memory and an event for each, for the state exchange
+struct PoolPins {
+    void* pin[2] = {nullptr, nullptr};
+    hipEvent_t ev[2] = {nullptr, nullptr};
+    size_t bytes = 0;  // of a chunk
+};
+hipError_t pool_take_pins(int device, size_t bytes, PoolPins* out);
+void pool_give_pins(int device, const PoolPins& p);
 // every context, from its creation to its end
 void pool_enter();
 void pool_leave();

@@ -1,13 +1,14 @@
 // pool.hip -- memory that a call needs only while it runs (the initial condition's
-// spectral planes), kept for the next call of any context instead of being
-// allocated and released each time.
+// spectral planes, the state exchange's pinned chunks), kept for the next call of
+// any context instead of being allocated and released each time.
 //
 // Allocating fresh device memory costs more than the allocation itself (the first
 // pass over new pages): with a block of its own per call the initial condition and
 // read-back of a 144^2 event took 1345 us against 1263 with the block kept, a 384^2
 // one 6.69 ms against 6.30.  What is kept does not grow with the number of contexts: two
-// idle blocks of at most 64 MiB, released with the last context.  Calls that run
-// at the same time on several threads get blocks of their own.
+// idle blocks of at most 64 MiB and two idle pairs of pinned chunks (of 8 MiB at most),
+// released with the last context.  Calls that run at the same time on several
+// threads get memory of their own.
 #include <mutex>
 
 #include "internal.h"
@@ -16,13 +17,45 @@ namespace cpic {
 namespace {
 
 constexpr int kIdle = 2;
-struct Idle {
-    PoolBlock b;
+template <typename B> struct Idle {
+    B b;
     int device = 0;
 };
 std::mutex g_lock;
-Idle g_idle[kIdle];
+Idle<PoolBlock> g_idle[kIdle];
+Idle<PoolPins> g_pins[kIdle];
 int64_t g_users = 0;
+
+// the smallest idle one that is large enough (under the lock)
+template <typename B> bool find(Idle<B> (&idle)[kIdle], int device, size_t bytes, B* out)
+{
+    Idle<B>* fit = nullptr;
+    for (Idle<B>& i : idle)
+        if (i.b.bytes >= bytes && i.b.bytes > 0 && i.device == device && (!fit || i.b.bytes < fit->b.bytes)) fit = &i;
+    if (!fit) return false;
+    *out = fit->b;
+    *fit = Idle<B>{};
+    return true;
+}
+// the larger ones stay; returns what is to be released
+template <typename B> B keep(Idle<B> (&idle)[kIdle], int device, const B& b)
+{
+    std::lock_guard<std::mutex> hold(g_lock);
+    Idle<B>* at = &idle[0];
+    for (Idle<B>& i : idle)
+        if (i.b.bytes < at->b.bytes) at = &i;
+    if (g_users <= 0 || at->b.bytes >= b.bytes) return b;
+    const B gone = at->b;
+    *at = Idle<B>{b, device};
+    return gone;
+}
+void release(const PoolPins& p)
+{
+    for (int k = 0; k < 2; k++) {
+        if (p.pin[k]) (void)hipHostFree(p.pin[k]);
+        if (p.ev[k]) (void)hipEventDestroy(p.ev[k]);
+    }
+}
 
 }  // namespace
 
@@ -30,14 +63,7 @@ hipError_t pool_take(int device, size_t bytes, PoolBlock* out)
 {
     {
         std::lock_guard<std::mutex> hold(g_lock);
-        Idle* fit = nullptr;
-        for (Idle& i : g_idle)
-            if (i.b.p && i.device == device && i.b.bytes >= bytes && (!fit || i.b.bytes < fit->b.bytes)) fit = &i;
-        if (fit) {
-            *out = fit->b;
-            *fit = Idle{};
-            return hipSuccess;
-        }
+        if (find(g_idle, device, bytes, out)) return hipSuccess;
     }
     *out = PoolBlock{};
     const hipError_t e = hipMalloc(&out->p, bytes);
@@ -52,20 +78,34 @@ hipError_t pool_take(int device, size_t bytes, PoolBlock* out)
 
 void pool_give(int device, PoolBlock b)
 {
-    if (!b.p) return;
-    if (b.bytes <= kPoolBlockBytes) {
-        std::lock_guard<std::mutex> hold(g_lock);
-        // the larger blocks stay
-        Idle* at = &g_idle[0];
-        for (Idle& i : g_idle)
-            if (i.b.bytes < at->b.bytes) at = &i;
-        if (g_users > 0 && at->b.bytes < b.bytes) {
-            const Idle gone = *at;
-            *at = Idle{b, device};
-            b = gone.b;
-        }
-    }
+    if (b.bytes <= kPoolBlockBytes) b = keep(g_idle, device, b);
     (void)hipFree(b.p);
+}
+
+hipError_t pool_take_pins(int device, size_t bytes, PoolPins* out)
+{
+    {
+        std::lock_guard<std::mutex> hold(g_lock);
+        if (find(g_pins, device, bytes, out)) return hipSuccess;
+    }
+    PoolPins p{};
+    p.bytes = (bytes + 65535) / 65536 * 65536;
+    hipError_t e = hipSuccess;
+    for (int k = 0; k < 2 && e == hipSuccess; k++) {
+        e = hipHostMalloc(&p.pin[k], p.bytes);
+        if (e == hipSuccess) e = hipEventCreateWithFlags(&p.ev[k], hipEventDisableTiming);
+    }
+    if (e != hipSuccess) {
+        (void)hipGetLastError();
+        release(p);
+        p = PoolPins{};
+    }
+    *out = p;
+    return e;
+}
+void pool_give_pins(int device, const PoolPins& p)
+{
+    release(keep(g_pins, device, p));
 }
 
 void pool_enter()
@@ -75,16 +115,20 @@ void pool_enter()
 }
 void pool_leave()
 {
-    Idle gone[kIdle];
+    Idle<PoolBlock> gone[kIdle];
+    Idle<PoolPins> pins[kIdle];
     {
         std::lock_guard<std::mutex> hold(g_lock);
         if (--g_users > 0) return;
         for (int k = 0; k < kIdle; k++) {
             gone[k] = g_idle[k];
-            g_idle[k] = Idle{};
+            pins[k] = g_pins[k];
+            g_idle[k] = Idle<PoolBlock>{};
+            g_pins[k] = Idle<PoolPins>{};
         }
     }
-    for (const Idle& i : gone) (void)hipFree(i.b.p);
+    for (const auto& i : gone) (void)hipFree(i.b.p);
+    for (const auto& i : pins) release(i.b);
 }
 
 }  // namespace cpic

@@ -1,6 +1,8 @@
-"""Device memory that a context holds: what a call needs only while it runs is released again."""
+"""Device memory that a context holds: what a call needs only while it runs is not kept by it."""
+import concurrent.futures
 import ctypes
 
+import numpy as np
 import pytest
 
 cp = pytest.importorskip("paper_2303_05599_amd")
@@ -59,3 +61,38 @@ KEPT = 2 * (64 << 20)  # blocks that wait for the next call, whatever the number
 def test_initial_condition(N, sheets, prec, nc):
     first, others = held_by_calls(lambda c: c.init_mv(), N, sheets, prec, nc)
     assert first <= KEPT + SLACK and others <= SLACK
+
+
+@pytest.mark.parametrize("N,prec,nc", [(96, cp.FP64, 3), (216, cp.FP32, 3), (324, cp.FP64, 2)])
+def test_state_exchange(N, prec, nc):
+    """Fields and particles read and installed; their chunks lie in memory that the context has anyway."""
+    def call(ctx):
+        ctx.init_mv()
+        st, P = ctx.state(), ctx.get_state(cp.STATE_PARTICLES)
+        ctx.load_state(st, 0, P)
+    first, others = held_by_calls(call, N, 1, prec, nc)
+    assert first <= KEPT + SLACK and others <= SLACK
+
+
+def test_threads():
+    """Contexts used side by side on threads of their own: initial conditions, steps and exchange as one after the other."""
+    sizes = [(48, 9, cp.FP64, 3), (96, 25, cp.FP64, 3), (96, 25, cp.FP32, 3), (144, 12, cp.FP64, 3), (128, 7, cp.FP64, 2), (216, 4, cp.FP32, 3)]
+
+    def work(size):
+        N, sheets, prec, nc = size
+        L = 6.0 * min(1.0, N / 64)
+        ctx = cp.Context(dict(N=N, L_fm=L, n_sheets=sheets, tau_max_fm=400 * L / N / 8, precision=prec, seed=5, n_colors=nc),
+                         dict(n=N * N // 3, mass_GeV=1.27, tau_form_fm=0.0, seed=4), stream=None)
+        for _ in range(2):
+            ctx.init_mv()
+            ctx.evolve(40 * L / N / 8 * (1 - 1e-12))
+            ctx.load_state(ctx.state(), ctx.n, ctx.get_state(cp.STATE_PARTICLES))
+        out = [ctx.get_state(k) for k in range(5)]
+        ctx.close()
+        return out
+
+    alone = [work(s) for s in sizes]
+    with concurrent.futures.ThreadPoolExecutor(len(sizes)) as ex:
+        together = list(ex.map(work, sizes))
+    for a, b in zip(alone, together):
+        assert all(np.array_equal(x, y) for x, y in zip(a, b))
