@@ -164,8 +164,9 @@ cpic_status cpic_step(cpic_ctx* ctx, int32_t n_steps);
  * moving particles starts with the reordering.  With the default launch, the
  * push of a step and the field update of the next share a launch inside a
  * graph on lattices where that pays (the same bits); it takes a third field
- * buffer set, allocated once 32 evolved steps (64 above 32 MB) pay for it.  A
- * no-op if already there. */
+ * buffer set, allocated once 32 evolved steps (64 above 32 MB) pay for it and
+ * only where a quarter of the device's memory stays free (else the steps are
+ * separate launches).  A no-op if already there. */
 cpic_status cpic_evolve(cpic_ctx* ctx, double tau_target_fm);
 
 /* Wait for the context's stream; reports CPIC_E_CELL_JUMP if any particle

@@ -668,8 +668,9 @@ static cpic_status eager_steps(cpic_ctx* c, int k)
 // second plaquette field are made here, once cpic_evolve has `steps` steps
 // behind and before it that pay for them (allocating and freeing 28 MB at 216^2
 // took 0.2 ms, the gain of 40 steps there, and 0.5 to 0.9 ms from 60 MB on, of 50 to 120;
-// 8 steps after a restart are faster without); without memory for them the steps
-// stay separate launches.
+// 8 steps after a restart are faster without); without memory for them, or where less
+// than a quarter of the device's would stay free (they are no reason for a program
+// with many contexts to run out of it), the steps stay separate launches.
 static int64_t pipeline_steps(size_t bytes) { return bytes <= (size_t)32 << 20 ? 32 : 64; }
 static bool pipelined(cpic_ctx* c, int k, int64_t steps)
 {
@@ -693,11 +694,16 @@ static bool pipelined(cpic_ctx* c, int k, int64_t steps)
     // a caller that captures this stream replays the graphs there are
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(c->st, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) return false;
-    // (relaxed: a capture on another stream of the process is left alone)
-    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
-    (void)hipThreadExchangeStreamCaptureMode(&mode);
-    const hipError_t e = hipMalloc(&c->fbuf[2], bytes);
-    (void)hipThreadExchangeStreamCaptureMode(&mode);
+    size_t avail = 0, total = 0;
+    hipError_t e = hipMemGetInfo(&avail, &total);
+    if (e == hipSuccess && avail < bytes + total / 4) e = hipErrorOutOfMemory;
+    if (e == hipSuccess) {
+        // (relaxed: a capture on another stream of the process is left alone)
+        hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+        (void)hipThreadExchangeStreamCaptureMode(&mode);
+        e = hipMalloc(&c->fbuf[2], bytes);
+        (void)hipThreadExchangeStreamCaptureMode(&mode);
+    }
     if (e == hipSuccess) {
         c->gpl2 = static_cast<char*>(c->fbuf[2]) + fbytes;
         return true;
@@ -1839,6 +1845,11 @@ template <typename T> static cpic_status tune_t(cpic_ctx* c, int reps, std::stri
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
     drop_graphs(c);
+    if (!c->cfg.pipe && c->fbuf[2]) {  // separate steps from here on: the third set is not needed
+        HIPCHK(c, hipStreamSynchronize(c->st), "tune");
+        (void)hipFree(c->fbuf[2]);
+        c->fbuf[2] = c->gpl2 = nullptr;
+    }
     return CPIC_OK;
 }
 

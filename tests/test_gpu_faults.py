@@ -100,8 +100,22 @@ def failed_workspace(cp, shim):
     check_same(ctx, make(cp, n_sheets=40))
 
 
+def failed_third_set(cp, shim):
+    """No memory for the third buffer set: the steps stay separate launches, without an error."""
+    ctx, ref = make(cp), make(cp)
+    shim.shim_fail(MALLOC, 0, ALL, 1 << 20)
+    k0 = shim.shim_calls(KERNEL)
+    evolve(ctx, 64)
+    assert shim.shim_calls(KERNEL) - k0 >= 32
+    shim.shim_fail(MALLOC, 0, 0, 0)
+    evolve(ctx, 40)
+    ctx.sync()
+    ref.step(104)
+    check_same(ctx, ref)
+
+
 @pytest.mark.gpu
-@pytest.mark.parametrize("scenario", [failed_graph_launch, tuner_keeps_the_faster_form, failed_workspace], ids=lambda f: f.__name__)
+@pytest.mark.parametrize("scenario", [failed_graph_launch, tuner_keeps_the_faster_form, failed_workspace, failed_third_set], ids=lambda f: f.__name__)
 def test_forced_failure(scenario, tmp_path):
     torch = pytest.importorskip("torch")
     if not torch.cuda.is_available():

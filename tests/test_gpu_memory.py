@@ -74,6 +74,31 @@ def test_state_exchange(N, prec, nc):
     assert first <= KEPT + SLACK and others <= SLACK
 
 
+def test_third_buffer_set():
+    """Taken by an evolve of many steps while a quarter of the device's memory stays free, and not otherwise."""
+    def run():
+        ctx = make(144, 1, cp.FP64, 3)
+        ctx.init_mv()
+        before = free()
+        ctx.evolve(64 * 6.0 / 144 / 8 * (1 - 1e-12))
+        ctx.sync()
+        assert ctx.n == 64
+        held, P = before - free(), ctx.get_state(cp.STATE_PARTICLES)
+        ctx.close()
+        return held, P
+    size = 144 * 144 * (68 + 8) * 8
+    held, P = run()
+    assert held >= size
+    avail, total = torch.cuda.mem_get_info()
+    filler = torch.empty(avail - total // 5, dtype=torch.uint8, device="cuda")
+    try:
+        held, Q = run()
+    finally:
+        del filler
+        torch.cuda.empty_cache()
+    assert held < size // 2 and np.array_equal(P, Q)
+
+
 def test_threads():
     """Contexts used side by side on threads of their own: initial conditions, steps and exchange as one after the other."""
     sizes = [(48, 9, cp.FP64, 3), (96, 25, cp.FP64, 3), (96, 25, cp.FP32, 3), (144, 12, cp.FP64, 3), (128, 7, cp.FP64, 2), (216, 4, cp.FP32, 3)]
