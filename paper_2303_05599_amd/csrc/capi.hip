@@ -484,6 +484,7 @@ extern "C" cpic_status cpic_init_mv(cpic_ctx* c)
         HIPCHK(c, hipStreamIsCapturing(c->st, &cap), "cpic_init_mv");
         if (cap != hipStreamCaptureStatusNone) return hip_fail(c, hipErrorStreamCaptureUnsupported, "cpic_init_mv");
     }
+    const OnDevice on(c);
     ICArgs a{};
     a.N = c->N;
     a.n_sheets = c->gp.n_sheets;
@@ -694,6 +695,7 @@ static bool pipelined(cpic_ctx* c, int k, int64_t steps)
     // a caller that captures this stream replays the graphs there are
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(c->st, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) return false;
+    const OnDevice on(c);
     size_t avail = 0, total = 0;
     hipError_t e = hipMemGetInfo(&avail, &total);
     if (e == hipSuccess && avail < bytes + total / 4) e = hipErrorOutOfMemory;
@@ -784,11 +786,12 @@ struct CaptureStream {
 static cpic_status build_graph(cpic_ctx* c, int from, int k, bool sorted, int tx, int ty, bool piped)
 {
     hipGraph_t g = nullptr;
-    CaptureStream on;
-    HIPCHK(c, on.open(c->st), "capture");
-    HIPCHK(c, hipStreamBeginCapture(on.st, hipStreamCaptureModeThreadLocal), "capture");
+    const OnDevice on(c);
+    CaptureStream cs;
+    HIPCHK(c, cs.open(c->st), "capture");
+    HIPCHK(c, hipStreamBeginCapture(cs.st, hipStreamCaptureModeThreadLocal), "capture");
     const hipStream_t st = c->st;
-    c->st = on.st;
+    c->st = cs.st;
     cpic_status s = CPIC_OK;
     if (sorted) {
         const hipError_t e = enqueue_sort(c, tx, ty);
@@ -802,7 +805,7 @@ static cpic_status build_graph(cpic_ctx* c, int from, int k, bool sorted, int tx
             s = dbl ? launch_one<double>(c, b, false) : launch_one<float>(c, b, false);
     }
     c->st = st;
-    hipError_t e = hipStreamEndCapture(on.st, &g);
+    hipError_t e = hipStreamEndCapture(cs.st, &g);
     if (s) { if (g) (void)hipGraphDestroy(g); return s; }
     if (e != hipSuccess) return hip_fail(c, e, "end capture");
     e = hipGraphInstantiate(&c->gexec[piped][sorted][from][k], g, nullptr, nullptr, 0);

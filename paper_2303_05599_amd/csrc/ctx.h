@@ -105,6 +105,21 @@ struct cpic_ctx {
 };
 
 namespace cpic {
+// A context's device, current for the time of a call that allocates (a caller may
+// have another one current by then).
+struct OnDevice {
+    int before = -1;
+    explicit OnDevice(const cpic_ctx* c)
+    {
+        int d = -1;
+        if (hipGetDevice(&d) == hipSuccess && d != c->device && hipSetDevice(c->device) == hipSuccess) before = d;
+    }
+    OnDevice(const OnDevice&) = delete;
+    ~OnDevice()
+    {
+        if (before >= 0) (void)hipSetDevice(before);
+    }
+};
 cpic_status fail(cpic_ctx* c, cpic_status code, const std::string& msg);
 cpic_status hip_fail(cpic_ctx* c, hipError_t e, const char* where);
 // reorder the particle records by cell if step c->n is a reordering point

@@ -231,11 +231,12 @@ template <typename T> bool describe(const cpic_ctx* c, int which, Part* p, T** a
 // larger (both idle between steps); pinned from the pool.
 struct Staging {
     cpic_ctx* c;
+    OnDevice on;
     PoolPins pins{};
     double* dev[2] = {nullptr, nullptr};
     size_t bytes = 0;
     bool done = false;  // the stream is idle
-    explicit Staging(cpic_ctx* ctx) : c(ctx) {}
+    explicit Staging(cpic_ctx* ctx) : c(ctx), on(ctx) {}
     Staging(const Staging&) = delete;
     hipError_t open(bool particles, size_t total)
     {

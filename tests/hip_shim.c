@@ -1,6 +1,6 @@
 /* Stands between libcpic and the HIP runtime in a test's own process (loaded before
  * both, globally): counts some calls, fails chosen ones from the host, and
- * answers elapsed times from a script.  No call is made that the library did
+ * answers elapsed times and the current device from a script.  No call is made that the library did
  * not make, and no failed call reaches the GPU. */
 #define _GNU_SOURCE
 #include <dlfcn.h>
@@ -26,6 +26,12 @@ void shim_elapsed(float before, long turn, float after)
     ms_after = after;
 }
 long shim_calls(int kind) { return calls[kind]; }
+/* the device that hipGetDevice names, and the allocations made while it was not 0 */
+static int device;
+static long elsewhere;
+void shim_set_device(int d) { device = d; }
+int shim_device(void) { return device; }
+long shim_elsewhere(void) { return elsewhere; }
 
 static void* real(const char* name)
 {
@@ -39,8 +45,19 @@ static int failing(int kind)
     return k >= fail_from[kind] && k < fail_to[kind];
 }
 
+int hipGetDevice(int* d)
+{
+    *d = device;
+    return 0;
+}
+int hipSetDevice(int d)
+{
+    device = d;
+    return 0;
+}
 int hipMalloc(void** p, size_t bytes)
 {
+    if (device) elsewhere++;
     static int (*f)(void**, size_t);
     if (!f) f = (int (*)(void**, size_t))real("hipMalloc");
     if (bytes >= fail_bytes && failing(MALLOC)) return 2; /* hipErrorOutOfMemory */
@@ -48,6 +65,7 @@ int hipMalloc(void** p, size_t bytes)
 }
 int hipHostMalloc(void** p, size_t bytes, unsigned flags)
 {
+    if (device) elsewhere++;
     static int (*f)(void**, size_t, unsigned);
     if (!f) f = (int (*)(void**, size_t, unsigned))real("hipHostMalloc");
     if (bytes >= fail_bytes && failing(HOST_MALLOC)) return 2;

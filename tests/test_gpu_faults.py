@@ -114,8 +114,24 @@ def failed_third_set(cp, shim):
     check_same(ctx, ref)
 
 
+def another_device_current(cp, shim):
+    """The caller has another device current: the context's memory still comes from its own, and the caller's choice stays."""
+    ctx, ref = make(cp, n_sheets=20, init=False), make(cp, n_sheets=20)
+    shim.shim_set_device(1)
+    ctx.init_mv()
+    evolve(ctx, 64)
+    got = state(ctx)
+    ctx.load_state(dict(zip(("U", "phi", "E", "pi"), got)), ctx.n, got[4])
+    evolve(ctx, 16)
+    ctx.sync()
+    assert shim.shim_device() == 1 and shim.shim_elsewhere() == 0
+    shim.shim_set_device(0)
+    ref.step(80)
+    check_same(ctx, ref)
+
+
 @pytest.mark.gpu
-@pytest.mark.parametrize("scenario", [failed_graph_launch, tuner_keeps_the_faster_form, failed_workspace, failed_third_set], ids=lambda f: f.__name__)
+@pytest.mark.parametrize("scenario", [failed_graph_launch, tuner_keeps_the_faster_form, failed_workspace, failed_third_set, another_device_current], ids=lambda f: f.__name__)
 def test_forced_failure(scenario, tmp_path):
     torch = pytest.importorskip("torch")
     if not torch.cuda.is_available():
@@ -131,6 +147,7 @@ if __name__ == "__main__":
     shim_ = ctypes.CDLL(sys.argv[2], mode=ctypes.RTLD_GLOBAL)   # before anything loads the runtime
     shim_.shim_fail.argtypes = [ctypes.c_int, ctypes.c_long, ctypes.c_long, ctypes.c_size_t]
     shim_.shim_elapsed.argtypes = [ctypes.c_float, ctypes.c_long, ctypes.c_float]
+    shim_.shim_elsewhere.restype = ctypes.c_long
     shim_.shim_calls.argtypes, shim_.shim_calls.restype = [ctypes.c_int], ctypes.c_long
     sys.path.insert(0, os.path.dirname(HERE))
     import paper_2303_05599_amd as cp_
