@@ -367,7 +367,8 @@ cpic_status cpic_set_launch(cpic_ctx* ctx, int32_t bx, int32_t by, int32_t xcd_r
  * helper wavefronts evaluate part of the colour fields at the particles' cells
  * while the owner wavefront rotates the charges, which shortens the chain of
  * dependent memory accesses per particle.  Default from n; cpic_tune times
- * all three. */
+ * all three.  They are the gather push's: beside light-like paths the call takes
+ * it, unless the caller or the tuner has chosen a mode. */
 cpic_status cpic_set_push_lanes(cpic_ctx* ctx, int32_t lanes);
 
 /* Where the push takes the colour fields at a particle's cell (the

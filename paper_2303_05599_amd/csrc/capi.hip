@@ -160,10 +160,11 @@ static int default_push_lanes(const cpic_ctx* c)
 // 91, 2.5 140 / 112, 324^2 at 1.1 38 / 42, 2.5 60 / 49).  Beside the light-like paths, which
 // need the table anyway, from 16384 particles on (FP32 96^2, 11060 particles 26.0 / 25.6;
 // 216^2, 23329: 34.0 / 32.1; 512^2, 26215: 106 / 93, 2621: 100 / 103).
+static bool dense(const cpic_ctx* c) { return 2 * c->np > 3 * (int64_t)c->V; }
 static bool default_push_table(const cpic_ctx* c)
 {
     if (c->nc != 3 || c->pp.color_update != CPIC_COLOR_ROTATE) return false;
-    return 2 * c->np > 3 * (int64_t)c->V || (c->jets && c->np >= 16384);
+    return dense(c) || (c->jets && c->np >= 16384);
 }
 
 extern "C" cpic_status cpic_create(const cpic_glasma_params* gp, const cpic_particle_params* pp, void* hip_stream,
@@ -1893,6 +1894,12 @@ extern "C" cpic_status cpic_set_push_lanes(cpic_ctx* c, int32_t lanes)
         return fail(c, CPIC_E_INVALID, "cpic_set_push_lanes: 1, 2, 4 or 8");
     if (c->nc == 2 && lanes != 1) return fail(c, CPIC_E_INVALID, "cpic_set_push_lanes: the SU(2) push takes 1");
     HIPCHK(c, hipStreamSynchronize(c->st), "set push lanes");
+    // the lanes are the gather push's: the force table, where it is the default only
+    // because the light-like paths read it, gives way to the choice
+    if (!c->push_set && c->push_table && !dense(c)) {
+        c->push_table = false;
+        set_store_policy(c);
+    }
     c->push_set = true;
     c->tpp = lanes;
     c->pblocks = c->np > 0 ? push_blocks((int)c->np, lanes) : 0;
