@@ -93,15 +93,17 @@ struct LaunchCfg {
 };
 // The field update of a new context, by lattice size (both precisions).  Up to
 // 384^2 the chip is short of wavefronts and four of them share 64 sites; above
-// that, one thread per site, in tiles of 64 x 8 where they fill the 256 CUs in
-// one or two whole rounds (one such workgroup per CU: a partly filled last
-// round leaves most CUs idle, and with more rounds two smaller workgroups per CU
-// overlap staging and arithmetic better), else 64 x 4.  Measured per step, FP64,
-// particles at 0.35 per site, four wavefronts per 64 sites / 64 x 8 / 64 x 4:
-// 384^2 70.2 / 81.0 / 72.7 us, 432^2 81.6 / 87.4 / 81.6, 486^2 103.6 / 106.4 /
-// 104.2, 512^2 123.0 / 110.0 / 110.9, 576^2 168.2 / 148.7 / 146.3, 768^2 313.5 /
-// 294.2 / 283.2, 1024^2 557.2 / 525.4 / 515.6; FP32: 384^2 46.3 / 50.0 / 47.9,
-// 512^2 66.2 / 63.4 / 63.7, 864^2 208.7 / 182.3 / 175.2.
+// that, one thread per site in tiles of 64 x 4.  Tiles of 64 x 8 (in FP64 one workgroup
+// per CU: a round of them is 256 x 512 sites, and a partly filled last one leaves
+// most CUs idle) only where the sites fill 95 % of two rounds; with more rounds two
+// smaller workgroups per CU overlap staging and arithmetic better.  Of the lattices the
+// library takes that is 512^2.  Measured per step of separate launches, FP64, 64 x 8 / 64 x 4, at
+// 0.05, 0.35 and 1 particle per site: 432^2 (71 % of two rounds) 67.9 / 61.8, 79.6 / 73.5,
+// 105.5 / 99.8 us; 486^2 (90 %) 78.3 / 76.7, 100.0 / 99.8, 132.3 / 132.5; 512^2 84.1 / 89.3,
+// 102.7 / 105.9, 141.6 / 145.6; 576^2 (84 % of three) 130.3 / 124.4, 143.2 / 134.5, 197.9 / 204.3;
+// at 0.35: 768^2 286 / 278, 1024^2 (eight whole rounds) 465 / 455; FP32 432^2 48.1 / 46.5, 512^2
+// 57.7 / 57.4, 1024^2 268 / 262.  Four wavefronts per 64 sites / 64 x 4, FP64: 384^2 70.2 /
+// 72.7 us, 432^2 81.6 / 81.6, 512^2 123.0 / 110.9; FP32: 384^2 46.3 / 47.9, 512^2 66.2 / 63.7.
 inline void default_field_launch(int N, LaunchCfg* cfg)
 {
     cfg->split = 3;
@@ -113,7 +115,8 @@ inline void default_field_launch(int N, LaunchCfg* cfg)
         return;
     }
     const int tiles = ((N + 63) / 64) * ((N + 7) / 8);
-    if (tiles == 256 || tiles == 512) cfg->by = 8;
+    constexpr int two_rounds = 2 * 256;
+    if (tiles <= two_rounds && N * N >= 0.95 * two_rounds * 512) cfg->by = 8;
 }
 
 struct PushArgs {

@@ -1,4 +1,4 @@
-"""Lanes chosen by the caller take effect in whatever order the calls come."""
+"""The launch a context starts with, and lanes chosen by the caller in whatever order the calls come."""
 import pytest
 
 cp = pytest.importorskip("paper_2303_05599_amd")
@@ -34,3 +34,12 @@ def test_lanes_and_paths(n, calls, mode):
     ctx.step(3)
     ctx.sync()
     ctx.close()
+
+
+@pytest.mark.parametrize("N,by", [(384, 4), (432, 4), (486, 4), (512, 8), (576, 4), (1024, 4)])
+def test_default_tiles(N, by):
+    for prec in (cp.FP64, cp.FP32):
+        ctx = cp.Context(dict(N=N, L_fm=6.0, n_sheets=1, tau_max_fm=0.1, precision=prec))
+        launch = ctx.get_launch()
+        assert (launch["variant"], launch["bx"], launch["by"]) == (3, 64, by)
+        ctx.close()
