@@ -104,6 +104,29 @@ def plan_steps(steps, warmup, n_form, n_max=1024):
     return w, min(128, spare)
 
 
+def capture_graphs(ctx, steps, n_max=1024):
+    """cpic_evolve replays one graph per stretch between reordering points
+    (multiples of 16).  The timed region starts four steps before such a
+    point: 4 steps, some 16s and a remainder.  The same pattern is run untimed from the
+    same alignment, which captures every graph the timed region replays.
+    Pipelined stretches of 4 and 16 steps end in the other one of two
+    buffers, so that the pattern holds two or three 16s where the timed region
+    holds more, as its number is even or odd, and is run twice: the timed
+    region then starts from a buffer that one of the passes started from.
+    (Events too short for that take one 16 and one pass; a few captures
+    among several hundred timed steps.)"""
+    def align():
+        ctx.step((SORT_EVERY - 4 - ctx.n % SORT_EVERY) % SORT_EVERY)
+    n16, rest = max(steps - 4, 0) // SORT_EVERY, max(steps - 4, 0) % SORT_EVERY
+    pre, passes = min(steps, 4) + SORT_EVERY * min(n16, 2 + n16 % 2) + rest, 2
+    if ctx.n + passes * (pre + 15) + 15 + 48 + steps > n_max:
+        pre, passes = min(steps, 4) + SORT_EVERY * min(n16, 1) + rest, 1
+    align()
+    for _ in range(passes):
+        ctx.evolve((ctx.n + pre) * DTAU_FM * (1 - 1e-12))
+        align()
+
+
 def run_event(precision, steps, warmup, tune=True, particles=None, jets=False, n_colors=3, fixed=None, nt=None,
               push=None):
     """One 512^2 event: IC (timed separately), warm-up steps at least to the
@@ -126,7 +149,8 @@ def run_event(precision, steps, warmup, tune=True, particles=None, jets=False, n
     ctx.init_mv()
     t_ic = time.perf_counter() - t0
     w, n_kt = plan_steps(steps, warmup, formation_step(p))
-    ctx.step(w)
+    # (from graphs, as the timed region: what a long evolution sets up is there before it)
+    ctx.evolve(w * DTAU_FM * (1 - 1e-12))
     ctx.sync()
     if fixed:
         ctx.set_launch(fixed[0], fixed[1], 1, 1, 3)
@@ -149,15 +173,7 @@ def run_event(precision, steps, warmup, tune=True, particles=None, jets=False, n
     if jets:
         tm.update(ctx.jets_timing())
     ctx.set_timing(False)
-    # graph capture: cpic_evolve replays one graph per stretch between
-    # reordering points (multiples of 16).  The timed region starts four steps
-    # before such a point; the same stretch pattern (4, 16, the remainder) is
-    # run once untimed from the same alignment, which captures every graph the
-    # timed region replays
-    ctx.step((SORT_EVERY - 4 - ctx.n % SORT_EVERY) % SORT_EVERY)
-    pre = steps if steps <= 4 + SORT_EVERY else 4 + SORT_EVERY + (steps - 4) % SORT_EVERY
-    ctx.evolve((ctx.n + pre) * DTAU_FM * (1 - 1e-12))
-    ctx.step((SORT_EVERY - 4 - ctx.n % SORT_EVERY) % SORT_EVERY)
+    capture_graphs(ctx, steps)
     # a region shorter than the drift watchdog's interval starts where it holds
     # no check (one in WATCH_EVERY steps, about 40 us at this size): its rate
     # is then the steady one, as in a long region, where the checks amortise
