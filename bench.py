@@ -127,6 +127,16 @@ def capture_graphs(ctx, steps, n_max=1024):
         align()
 
 
+def skip_watch(ctx, steps):
+    """A region shorter than the drift watchdog's interval starts where it holds
+    no check (one in WATCH_EVERY steps, about 40 us at this size): its rate
+    is then the steady one, as in a long region, where the checks amortise.  Three moves
+    reach every place between two checks; a region of 52 steps or more holds one anyway."""
+    for _ in range(3):
+        if steps < WATCH_EVERY and (ctx.n + steps) // WATCH_EVERY > ctx.n // WATCH_EVERY:
+            ctx.step(SORT_EVERY)
+
+
 def run_event(precision, steps, warmup, tune=True, particles=None, jets=False, n_colors=3, fixed=None, nt=None,
               push=None):
     """One 512^2 event: IC (timed separately), warm-up steps at least to the
@@ -174,11 +184,7 @@ def run_event(precision, steps, warmup, tune=True, particles=None, jets=False, n
         tm.update(ctx.jets_timing())
     ctx.set_timing(False)
     capture_graphs(ctx, steps)
-    # a region shorter than the drift watchdog's interval starts where it holds
-    # no check (one in WATCH_EVERY steps, about 40 us at this size): its rate
-    # is then the steady one, as in a long region, where the checks amortise
-    while steps < WATCH_EVERY and (ctx.n + steps) // WATCH_EVERY > ctx.n // WATCH_EVERY:
-        ctx.step(SORT_EVERY)
+    skip_watch(ctx, steps)
     # the samples taken so far are summed now, so that the readout in the
     # timed region reduces only the samples of the timed steps
     ctx.observables()

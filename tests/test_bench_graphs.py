@@ -38,8 +38,9 @@ def test_timed_region_captures_nothing(piped):
                 w, n_kt = bench.plan_steps(steps, 5 + first, 69)
                 ctx = Event(w + n_kt, cur, piped)
                 bench.capture_graphs(ctx, steps)
-                while steps <= 51 and (ctx.n + steps) // bench.WATCH_EVERY > ctx.n // bench.WATCH_EVERY:
-                    ctx.step(bench.SORT_EVERY)
+                n = ctx.n
+                bench.skip_watch(ctx, steps)
+                assert ctx.n <= n + 48 and (steps > 51 or ctx.n // 64 == (ctx.n + steps) // 64)
                 assert ctx.n + steps <= 1024
                 ctx.captured = 0
                 ctx.evolve((ctx.n + steps) * bench.DTAU_FM * (1 - 1e-12))
