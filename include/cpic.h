@@ -11,7 +11,7 @@
  *     failure; nothing aborts.  cpic_last_error() gives a message.
  *   - A context owns all device memory it allocates and frees it in
  *     cpic_destroy().  Memory that a call needs only while it runs is shared by
- *     all contexts of the process: up to two blocks of 64 MiB, and 32 MiB of
+ *     all contexts of the process: up to 256 MiB, and 32 MiB of
  *     pinned host memory, stay allocated between calls, until the last context
  *     is destroyed.  Host buffers passed in are owned by the caller; the
  *     library reads/writes them only during the call, after synchronising
@@ -147,9 +147,9 @@ cpic_status cpic_create(const cpic_glasma_params* glasma, const cpic_particle_pa
  * Particles: positions uniform, |p_T| and azimuth as configured, eta = p^eta = 0.
  * Resets the step counter and the recorded samples.  Runs on the GPU in double
  * precision and synchronises.  It works in the field buffers and in device memory
- * for the time of the call (up to 64 MiB for the spectral planes, and
- * Wilson lines that do not fit into the buffers); without that memory it fails and
- * the state stays.  CPIC_E_IC_NEWTON if a link did not converge. */
+ * for the time of the call (spectral planes, and Wilson lines and links that
+ * do not fit into the buffers: up to 256 MiB, or 302 MB at 1024^2 in single precision);
+ * without that memory it fails and the state stays.  CPIC_E_IC_NEWTON if a link did not converge. */
 cpic_status cpic_init_mv(cpic_ctx* ctx);
 
 /* Advance n_steps leapfrog steps (Sec. II.A) with the particle push at each

@@ -495,14 +495,19 @@ extern "C" cpic_status cpic_init_mv(cpic_ctx* c)
     a.uvhat = c->gp.uv_GeV > 0 ? c->gp.uv_GeV * c->a_gev : 0.0;
     a.tol = 1e-14;
     a.maxit = 50;
-    // It works in the buffer sets, whose state it replaces (the new one goes to the
-    // first, from the links on), and allocates only what does not fit there.
+    // It works in the buffer sets, whose state it replaces, and takes from the pool only
+    // what does not fit there.  The new state goes to the first set from the links on; in
+    // single precision its links are rounded there last of all, from double ones that
+    // may not lie in their place.
     const size_t fbytes = (size_t)c->rps * c->V * c->tsz;
+    const size_t links = c->prec == CPIC_FP32 ? (size_t)(c->nc == 2 ? 8 : 36) * c->V * c->tsz : 0;
     ICScratch mem(c->device);
     ICWork w{};
-    mem.lend(c->fbuf[2], fbytes, true);
-    mem.lend(c->fbuf[1], fbytes, true);
-    mem.lend(c->fbuf[0], fbytes, false);
+    mem.lend(c->fbuf[2], fbytes, ICScratch::kAll);
+    mem.lend(c->fbuf[1], fbytes, ICScratch::kAll);
+    mem.lend(c->fbuf[0], links, ICScratch::only(ICScratch::kThroughout) | ICScratch::only(ICScratch::kBefore));
+    const size_t rest = std::min(fbytes, (links + 255) / 256 * 256);
+    mem.lend(static_cast<char*>(c->fbuf[0]) + rest, fbytes - rest, ICScratch::only(ICScratch::kBefore));
     HIPCHK(c, ic_reserve(a, c->nc, c->prec == CPIC_FP32, mem, &w), "cpic_init_mv");
     c->initialised = false;  // until the new state is there
     const cpic_status s = enqueue_init(c, a, w);

@@ -505,6 +505,11 @@ __global__ void join_segments_kernel(Segments seg, int nseg, int V, int fresh, d
     }
 }
 
+// the double-precision links along x and y
+struct Links {
+    double *x, *y;
+};
+
 // the pure-gauge link U^X_i(x) = V(x) V(x+i)^+ = (V^+(x))^+ V^+(x+i) of sites s and s+i
 __device__ __forceinline__ m3<double> pure_link(const double* Vdag, int s, int si, int V)
 {
@@ -651,7 +656,7 @@ __device__ __forceinline__ void jacobian(const m3<double>& M, double (&J)[8][8])
 // M ~ 2, a dominant diagonal).  Eight general products and a pivoted elimination ->
 // this: 32^2 37.8 -> 22.0 us, 96^2 28.2 -> 15.8, 384^2 123 -> 78, 1024^2 764 -> 470.
 __global__ __launch_bounds__(128) void links_kernel(const double* __restrict__ VA, const double* __restrict__ VB, int N, double tol,
-                             int maxit, double* U, int* fails)
+                             int maxit, Links U, int* fails)
 {
     const int V = N * N;
     const int id = blockIdx.x * blockDim.x + threadIdx.x;
@@ -685,13 +690,13 @@ __global__ __launch_bounds__(128) void links_kernel(const double* __restrict__ V
         if (xmax < 1e-15) { ok = true; break; }
     }
     if (!ok) atomicAdd(fails, 1);
-    stM(U + (size_t)i * 18 * V, s, V, u);
+    stM(i == 0 ? U.x : U.y, s, V, u);
 }
 
 // pi(x) = (1/2) sum_i Proj[(U_i(x)-1)(U^B_i(x)^+ - U^A_i(x)^+) + (U_i(x-i)^+ - 1)(U^B_i(x-i) - U^A_i(x-i))]
 template <typename T>
 __global__ __launch_bounds__(128) void pi0_kernel(const double* __restrict__ VA, const double* __restrict__ VB,
-                                                  const double* __restrict__ U, int N, T* pi)
+                                                  Links U, int N, T* pi)
 {
     const int V = N * N;
     const int s = blockIdx.x * blockDim.x + threadIdx.x;
@@ -700,8 +705,8 @@ __global__ __launch_bounds__(128) void pi0_kernel(const double* __restrict__ VA,
     for (int c = 0; c < 9; c++) acc.e[c] = {0, 0};
     for (int i = 0; i < 2; i++) {
         const int sm = site_down(s, i, N), sp = site_up(s, i, N);
-        const size_t o = (size_t)i * 18 * V;
-        m3<double> u = ldM(U + o, s, V), a = pure_link(VA, s, sp, V), b = pure_link(VB, s, sp, V);
+        const double* const Ui = i == 0 ? U.x : U.y;
+        m3<double> u = ldM(Ui, s, V), a = pure_link(VA, s, sp, V), b = pure_link(VB, s, sp, V);
         m3<double> L = u, R;
         L.e[0].re -= 1; L.e[4].re -= 1; L.e[8].re -= 1;
         for (int c = 0; c < 9; c++) {  // U^B^+ - U^A^+
@@ -709,7 +714,7 @@ __global__ __launch_bounds__(128) void pi0_kernel(const double* __restrict__ VA,
             R.e[c] = {b.e[tr].re - a.e[tr].re, -(b.e[tr].im - a.e[tr].im)};
         }
         m3<double> P1 = mul(L, R);
-        u = ldM(U + o, sm, V); a = pure_link(VA, sm, s, V); b = pure_link(VB, sm, s, V);
+        u = ldM(Ui, sm, V); a = pure_link(VA, sm, s, V); b = pure_link(VB, sm, s, V);
         L = adj(u);
         L.e[0].re -= 1; L.e[4].re -= 1; L.e[8].re -= 1;
         for (int c = 0; c < 9; c++) R.e[c] = {b.e[c].re - a.e[c].re, b.e[c].im - a.e[c].im};
@@ -786,17 +791,17 @@ template <typename T> __global__ void particles_kernel(PartICArgs a, T* r, int* 
     cell[np + p] = ny >= N ? ny - N : ny;
 }
 
-__global__ void convert_kernel(const double* __restrict__ s, float* __restrict__ d, size_t n)
+// the links of both directions, n reals each, rounded
+__global__ void convert_kernel(const double* __restrict__ x, const double* __restrict__ y, float* __restrict__ d, size_t n)
 {
     const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) d[i] = (float)s[i];
+    if (i < 2 * n) d[i] = (float)(i < n ? x[i] : y[i - n]);
 }
 
 // ------------------------------------------------------------------ drivers
-static hipError_t convert_to_float(const double* src, float* dst, size_t n, hipStream_t st)
+static hipError_t convert_to_float(const double* x, const double* y, float* dst, size_t n, hipStream_t st)
 {
-    if (!n) return hipSuccess;
-    hipLaunchKernelGGL(convert_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, src, dst, n);
+    hipLaunchKernelGGL(convert_kernel, dim3((unsigned)((2 * n + 255) / 256)), dim3(256), 0, st, x, y, dst, n);
     return hipGetLastError();
 }
 
@@ -811,52 +816,51 @@ static hipError_t convert_to_float(const double* src, float* dst, size_t n, hipS
 // to the next.
 constexpr size_t kChunkBytes = (size_t)64 << 20;
 
-void ICScratch::lend(void* base, size_t bytes, bool to_end)
+static size_t padded(size_t bytes) { return (bytes + 255) / 256 * 256; }
+void ICScratch::lend(void* base, size_t bytes, unsigned spans)
 {
-    if (base) ranges[nranges++] = {static_cast<char*>(base), bytes / 256 * 256, to_end};
+    if (base) ranges[nranges++] = {static_cast<char*>(base), bytes, spans};
 }
-int ICScratch::want(size_t bytes, bool to_end)
+int ICScratch::want(size_t bytes, Span span)
 {
     Part& p = parts[nparts++];
-    p = {(bytes + 255) / 256 * 256, nullptr};
+    p = {bytes, span, nullptr};
     for (int k = 0; k < nranges && !p.at; k++) {
         Range& r = ranges[k];
-        if (p.bytes > r.left || (to_end && !r.to_end)) continue;
+        if (bytes > r.left || !(r.spans & only(span))) continue;
         p.at = r.base;
-        r.base += p.bytes;
-        r.left -= p.bytes;
+        r.base += std::min(padded(bytes), r.left);
+        r.left -= std::min(padded(bytes), r.left);
     }
     return nparts - 1;
 }
+int ICScratch::room(size_t bytes, Span span) const
+{
+    int n = 0;
+    for (int k = 0; k < nranges; k++)
+        if (ranges[k].spans & only(span)) n += (int)(ranges[k].left / padded(bytes));
+    return n;
+}
 hipError_t ICScratch::make()
 {
-    for (;;) {
-        // the largest part left starts a block, the others that fit into it follow
-        int first = -1;
-        for (int k = 0; k < nparts; k++)
-            if (!parts[k].at && (first < 0 || parts[k].bytes > parts[first].bytes)) first = k;
-        if (first < 0) return hipSuccess;
-        bool in[32] = {};
-        size_t total = parts[first].bytes;
-        in[first] = true;
-        for (int k = 0; k < nparts; k++)
-            if (!parts[k].at && !in[k] && total + parts[k].bytes <= kPoolBlockBytes) {
-                in[k] = true;
-                total += parts[k].bytes;
-            }
-        CK(pool_take(device, total, &blocks[nblocks]));
-        char* at = static_cast<char*>(blocks[nblocks++].p);
-        for (int k = 0; k < nparts; k++)
-            if (in[k]) {
-                parts[k].at = at;
-                at += parts[k].bytes;
-            }
-    }
+    // what is needed before the links and what is from then on share their memory
+    size_t sum[3] = {0, 0, 0};
+    for (int k = 0; k < nparts; k++)
+        if (!parts[k].at) sum[parts[k].span] += padded(parts[k].bytes);
+    const size_t total = sum[kThroughout] + std::max(sum[kBefore], sum[kAfter]);
+    if (!total) return hipSuccess;
+    CK(pool_take(device, total, &block));
+    char* at[3];
+    at[kThroughout] = static_cast<char*>(block.p);
+    at[kBefore] = at[kAfter] = at[kThroughout] + sum[kThroughout];
+    for (int k = 0; k < nparts; k++)
+        if (!parts[k].at) {
+            parts[k].at = at[parts[k].span];
+            at[parts[k].span] += padded(parts[k].bytes);
+        }
+    return hipSuccess;
 }
-ICScratch::~ICScratch()
-{
-    for (int k = 0; k < nblocks; k++) pool_give(device, blocks[k]);
-}
+ICScratch::~ICScratch() { pool_give(device, block); }
 
 hipError_t ic_reserve(const ICArgs& a, int n_colors, bool double_links, ICScratch& mem, ICWork* w)
 {
@@ -873,12 +877,19 @@ hipError_t ic_reserve(const ICArgs& a, int n_colors, bool double_links, ICScratc
     // afterwards) so that the workgroups fill the chip in whole rounds: the
     // register file holds 16 of their wavefronts per CU.  The cost is counted in
     // sheets: the rounds times a segment's sheets and its start and end, and the
-    // joining.  (384^2: four segments 37 sheets long instead of one of 50.)
+    // joining.  (384^2: four segments 37 sheets long instead of one of 50.)  Segments
+    // whose products fit neither the lent ranges nor, beside the planes, what the pool
+    // keeps are not considered.
+    const size_t mw = sizeof(double) * MW * V;
+    const int va = mem.want(mw, ICScratch::kThroughout), vb = mem.want(mw, ICScratch::kThroughout);
+    const int in_range = mem.room(mw, ICScratch::kBefore);
+    const size_t spare = std::max(kPoolBytes, double_links ? 2 * mw : 0) - std::min(per_sheet * chunk, kPoolBytes);
     const int RB = std::max(1, 256 / N), groups = (N + RB - 1) / RB;
     const int sites = RB * N, wt = std::min(512, (sites + 63) / 64 * 64), slots = 256 * (16 / (wt / 64));
     int seg_len = chunk;
     for (double best = 1e300, k = 1; k <= std::min(chunk, kMaxSegments); k++) {
         const int len = (chunk + (int)k - 1) / (int)k, nseg = (chunk + len - 1) / len;
+        if (nseg > 1 && nseg > in_range && (nseg - in_range) * mw > spare) continue;
         const double cost = ((groups * nseg + slots - 1) / slots) * (len + 0.7) + 0.1 * nseg;
         if (cost < best) {
             best = cost;
@@ -889,16 +900,18 @@ hipError_t ic_reserve(const ICArgs& a, int n_colors, bool double_links, ICScratc
     w->chunk = chunk;
     w->seg_len = seg_len;
     w->direct = nseg == 1 && chunk >= a.n_sheets;  // one segment: no joining
-    const size_t mw = sizeof(double) * MW * V;
-    const int va = mem.want(mw, true), vb = mem.want(mw, true), u = double_links ? mem.want(2 * mw, true) : -1;
     int seg[kMaxSegments];
-    for (int k = 0; k < nseg && !w->direct; k++) seg[k] = mem.want(mw, false);
-    const int K = mem.want(sizeof(double) * bd.nk * N, false), tw = mem.want(sizeof(d2) * 3 * N, false);
-    const int spec = mem.want(per_sheet * chunk, false);
+    for (int k = 0; k < nseg && !w->direct; k++) seg[k] = mem.want(mw, ICScratch::kBefore);
+    const int K = mem.want(sizeof(double) * bd.nk * N, ICScratch::kBefore);
+    const int tw = mem.want(sizeof(d2) * 3 * N, ICScratch::kBefore), spec = mem.want(per_sheet * chunk, ICScratch::kBefore);
+    const int ux = double_links ? mem.want(mw, ICScratch::kAfter) : -1, uy = double_links ? mem.want(mw, ICScratch::kAfter) : -1;
     CK(mem.make());
     w->VA = mem.at<double>(va);
     w->VB = mem.at<double>(vb);
-    if (double_links) w->U = mem.at<double>(u);
+    if (double_links) {
+        w->U[0] = mem.at<double>(ux);
+        w->U[1] = mem.at<double>(uy);
+    }
     for (int k = 0; k < nseg && !w->direct; k++) w->seg[k] = mem.at<double>(seg[k]);
     w->K = mem.at<double>(K);
     w->tw = mem.at<d2>(tw);
@@ -957,14 +970,14 @@ hipError_t ic_glasma(const ICArgs& a, const ICWork& w, const Fields<T>& out, int
     constexpr bool own = std::is_same<T, double>::value;  // the links are solved in place
     const int N = a.N, V = N * N;
     CK(wilson_lines<3>(a, w, st));
-    double* U = w.U;
-    if constexpr (own) U = out.U;
+    Links U = {w.U[0], w.U[1]};
+    if constexpr (own) U = {out.U, out.U + (size_t)18 * V};
     hipLaunchKernelGGL(links_kernel, dim3((2 * V + 127) / 128), dim3(128), 0, st, w.VA, w.VB, N, a.tol, a.maxit, U,
                        d_fails);
     hipLaunchKernelGGL(pi0_kernel<T>, dim3((V + 127) / 128), dim3(128), 0, st, w.VA, w.VB, U, N, out.pi);
     const size_t nz = (size_t)24 * V;  // phi (8V) and E (16V) are adjacent
     hipLaunchKernelGGL(zero_kernel<T>, dim3((unsigned)((nz + 255) / 256)), dim3(256), 0, st, out.phi, nz);
-    if constexpr (!own) CK(convert_to_float(U, out.U, (size_t)36 * V, st));
+    if constexpr (!own) CK(convert_to_float(U.x, U.y, out.U, (size_t)18 * V, st));
     return hipGetLastError();
 }
 template hipError_t ic_glasma<double>(const ICArgs&, const ICWork&, const Fields<double>&, int*, hipStream_t);
@@ -974,22 +987,20 @@ template hipError_t ic_glasma<float>(const ICArgs&, const ICWork&, const Fields<
 // tau = 0 links: W = U^A + U^B is a real multiple of an SU(2) element S, and
 // U = S^2 = W W / |W|^2 solves Proj[W (1 + U^+)] = 0 (W (1 + U^+) = W + W^+ |W|^0
 // is then a multiple of 1)
-__global__ void links2_kernel(const double* __restrict__ VA, const double* __restrict__ VB, int N, double* U)
+__global__ void links2_kernel(const double* __restrict__ VA, const double* __restrict__ VB, int N, Links U)
 {
     const int V = N * N;
     const int k = blockIdx.x * blockDim.x + threadIdx.x;
     if (k >= 2 * V) return;
     const int i = k / V, s = k - i * V, si = site_up(s, i, N);
-    const size_t o = (size_t)i * 4 * V;
     const q4<double> W = qadd(pure_link2(VA, s, si, V), pure_link2(VB, s, si, V));
     const double n2 = W.w * W.w + W.x * W.x + W.y * W.y + W.z * W.z;
     const q4<double> S2 = qmul(W, W);
-    stQ(U + o, s, V, {S2.w / n2, S2.x / n2, S2.y / n2, S2.z / n2});
+    stQ(i == 0 ? U.x : U.y, s, V, {S2.w / n2, S2.x / n2, S2.y / n2, S2.z / n2});
 }
 // pi(0) of the SU(3) kernel on quaternions
 template <typename T>
-__global__ void pi02_kernel(const double* __restrict__ VA, const double* __restrict__ VB, const double* __restrict__ U,
-                            int N, T* pi)
+__global__ void pi02_kernel(const double* __restrict__ VA, const double* __restrict__ VB, Links U, int N, T* pi)
 {
     const int V = N * N;
     const int s = blockIdx.x * blockDim.x + threadIdx.x;
@@ -997,10 +1008,10 @@ __global__ void pi02_kernel(const double* __restrict__ VA, const double* __restr
     q4<double> acc = {0, 0, 0, 0};
     for (int i = 0; i < 2; i++) {
         const int sm = site_down(s, i, N), sp = site_up(s, i, N);
-        const size_t o = (size_t)i * 4 * V;
-        const q4<double> P1 = qmul(qsub(ldQ(U + o, s, V), qone<double>()),
+        const double* const Ui = i == 0 ? U.x : U.y;
+        const q4<double> P1 = qmul(qsub(ldQ(Ui, s, V), qone<double>()),
                                    qsub(qadj(pure_link2(VB, s, sp, V)), qadj(pure_link2(VA, s, sp, V))));
-        const q4<double> P2 = qmul(qsub(qadj(ldQ(U + o, sm, V)), qone<double>()),
+        const q4<double> P2 = qmul(qsub(qadj(ldQ(Ui, sm, V)), qone<double>()),
                                    qsub(pure_link2(VB, sm, s, V), pure_link2(VA, sm, s, V)));
         acc = qadd(acc, qadd(P1, P2));
     }
@@ -1014,13 +1025,13 @@ hipError_t ic_glasma2(const ICArgs& a, const ICWork& w, const Fields2<T>& out, h
     constexpr bool own = std::is_same<T, double>::value;
     const int N = a.N, V = N * N;
     CK(wilson_lines<2>(a, w, st));
-    double* U = w.U;
-    if constexpr (own) U = out.U;
+    Links U = {w.U[0], w.U[1]};
+    if constexpr (own) U = {out.U, out.U + (size_t)4 * V};
     hipLaunchKernelGGL(links2_kernel, dim3((2 * V + 255) / 256), dim3(256), 0, st, w.VA, w.VB, N, U);
     hipLaunchKernelGGL(pi02_kernel<T>, dim3((V + 255) / 256), dim3(256), 0, st, w.VA, w.VB, U, N, out.pi);
     const size_t nz = (size_t)9 * V;  // phi (3V) and E (6V) are adjacent
     hipLaunchKernelGGL(zero_kernel<T>, dim3((unsigned)((nz + 255) / 256)), dim3(256), 0, st, out.phi, nz);
-    if constexpr (!own) CK(convert_to_float(U, out.U, (size_t)8 * V, st));
+    if constexpr (!own) CK(convert_to_float(U.x, U.y, out.U, (size_t)4 * V, st));
     return hipGetLastError();
 }
 template hipError_t ic_glasma2<double>(const ICArgs&, const ICWork&, const Fields2<double>&, hipStream_t);

@@ -340,7 +340,7 @@ constexpr int kGatherSortTileX = 32, kGatherSortTileY = 16;
 constexpr int kSortEvery = 16;  // steps between reorderings of moving particles (measured best of 8, 16, 32, 64)
 
 // ---- memory for the time of one call (pool.hip)
-constexpr size_t kPoolBlockBytes = (size_t)64 << 20;  // larger blocks are not kept
+constexpr size_t kPoolBytes = (size_t)256 << 20;  // kept at most
 struct PoolBlock {
     void* p = nullptr;
     size_t bytes = 0;
@@ -369,29 +369,35 @@ struct ICArgs {
     int maxit;
 };
 // Device memory an initial condition works in, for the time of one call: ranges lent
-// to it (buffer sets whose contents the call replaces or does not need) and blocks of
-// the pool for what does not fit there, at most 64 MiB each where the parts allow.
+// to it (buffer sets whose contents the call replaces or does not need), and one block of
+// the pool for what does not fit there.
 struct ICScratch {
+    // when a part is in use: before the links are solved, from then on, or throughout
+    enum Span { kBefore, kAfter, kThroughout };
+    static constexpr unsigned kAll = 7;
+    static constexpr unsigned only(Span s) { return 1u << s; }
     struct Range {
         char* base;
         size_t left;
-        bool to_end;  // free until the call's last kernel, not only until the links are solved
+        unsigned spans;  // of the parts it may hold
     };
     struct Part {
         size_t bytes;
+        Span span;
         char* at;
     };
     int device;
-    Range ranges[3];
+    Range ranges[4];
     Part parts[32];
-    PoolBlock blocks[32];
-    int nranges = 0, nparts = 0, nblocks = 0;
+    PoolBlock block;
+    int nranges = 0, nparts = 0;
     explicit ICScratch(int dev) : device(dev) {}
     ICScratch(const ICScratch&) = delete;
     ~ICScratch();  // (the stream has to be idle)
-    void lend(void* base, size_t bytes, bool to_end);
-    int want(size_t bytes, bool to_end);  // a part's number
-    hipError_t make();                    // the parts have their places (256-byte aligned) from here on
+    void lend(void* base, size_t bytes, unsigned spans);
+    int want(size_t bytes, Span span);          // a part's number
+    int room(size_t bytes, Span span) const;    // how many more such parts fit into the lent ranges
+    hipError_t make();                          // the parts have their places (256-byte aligned) from here on
     template <typename T> T* at(int part) const { return reinterpret_cast<T*>(parts[part].at); }
 };
 // Where the parts of an initial condition lie and how its sheets are split
@@ -399,7 +405,7 @@ constexpr int kMaxSegments = 16;
 struct ICWork {
     double2 *tw, *spec;        // twiddle tables [3][N], spectral planes of a chunk
     double *K, *VA, *VB;       // Poisson factors, Wilson lines of the nuclei
-    double* U;                 // links in double precision (single-precision runs)
+    double* U[2];              // links in double precision (single-precision runs)
     double* seg[kMaxSegments]; // products of a segment's sheets
     int chunk, seg_len;
     bool direct;               // one segment, which is the Wilson line

@@ -5,11 +5,13 @@
 // Allocating fresh device memory costs more than the allocation itself (the first
 // pass over new pages): with a block of its own per call the initial condition and
 // read-back of a 144^2 event took 1345 us against 1263 with the block kept, a 384^2
-// one 6.69 ms against 6.30.  What is kept does not grow with the number of contexts: two
-// idle blocks of at most 64 MiB and two idle pairs of pinned chunks (of 8 MiB at most),
-// released with the last context.  Calls that run at the same time on several
-// threads get memory of their own.
+// one 6.69 ms against 6.30.  One block serves a call: releasing one takes about 0.3 ms,
+// whatever its size (four of 36 MiB: 0.82 ms, one of 144: 0.34).  What is kept does not
+// grow with the number of contexts: two idle blocks of 256 MiB together and two idle
+// pairs of pinned chunks (of 8 MiB at most), released with the last context.  Calls
+// that run at the same time on several threads get memory of their own.
 #include <mutex>
+#include <utility>
 
 #include "internal.h"
 
@@ -37,14 +39,17 @@ template <typename B> bool find(Idle<B> (&idle)[kIdle], int device, size_t bytes
     *fit = Idle<B>{};
     return true;
 }
-// the larger ones stay; returns what is to be released
-template <typename B> B keep(Idle<B> (&idle)[kIdle], int device, const B& b)
+// the larger ones stay, up to `most` bytes together; returns what is to be released
+template <typename B> B keep(Idle<B> (&idle)[kIdle], int device, const B& b, size_t most)
 {
     std::lock_guard<std::mutex> hold(g_lock);
     Idle<B>* at = &idle[0];
-    for (Idle<B>& i : idle)
+    size_t others = 0;
+    for (Idle<B>& i : idle) {
+        others += i.b.bytes;
         if (i.b.bytes < at->b.bytes) at = &i;
-    if (g_users <= 0 || at->b.bytes >= b.bytes) return b;
+    }
+    if (g_users <= 0 || at->b.bytes >= b.bytes || others - at->b.bytes + b.bytes > most) return b;
     const B gone = at->b;
     *at = Idle<B>{b, device};
     return gone;
@@ -78,7 +83,7 @@ hipError_t pool_take(int device, size_t bytes, PoolBlock* out)
 
 void pool_give(int device, PoolBlock b)
 {
-    if (b.bytes <= kPoolBlockBytes) b = keep(g_idle, device, b);
+    if (b.p) b = keep(g_idle, device, b, kPoolBytes);
     (void)hipFree(b.p);
 }
 
@@ -105,7 +110,7 @@ hipError_t pool_take_pins(int device, size_t bytes, PoolPins* out)
 }
 void pool_give_pins(int device, const PoolPins& p)
 {
-    release(keep(g_pins, device, p));
+    release(keep(g_pins, device, p, SIZE_MAX));
 }
 
 void pool_enter()
@@ -120,12 +125,8 @@ void pool_leave()
     {
         std::lock_guard<std::mutex> hold(g_lock);
         if (--g_users > 0) return;
-        for (int k = 0; k < kIdle; k++) {
-            gone[k] = g_idle[k];
-            pins[k] = g_pins[k];
-            g_idle[k] = Idle<PoolBlock>{};
-            g_pins[k] = Idle<PoolPins>{};
-        }
+        std::swap(gone, g_idle);
+        std::swap(pins, g_pins);
     }
     for (const auto& i : gone) (void)hipFree(i.b.p);
     for (const auto& i : pins) release(i.b);
