@@ -412,7 +412,8 @@ class Batch:
         self._chk(lib().cpic_batch_set_launch(self.h, bx, by, xcd_remap, push_lanes))
 
     def set_lanes(self, lanes):
-        """Launch lanes, 1 to 4: the launch groups dealt to that many concurrent streams (default 2; 3 in FP32)."""
+        """Launch lanes, 1 to 4: the launch groups dealt to that many concurrent streams (default 2; in FP32 3 where
+        events larger than a group do less than a third of the work and the group budget is not set)."""
         self._chk(lib().cpic_batch_set_lanes(self.h, lanes))
 
     def set_group_bytes(self, nbytes):
